@@ -203,10 +203,10 @@ def main():
 
     def packs_inline(c):
         # the search kernel packs the reads itself (no pack pass) when the
-        # batch is in input order and its tile plus one packing area per
-        # wave fit in LDS (160 KB less room for static variables); an area
-        # holds 64 slots of 2 * max_words + 1 16-byte pieces (codes and
-        # flags) and a queue of 128 set-aside read ids (kernels.h)
+        # batch is in input order and a tile plus one area per wave fit in
+        # LDS (160 KB less room for static variables); by this rule
+        # (tuned_lds_bytes in kernels.h) an area holds 64 slots of
+        # 2 * max_words + 1 16-byte pieces (codes and flags) and 128 read ids
         tile = ((1 << c.tile_levels) - 1) * 12
         area = (((64 * (2 * c.max_words + 1) + 4) * 6 + 8) + 15) // 16 * 16 + 4 * 128
         return (c.kernel == S.SA_KERNEL_TUNED and c.inline_pack == 1 and c.sort == 0 and

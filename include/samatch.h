@@ -51,9 +51,7 @@ enum {
 };
 
 /* Longest read the search kernels take (32 packed 64-bit words: the
- * paper's 1024-base queries, Section V).  Reads of up to 320 bases are
- * searched with their words in registers; longer ones are packed into LDS
- * and searched from there by a kernel of their own. */
+ * paper's 1024-base queries, Section V). */
 #define SA_MAX_READ 1024
 
 typedef struct sa_index sa_index;     /* host index: n, 2-bit packed text, int32 SA */
@@ -185,24 +183,22 @@ typedef struct {
                             (1..64): workgroup rank r takes blocks r, r+G, ... */
     int prefix_table;    /* tuned: 1 = start each search from the prefix table
                             (when the index has one), 0 = from the LDS tile     */
-    int inline_pack;     /* tuned, reads in input order (sort 0) given by CSR
-                            offsets: 1 = the search kernel converts its reads
-                            from ASCII itself (no separate pack pass), when its
-                            tile and packing areas fit in LDS (160 KB);
+    int inline_pack;     /* tuned, reads in input order (sort 0): 1 = the search
+                            kernel converts its reads from ASCII itself (no
+                            separate pack pass, one launch for the batch), when
+                            its tile and packing areas of 64 reads of 32 *
+                            max_words bases per wave fit in LDS (160 KB);
                             0 = a pack pass first                               */
-    int max_words;       /* tuned, with inline_pack: 64-bit words of a read the
-                            search kernel holds in registers, 5 or 10 (reads of
-                            up to 160 or 320 bases; longer ones go to the
-                            long-read kernel).  5 keeps fewer registers live so
-                            that more waves fit a compute unit; 0 = the
-                            index's default                                     */
-    int defer;           /* tuned, with inline_pack: a read whose binary searches
-                            take more than this many probes of row records is
-                            set aside and searched again, without a limit,
-                            together with 63 other such reads, so that one long
-                            search does not keep 63 lanes of its wave idle
-                            (0..1024; 0 = never; the index default is 3).
-                            Results never change.                              */
+    int max_words;       /* tuned, with inline_pack: 5 or 10, see inline_pack (the
+                            search kernel's own area does not depend on it);
+                            0 = the index's default                             */
+    int defer;           /* tuned, with inline_pack: not 0 = a read whose prefix-
+                            table bracket holds more than one row (or that has
+                            none) is set aside and searched together with other
+                            such reads, so that one long search does not keep the
+                            other lanes of its wave idle; 0 = every 64 reads are
+                            searched to their end before the next (0..1024; the
+                            index default is 3).  Results never change.         */
 } sa_match_cfg;
 
 /* Fill cfg with the index's current defaults. */

@@ -62,12 +62,16 @@ static hipError_t grow(void **p, size_t bytes) {
     return hipMalloc(p, bytes ? bytes : 16);
 }
 
-int Workspace::reserve(int64_t nreads) {
-    if (nreads <= cap) return SA_OK;
+int Workspace::reserve(int64_t nreads, bool pack_pass) {
+    hipError_t e;
+    if (!b.stats && (e = hipMalloc((void **)&b.stats, sizeof(unsigned long long) * kStatWords)) != hipSuccess)
+        return hip_fail(e, "scratch allocation");
+    for (hipEvent_t &ev_i : ev)
+        if (!ev_i && (e = hipEventCreate(&ev_i)) != hipSuccess) return hip_fail(e, "event creation");
+    if (!pack_pass || nreads <= cap) return SA_OK;
     drop_graphs();  // captured graphs point at the buffers about to be replaced
     const int64_t c = std::max<int64_t>(nreads, 1024);
     const int64_t nblocks = (c + kSortTile - 1) / kSortTile;
-    hipError_t e;
     if ((e = grow((void **)&b.qw, sizeof(uint64_t) * kWMax * (size_t)c)) != hipSuccess ||
         (e = grow((void **)&b.qlm, sizeof(int2) * (size_t)c)) != hipSuccess ||
         (e = grow((void **)&b.key[0], sizeof(uint32_t) * (size_t)c)) != hipSuccess ||
@@ -78,10 +82,6 @@ int Workspace::reserve(int64_t nreads) {
         return hip_fail(e, "scratch allocation");
     if (!b.digit_total && (e = hipMalloc((void **)&b.digit_total, sizeof(uint32_t) * 256)) != hipSuccess)
         return hip_fail(e, "scratch allocation");
-    if (!b.stats && (e = hipMalloc((void **)&b.stats, sizeof(unsigned long long) * kStatWords)) != hipSuccess)
-        return hip_fail(e, "scratch allocation");
-    for (hipEvent_t &ev_i : ev)
-        if (!ev_i && (e = hipEventCreate(&ev_i)) != hipSuccess) return hip_fail(e, "event creation");
     cap = c;
     return SA_OK;
 }
@@ -173,7 +173,7 @@ sa_match_cfg resolve_cfg(const sa_dindex *d, const sa_match_cfg *cfg) {
 
 bool packs_inline(const sa_match_cfg &c) {
     return c.kernel == SA_KERNEL_TUNED && c.inline_pack && c.sort == 0 &&
-           tuned_lds_bytes(c.tile_levels, c.count ? 256 : c.block, true, c.max_words) <= inline_lds_limit();
+           tuned_lds_bytes(c.tile_levels, c.count ? 256 : c.block, c.max_words) <= inline_lds_limit();
 }
 
 // Enqueue the whole device pipeline for one batch: pack, optional prefix
@@ -181,7 +181,7 @@ bool packs_inline(const sa_match_cfg &c) {
 // offsets) or give each read's end (reads scattered over d_reads).
 int enqueue_batch(sa_dindex *d, Workspace *ws, const uint8_t *d_reads, const int64_t *d_offs, const int64_t *d_ends,
                   int64_t nreads, sa_hit *d_out, hipStream_t s, const sa_match_cfg &c) {
-    int rc = ws->reserve(nreads);
+    int rc = ws->reserve(nreads, !packs_inline(c));
     if (rc) return rc;
     rc = enqueue_pipeline(d, ws->b, c.profile ? ws->ev : nullptr, d_reads, d_offs, d_ends, nreads, d_out, s, c);
     if (rc) return rc;
@@ -196,12 +196,10 @@ int enqueue_pipeline(sa_dindex *d, const BatchBuffers &b, const hipEvent_t *ev, 
     const bool prof = ev != nullptr;
     hipError_t e = hipSuccess;
     if (prof && (e = hipEventRecord(ev[0], s)) != hipSuccess) return hip_fail(e, "event record");
-    // reads in input order: the tuned kernel can pack them itself when its
-    // tile and the waves' packing areas fit in LDS
+    // reads in input order: one kernel packs and searches them
     const bool inl = packs_inline(c);
     if (inl) {
-        e = launch_clear_stats(b, s);
-        if (e != hipSuccess) return hip_fail(e, "stats clear launch");
+        if (c.count && (e = launch_clear_stats(b, s)) != hipSuccess) return hip_fail(e, "stats clear launch");
     } else {
         BucketTable bt = bucket_table(c);
         bt.keys = (c.kernel == SA_KERNEL_TUNED && c.sort) ? 1 : 0;
@@ -235,6 +233,10 @@ int enqueue_pipeline(sa_dindex *d, const BatchBuffers &b, const hipEvent_t *ev, 
     if (c.kernel == SA_KERNEL_PLAIN) {
         e = launch_search_plain(d->view, b, nreads, d_out, c.count != 0, s);
         if (e != hipSuccess) return hip_fail(e, "plain search launch");
+    } else if (inl) {
+        e = launch_search_reads(d->view, c.tile_levels, c.prefix_table, c.block, c.blocks_per_cu, d->cu_count, c.group,
+                                c.defer, b.stats, d_reads, d_offs, d_ends, nreads, d_out, c.count != 0, s);
+        if (e != hipSuccess) return hip_fail(e, "search launch");
     } else {
         // persistent workgroups; a batch too small to give each of them
         // `group` chunks of 64 reads takes smaller blocks, and no more
@@ -242,18 +244,19 @@ int enqueue_pipeline(sa_dindex *d, const BatchBuffers &b, const hipEvent_t *ev, 
         const int64_t chunks = (nreads + 63) / 64, gmax = std::max<int64_t>(1, (int64_t)d->cu_count * c.blocks_per_cu);
         const int group = (int)std::max<int64_t>(1, std::min<int64_t>(c.group, chunks / gmax));
         const int grid = (int)std::min<int64_t>(gmax, (chunks + group - 1) / group);
-        e = launch_search_tuned(d->view, c.tile_levels, c.prefix_table, c.block, grid, group, c.defer, b, order,
-                                inl ? d_reads : nullptr, inl ? d_offs : nullptr, inl ? d_ends : nullptr, nreads,
-                                inl ? c.max_words : kWMax, d_out, c.count != 0, s);
+        e = launch_search_packed(d->view, c.tile_levels, c.prefix_table, c.block, grid, group, b, order, nreads, d_out,
+                                 c.count != 0, s);
         if (e != hipSuccess) return hip_fail(e, "tuned search launch");
     }
-    // reads longer than kShortMax: their own kernel, over the tail of the sorted order
-    const uint32_t long_field = (long_read_key(c.nbuckets) >> key_shift) & key_mask;
-    e = launch_search_long(d->view, d_reads, d_offs, b, order, sorted_key, key_shift, key_mask, long_field,
-                           c.prefix_table, inl, 32 * (inl ? c.max_words : kWMax), inl ? d_ends : nullptr,
-                           (int)std::max<int64_t>(1, std::min<int64_t>((int64_t)d->cu_count * 8, (nreads + 63) / 64)),
-                           nreads, d_out, c.count != 0, s);
-    if (e != hipSuccess) return hip_fail(e, "long-read search launch");
+    if (!inl) {
+        // reads longer than kShortMax: their own kernel, over the tail of the sorted order
+        const uint32_t long_field = (long_read_key(c.nbuckets) >> key_shift) & key_mask;
+        e = launch_search_long(d->view, d_reads, d_offs, b, order, sorted_key, key_shift, key_mask, long_field,
+                               c.prefix_table,
+                               (int)std::max<int64_t>(1, std::min<int64_t>((int64_t)d->cu_count * 8, (nreads + 63) / 64)),
+                               nreads, d_out, c.count != 0, s);
+        if (e != hipSuccess) return hip_fail(e, "long-read search launch");
+    }
     if (prof && (e = hipEventRecord(ev[3], s)) != hipSuccess) return hip_fail(e, "event record");
     return SA_OK;
 }
@@ -265,7 +268,7 @@ int run_batch(sa_dindex *d, Workspace *ws, const uint8_t *d_reads, const int64_t
     // the null stream cannot be captured; profiling and counting need eager launches
     if (!c.use_graph || !s || c.profile || c.count)
         return enqueue_batch(d, ws, d_reads, d_offs, d_ends, nreads, d_out, s, c);
-    int rc = ws->reserve(nreads);  // no allocation may happen during capture
+    int rc = ws->reserve(nreads, !packs_inline(c));  // no allocation may happen during capture
     if (rc) return rc;
     for (GraphEntry &g : ws->graphs) {
         if (g.reads == d_reads && g.offs == d_offs && g.ends == d_ends && g.out == d_out && g.nreads == nreads &&
@@ -417,21 +420,22 @@ int make_dindex(int device, int64_t n, const std::vector<uint64_t> &packed, cons
     sa_match_cfg &c = d->defaults;
     std::memset(&c, 0, sizeof c);
     c.kernel = SA_KERNEL_TUNED;
-    // one workgroup of 16 waves per compute unit; with a prefix table the
-    // tile serves only reads with fewer than k leading bases
+    // three workgroups of 8 waves per compute unit (as many waves as fit, see
+    // kernels.h); with a prefix table the tile serves only reads with fewer
+    // than k leading bases
     c.tile_levels = std::min(d->view.ptab_k > 0 ? 8 : 10, d->tile_levels);
-    c.block = 1024;
-    c.blocks_per_cu = 1;
+    c.block = 512;
+    c.blocks_per_cu = 3;
     c.nbuckets = 1;
     c.bucket_edge[0] = SA_MAX_READ;
     // with the prefix table, reads in input order search as fast as sorted
     // ones and the sort is saved (MI355X, every workload measured)
     c.sort = d->view.ptab_k > 0 ? 0 : 1;
     c.use_graph = 0;
-    c.group = 4;
+    c.group = 1;
     c.prefix_table = d->view.ptab_k > 0 ? 1 : 0;
     c.inline_pack = 1;
-    c.max_words = kWMax;
+    c.max_words = kShortWords;
     c.defer = kDefaultDefer;
     *out = d.release();
     return SA_OK;
@@ -616,7 +620,7 @@ extern "C" int match_batch(const sa_dindex *dc, const char *reads, const int64_t
         most = std::max(most, r1 - r0);
         cuts.push_back(r1);
     }
-    if ((rc = ws->reserve(most))) return rc;  // no scratch growth between chunks
+    if ((rc = ws->reserve(most, !packs_inline(c)))) return rc;  // no scratch growth between chunks
     const size_t nchunks = cuts.size() - 1;
     auto finish = [&](size_t k) -> int {
         HostSlot &hs = ws->host[k & 1];

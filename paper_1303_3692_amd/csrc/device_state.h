@@ -51,7 +51,8 @@ struct HostSlot {
 
 struct Workspace {
     ~Workspace();
-    int reserve(int64_t nreads);
+    // counters and events, and with pack_pass the arrays that hold nreads packed reads
+    int reserve(int64_t nreads, bool pack_pass);
     void drop_graphs();
 
     // replayable launch sequences (at most kMaxGraphs, least recently used dropped)

@@ -9,10 +9,10 @@
 namespace samatch {
 
 constexpr int kWMax = 10;                 // packed words per read slot of the short-read path
-constexpr int kShortWords = 5;            // query words of the search kernel's register-light instance
+constexpr int kShortWords = 5;            // the smaller value of sa_match_cfg.max_words
 constexpr int kShortMax = kWMax * 32;     // longest read of the short-read path (320 bases)
 constexpr int kLongWords = SA_MAX_READ / 32;  // words of a read on the long-read path
-constexpr int kDefaultDefer = 3;          // probes before a read is set aside (sa_match_cfg.defer)
+constexpr int kDefaultDefer = 3;          // sa_match_cfg.defer: any value but 0 sets reads aside
 constexpr int kStatWords = 11;
 constexpr int kLongFlag = 10;
 constexpr int kMaxTileLevels = 13;        // 8191 nodes x 12 B = 96 KiB of LDS
@@ -122,27 +122,29 @@ hipError_t launch_pack(const uint8_t *reads, const int64_t *offs, const int64_t 
 // ping-pong slot that holds the result.
 hipError_t launch_sort(const BatchBuffers &b, int64_t nreads, int lo_bit, int hi_bit, int *which, hipStream_t s);
 
+// Search of a batch that launch_pack has packed (and launch_sort, when order
+// is not NULL, has put in order).
 // count = true runs the instrumented variant that fills b.stats.
 // group: 64-read chunks per block of the work split (see the kernel).
 // use_table: start LB searches from the prefix table (when the index has one).
-// offs not NULL: the kernel packs the reads itself from reads/offs (and
-// ends, when not NULL: read i is reads[offs[i] .. ends[i]), else CSR) in
-// input order (order must be NULL; no pack kernel runs, and b.stats must be
-// cleared before, see launch_clear_stats); the dynamic LDS is then
-// tuned_lds_bytes(tile_levels, block, true), which must not exceed
-// inline_lds_limit().
-// words: query words a read may hold (kShortWords or kWMax); with offs,
-// longer reads are left to launch_search_long (long_min = 32 * words).
-// defer (with offs, > 0): a read whose searches take more than this many
-// probes of row records is set aside and searched again, without a limit,
-// in a chunk of such reads (0: never; the counting variant never does).
-hipError_t launch_search_tuned(const DevIndex &ix, int tile_levels, int use_table, int block, int grid,
-                               int group, int defer, const BatchBuffers &b, const uint32_t *order, const uint8_t *reads,
-                               const int64_t *offs, const int64_t *ends, int64_t nreads, int words, void *out,
-                               bool count, hipStream_t s);
+hipError_t launch_search_packed(const DevIndex &ix, int tile_levels, int use_table, int block, int grid, int group,
+                                const BatchBuffers &b, const uint32_t *order, int64_t nreads, void *out, bool count,
+                                hipStream_t s);
 
-// Most dynamic LDS an inline-packing tuned kernel may take on the device
-// that prepare_kernels last ran on (0 before).
+// Search of a batch in input order straight from its ASCII bytes: reads of
+// any length up to SA_MAX_READ, read i at reads[offs[i] .. offs[i+1]), or
+// reads[offs[i] .. ends[i]) when ends is not NULL.  One launch; stats is
+// used only with count (and must be cleared before, see launch_clear_stats).
+// defer: 0 searches each turn's reads to their
+// end before the next; otherwise reads that need more than one comparison
+// wait in the wave's queue until kQueueReads of them can be searched together.
+hipError_t launch_search_reads(const DevIndex &ix, int tile_levels, int use_table, int block, int blocks_per_cu,
+                               int cus, int group, int defer, unsigned long long *stats,
+                               const uint8_t *reads, const int64_t *offs, const int64_t *ends, int64_t nreads,
+                               void *out, bool count, hipStream_t s);
+
+// Most dynamic LDS a search kernel may take on the device that
+// prepare_kernels last ran on (0 before).
 size_t inline_lds_limit();
 
 // Zero b.stats (the pack kernel does it otherwise).
@@ -157,13 +159,10 @@ hipError_t launch_search_plain(const DevIndex &ix, const BatchBuffers &b, int64_
 // long reads sort last, from the first row whose key bits
 // [key_shift, key_shift + bits(key_mask)) reach long_field.
 // Read i starts at reads[offs[i]] (offs holds the start array in gather mode).
-// lengths_from_offs: take each read's length from offs (and ends, when not
-// NULL) instead of the pack kernel's record (when the search kernel packed
-// its reads); a read is then long when it has more than long_min bases.
 hipError_t launch_search_long(const DevIndex &ix, const uint8_t *reads, const int64_t *offs, const BatchBuffers &b,
                               const uint32_t *order, const uint32_t *sorted_key, int key_shift, uint32_t key_mask,
-                              uint32_t long_field, int use_table, bool lengths_from_offs, int long_min,
-                              const int64_t *ends, int grid, int64_t nreads, void *out, bool count, hipStream_t s);
+                              uint32_t long_field, int use_table, int grid, int64_t nreads, void *out, bool count,
+                              hipStream_t s);
 
 // Suffix-tree search, one read per lane, reads in input order, each packed
 // into LDS by its wave (reads of up to SA_MAX_READ bases).
@@ -184,28 +183,53 @@ __host__ __device__ inline size_t tile_lds_bytes(int levels) {
 // Start of the per-wave packing areas after the tile (16-byte aligned).
 __host__ __device__ inline size_t inline_area_offset(int levels) { return (tile_lds_bytes(levels) + 15) & ~(size_t)15; }
 
-// 16-byte pieces of ASCII a wave's packing area holds in the search kernel
-// whose reads hold up to `words` query words: 64 slots of 2 * words + 1
-// pieces, each the most a read of up to 32 * words bases can touch; a span
-// of 64 consecutive such reads fits too.
-__host__ __device__ constexpr int inline_slot(int words) { return 2 * words + 1; }
-__host__ __device__ constexpr int inline_vec(int words) { return 64 * inline_slot(words); }
+// search_reads_kernel.  Registers are held to six waves per SIMD (78 used, no
+// spills), and a wave's LDS area is sized so that 24 waves fit a compute
+// unit: what a wave waits for is memory latency, so more waves in flight
+// mean more of the memory's rate.  250 Mbp, 64M reads of 150 bases on
+// MI355X: 5.52 ms at 16 waves, 5.16 at 24; held to 8 waves per SIMD it spills
+// 7 registers and was slower (5.08 against 5.00).
+constexpr int kSearchWavesPerSimd = 6;
 
-// Entries of a wave's queue of set-aside reads (it is drained at 64, and a
-// chunk adds at most 64).
-constexpr int kDeferCap = 128;
+// LDS of search_reads_kernel in 4-byte words: after the tile (when it is
+// staged), an area per wave (see WaveArea).
+struct InlineArea {
+    int first_word;   // of the first wave's area
+    int wave_words;   // per wave
+};
+// 16-byte pieces of ASCII (words of 16 codes) a wave stages at a time: 64
+// reads of 160 bases, with a piece more each for where they start, or any one
+// read.  Twice the pieces (64 reads of 320 bases, 16 waves per compute unit)
+// took 264 against 258 us for 2M reads of 250 bases, 227 against 197 us for
+// 20-250 bases: fewer turns, but fewer waves.
+constexpr int kStagePieces = 64 * 11;
+constexpr int kStageBadWords = kStagePieces / 32;  // a bit per piece
+static_assert(kStagePieces % 32 == 0 && kStagePieces >= SA_MAX_READ / 16 + 1, "any read fits a wave's staging area");
+// Queued reads a wave searches together at most, and the words of their
+// records.  32 of them, two lanes each, against 64: 250 Mbp / 64M reads 4.75
+// against 4.82 ms, 4M reads of 20-300 bases 379 against 392 us (4M x 100
+// 280 against 273); 16: 4.94 ms.
+constexpr int kQueueReads = 32;
+constexpr int kPoolWords = 768;
 
-// LDS bytes of such an area: a 4-byte code word and a 2-byte flag word per
-// piece (with four pieces of slack), then the queue of set-aside reads (4
-// bytes each), rounded up to 16 bytes.
-__host__ __device__ constexpr int inline_codes_bytes(int words) { return (((inline_vec(words) + 4) * 6 + 8) + 15) & ~15; }
-__host__ __device__ constexpr int inline_wave_bytes(int words) { return inline_codes_bytes(words) + 4 * kDeferCap; }
+// levels 0: no tile.
+inline InlineArea inline_area(int levels) {
+    InlineArea a;
+    a.first_word = levels ? (int)(inline_area_offset(levels) / 4) : 0;
+    a.wave_words = ((kStagePieces + 4) + kStageBadWords + kQueueReads + (kPoolWords + 2) + 3) & ~3;
+    return a;
+}
+inline size_t inline_lds_bytes(const InlineArea &a, int block) {
+    return 4 * ((size_t)a.first_word + (size_t)(block / 64) * (size_t)a.wave_words);
+}
 
-// Dynamic LDS of the tuned kernel: the tile, plus one packing area per wave
-// when it packs its reads itself.
-inline size_t tuned_lds_bytes(int levels, int block, bool inline_pack, int words = kWMax) {
-    return inline_pack ? inline_area_offset(levels) + (size_t)(block / 64) * inline_wave_bytes(words)
-                       : tile_lds_bytes(levels);
+// Whether a tile of `levels` and the packing areas of a workgroup fit the
+// LDS, by the measure that decides which settings pack in a pass of their
+// own (sa_match_cfg.inline_pack): 64 slots of 2 * words + 1 pieces of 6
+// bytes per wave and a queue of 128 reads.
+inline size_t tuned_lds_bytes(int levels, int block, int words) {
+    const size_t wave = ((((size_t)64 * (2 * (size_t)words + 1) + 4) * 6 + 8 + 15) & ~(size_t)15) + 4 * 128;
+    return inline_area_offset(levels) + (size_t)(block / 64) * wave;
 }
 
 }  // namespace samatch

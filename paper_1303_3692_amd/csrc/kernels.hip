@@ -26,10 +26,6 @@ namespace {
 
 constexpr uint32_t kHitExact = 1u;
 constexpr uint32_t kHitTooLong = 2u;
-// Internal result of a search that ran out of its probe budget (never
-// written out: the read is searched again without a limit).
-constexpr uint32_t kHitDeferred = 0x40000000u;
-constexpr int kNoBudget = 0x7FFFFFFF;
 
 // ------------------------------------------------------------------ helpers
 
@@ -228,6 +224,76 @@ __device__ __forceinline__ RowHead row_head(const RowRec *__restrict__ rows, int
     return h;
 }
 
+// Query words that lie in LDS and are read on demand (the W of the search
+// templates otherwise counts words held in registers).
+constexpr int kWordsInLds = 0;
+
+// compare_row for a query whose words are read from LDS as they are needed:
+// a loop over two query words at a time, so that it holds few registers and
+// stops at the first difference whatever the read's length.  The text words
+// of the second of them are loaded together with those of the first (one
+// latency for up to 96 bases), and words stay in registers from one turn
+// to the next: each text word is loaded once.  key0 holds the suffix's
+// first key_bases bases (at least 20, at most 32).
+template <class Q, class Cnt>
+__device__ __forceinline__ int compare_lds(const DevIndex &ix, const Q &q, int plen, int32_t p, uint64_t key0, int h,
+                                           int &lcp, Cnt &cnt, int key_bases) {
+    const int lim = min_i(plen, ix.n - p);
+    const int at_end = (lim == plen) ? 0 : 1;
+    lcp = lim;
+    int k = h >> 5;
+    if (k == 0) {
+        const uint64_t q0 = q[0], x = q0 ^ key0;
+        const int mm = x ? (int)(__clzll((long long)x) >> 1) : 32;
+        if (mm < min_i(key_bases, lim)) {
+            lcp = mm;
+            return q0 > key0 ? 1 : -1;
+        }
+        k = key_bases >= 32 ? 1 : 0;
+        if (lim <= key_bases) return at_end;
+    }
+    if ((k << 5) >= lim) return at_end;
+    const uint64_t *tp = ix.text + ((uint32_t)p >> 5) + k;
+    const uint32_t sh = ((uint32_t)p & 31u) << 1;
+    const uint32_t first = (uint32_t)p + ((uint32_t)k << 5);
+    u64x2_a8 a = load_u64x2(tp), b = a;
+    cnt.index_touch(tp, 16);
+    if ((k << 5) + 32 < lim) {
+        b = load_u64x2(tp + 2);
+        cnt.index_touch(tp + 2, 16);
+    }
+    int res = lim, sign = at_end;
+    for (;;) {
+        uint64_t t = (a.x << sh) | ((a.y >> 1) >> (63u - sh));
+        uint64_t w = q[k];
+        if (w == t) {
+            if ((k << 5) + 32 >= lim) break;
+            ++k;
+            t = (a.y << sh) | ((b.x >> 1) >> (63u - sh));
+            w = q[k];
+        }
+        if (w != t) {
+            const int mm = (k << 5) + (int)(__clzll((long long)(w ^ t)) >> 1);
+            if (mm < lim) {
+                res = mm;
+                sign = w > t ? 1 : -1;
+            }
+            break;
+        }
+        if ((k << 5) + 32 >= lim) break;
+        ++k;
+        tp += 2;
+        a = b;
+        if ((k << 5) + 32 < lim) {
+            b = load_u64x2(tp + 2);
+            cnt.index_touch(tp + 2, 16);
+        }
+    }
+    lcp = res;
+    cnt.text_words(first, (uint32_t)p + (uint32_t)min_i(lim, res + 1));
+    return sign;
+}
+
 // Probe of one suffix (text position p) whose first key_bases bases (key0,
 // the rest of its first word zero) are in hand, with h bases known to
 // match: like compare_from, but word 0 comes from key0 and words 1 ..
@@ -239,6 +305,7 @@ template <int W, class Q, class Cnt>
 __device__ __forceinline__ int compare_row(const DevIndex &ix, const Q &q, int plen,
                                            const RowRec *__restrict__ rec, int32_t p, uint64_t key0, int h,
                                            int &lcp, Cnt &cnt, int key_bases = 32) {
+    if constexpr (W == kWordsInLds) return compare_lds(ix, q, plen, p, key0, h, lcp, cnt, key_bases);
     const int lim = min_i(plen, ix.n - p);
     const int k0 = h >> 5;
     int res = lim;
@@ -285,14 +352,10 @@ __device__ __forceinline__ int compare_row(const DevIndex &ix, const Q &q, int p
 // starts comparing at that word.  UPPER = false: first row whose suffix is
 // not below P[0..plen) (LB); UPPER = true: first row strictly above every
 // extension of P[0..plen) (RB + 1).
-//
-// left: probes the read may still take; a search that would take one more
-// when none is left stops and returns -1 (every result is >= 0).
 template <int W, bool UPPER, class Q, class Cnt>
 __device__ __forceinline__ int bounded_search(const DevIndex &ix, const Q &q, int plen, int L, int R,
-                              int lcpL, int lcpR, int &left, Cnt &cnt) {
+                              int lcpL, int lcpR, Cnt &cnt) {
     while (R > L + 1) {
-        if (--left < 0) return -1;
         const int piv = midpoint(L, R);
         const RowHead row = row_head(ix.rows, piv);
         cnt.index_touch(ix.rows + piv, 16);
@@ -326,14 +389,29 @@ __device__ __forceinline__ void lb_update(LbState &st, int sign, int piv, int lc
     }
 }
 
-// Full LB search of P[0..plen).  The first `levels` probes of every search
+// LB search of P[0..plen) from the bounds in st to its end, on row records.
+template <int W, class Q, class Cnt>
+__device__ __forceinline__ void lb_rows(const DevIndex &ix, const Q &q, int plen, LbState &st, Cnt &cnt) {
+    while (st.R > st.L + 1) {
+        const int piv = midpoint(st.L, st.R);
+        const RowHead row = row_head(ix.rows, piv);
+        cnt.index_touch(ix.rows + piv, 16);
+        int lcp;
+        cnt.key_probe();
+        const int sign =
+            compare_row<W>(ix, q, plen, ix.rows + piv, row.pos, row.key0, min_i(st.lcpL, st.lcpR), lcp, cnt);
+        lb_update(st, sign, piv, lcp);
+    }
+}
+
+// Full LB search of P[0..plen) (lb_tile: its part in the tile, then the rest
+// on row records).  The first `levels` probes of every search
 // from (-1, n) visit nodes of one fixed implicit binary tree; their pivot
 // suffixes (first 32 bases and text position) sit in LDS.  A probe that
 // ties on all 32 staged bases continues in global memory at word 1.
-// Returns false when the global probes ran out of `left`.
 template <int W, class Q, class Cnt>
-__device__ __forceinline__ bool lb_search(const DevIndex &ix, const uint64_t *s_key, const int32_t *s_sa, int levels,
-                          const Q &q, int plen, LbState &st, int &left, Cnt &cnt) {
+__device__ __forceinline__ void lb_tile(const DevIndex &ix, const uint64_t *s_key, const int32_t *s_sa, int levels,
+                          const Q &q, int plen, LbState &st, Cnt &cnt) {
     st.L = -1; st.R = ix.n; st.lcpL = 0; st.lcpR = 0;
     st.Llt = -1; st.lcpLlt = 0; st.Rlt = ix.n; st.lcpRlt = 0;
     int node = 0;
@@ -347,18 +425,13 @@ __device__ __forceinline__ bool lb_search(const DevIndex &ix, const uint64_t *s_
         lb_update(st, sign, piv, lcp);
         node = 2 * node + (sign <= 0 ? 1 : 2);
     }
-    while (st.R > st.L + 1) {
-        if (--left < 0) return false;
-        const int piv = midpoint(st.L, st.R);
-        const RowHead row = row_head(ix.rows, piv);
-        cnt.index_touch(ix.rows + piv, 16);
-        int lcp;
-        cnt.key_probe();
-        const int sign =
-            compare_row<W>(ix, q, plen, ix.rows + piv, row.pos, row.key0, min_i(st.lcpL, st.lcpR), lcp, cnt);
-        lb_update(st, sign, piv, lcp);
-    }
-    return true;
+}
+
+template <int W, class Q, class Cnt>
+__device__ __forceinline__ void lb_search(const DevIndex &ix, const uint64_t *s_key, const int32_t *s_sa, int levels,
+                                          const Q &q, int plen, LbState &st, Cnt &cnt) {
+    lb_tile<W>(ix, s_key, s_sa, levels, q, plen, st, cnt);
+    lb_rows<W>(ix, q, plen, st, cnt);
 }
 
 // ---- prefix table
@@ -368,93 +441,77 @@ __device__ __forceinline__ bool lb_search(const DevIndex &ix, const uint64_t *s_
 // does not start with v after them is above it, so the LB search of P runs
 // inside the bracket of rows that start with v (see PrefixEntry).
 
-// LB search of P[0..plen) inside the table bracket of its first k bases v.
-// Returns false when no suffix starts with v: the entry then holds the
-// read's result (ans); also when the record probes ran out of `left` (ans
-// is then flagged kHitDeferred).  Otherwise st holds the LB search's final
-// state.
+// The entry of the read's first K bases (one 16-byte load).
+template <class Cnt>
+__device__ __forceinline__ PrefixEntry table_entry(const DevIndex &ix, uint32_t v, Cnt &cnt) {
+    const uint4 e = load_stream16(ix.ptab + v);
+    cnt.index_touch(ix.ptab + v, 16);
+    cnt.table_probe();
+    return PrefixEntry{e.x, e.y, (int32_t)e.z, e.w};
+}
+
+// LB search of P[0..plen) inside the bracket of an entry that has one.
 // Rows inside the bracket share k bases with P, so when the search moves a
 // bound inside, the other bound's common-prefix length (below k) never
 // decides anything and starts as 0.  The first probe takes its pivot
 // suffix's position and first k + 16 bases from the entry, with no load of
 // its own.
-template <int W, class Q, class Cnt>
-__device__ __forceinline__ bool lb_search_table(const DevIndex &ix, const Q &q, int plen, LbState &st,
-                                                int4 &ans, int &left, Cnt &cnt) {
-    const int K = ix.ptab_k;
-    const uint32_t v = (uint32_t)(q[0] >> (64 - 2 * K));
-    const uint4 e4 = load_stream16(ix.ptab + v);
-    const PrefixEntry ent{e4.x, e4.y, (int32_t)e4.z, e4.w};
-    cnt.index_touch(ix.ptab + v, 16);
-    cnt.table_probe();
-    if (ent.size & kPtabAnswer) {
-        ans = make_int4(ent.pos, (int)ent.next, (int)(ent.size & ~kPtabAnswer), 0);
-        return false;
-    }
-    const int lo_k = (int)ent.row;
-    const int hi_k = lo_k + (int)ent.size;
-    st.L = lo_k - 1; st.R = hi_k; st.lcpL = 0; st.lcpR = 0;
+__device__ __forceinline__ void open_bracket(const DevIndex &ix, int row, int size, LbState &st) {
+    st.L = row - 1; st.R = row + size; st.lcpL = 0; st.lcpR = 0;
     st.Llt = -1; st.lcpLlt = 0; st.Rlt = ix.n; st.lcpRlt = 0;
-    {
-        const int piv = midpoint(st.L, st.R);
-        const uint64_t key = (q[0] & ~(~0ull >> (2 * K))) | ((uint64_t)ent.next << (32 - 2 * K));
-        int lcp;
-        cnt.global_probe();  // its position and bases came with the entry, not from a record
-        const int sign = compare_row<W>(ix, q, plen, nullptr, ent.pos, key, 0, lcp, cnt, K + 16);
-        lb_update(st, sign, piv, lcp);
-    }
-    while (st.R > st.L + 1) {
-        if (--left < 0) {
-            ans = make_int4(0, 0, 0, (int)kHitDeferred);
-            return false;
-        }
-        const int piv = midpoint(st.L, st.R);
-        const RowHead row = row_head(ix.rows, piv);
-        cnt.index_touch(ix.rows + piv, 16);
-        int lcp;
-        cnt.key_probe();
-        const int sign =
-            compare_row<W>(ix, q, plen, ix.rows + piv, row.pos, row.key0, min_i(st.lcpL, st.lcpR), lcp, cnt);
-        lb_update(st, sign, piv, lcp);
-    }
-    return true;
 }
 
-// One read: LB search of its ACGT prefix; exact reads finish with an RB
-// search confined to (LB, Rlt]; other reads take the longest matched prefix
-// l = max(lcpL, lcpR) from the two rows around the insertion point and find
-// the interval of P[0..l) inside the bounds the LB search already bracketed.
-// The empty prefix (an empty read, or one that starts with a non-base)
-// matches every suffix.  `budget` bounds the probes of row records and of
-// the global part of the tree; a read that needs more gets a result
-// flagged kHitDeferred instead (kNoBudget: no bound).
 template <int W, class Q, class Cnt>
-__device__ __forceinline__ int4 match_read(const DevIndex &ix, const uint64_t *s_key, const int32_t *s_sa, int levels,
-                           bool use_table, const Q &q, int m, int mv, int budget, Cnt &cnt) {
-    if (mv == 0) return make_int4(0, ix.n, 0, m == 0 ? (int)kHitExact : 0);
-    const int4 deferred = make_int4(0, 0, 0, (int)kHitDeferred);
-    int left = budget;
-    LbState st;
-    if (use_table && ix.ptab_k > 0 && mv >= ix.ptab_k) {
-        int4 ans;
-        if (!lb_search_table<W>(ix, q, mv, st, ans, left, cnt)) return ans;
-    } else {
-        if (!lb_search<W>(ix, s_key, s_sa, levels, q, mv, st, left, cnt)) return deferred;
-    }
+__device__ __forceinline__ void lb_search_table(const DevIndex &ix, const PrefixEntry &ent, const Q &q, int plen,
+                                                LbState &st, Cnt &cnt) {
+    const int K = ix.ptab_k;
+    open_bracket(ix, (int)ent.row, (int)ent.size, st);
+    const int piv = midpoint(st.L, st.R);
+    const uint64_t key = (q[0] & ~(~0ull >> (2 * K))) | ((uint64_t)ent.next << (32 - 2 * K));
+    int lcp;
+    cnt.global_probe();  // its position and bases came with the entry, not from a record
+    const int sign = compare_row<W>(ix, q, plen, nullptr, ent.pos, key, 0, lcp, cnt, K + 16);
+    lb_update(st, sign, piv, lcp);
+    lb_rows<W>(ix, q, plen, st, cnt);
+}
+
+// The read's result from the final state of the LB search of its ACGT
+// prefix P[0..mv): exact reads finish with an RB search confined to (LB,
+// Rlt]; other reads take the longest matched prefix l = max(lcpL, lcpR) from
+// the two rows around the insertion point and find the interval of P[0..l)
+// inside the bounds the LB search already bracketed.
+template <int W, class Q, class Cnt>
+__device__ __forceinline__ int4 finish_read(const DevIndex &ix, const Q &q, int m, int mv, const LbState &st,
+                                            Cnt &cnt) {
     if (mv == m && st.lcpR == m) {
-        const int hi = bounded_search<W, true>(ix, q, m, st.R, st.Rlt, m, st.lcpRlt, left, cnt);
-        if (hi < 0) return deferred;
+        const int hi = bounded_search<W, true>(ix, q, m, st.R, st.Rlt, m, st.lcpRlt, cnt);
         return make_int4(st.R, hi, m, (int)kHitExact);
     }
     // (after a search inside a table bracket l >= k: one of the final
     // bounds is a probed row of the bracket, which shares the k bases)
     const int l = max_i(st.lcpL, st.lcpR);
     if (l == 0) return make_int4(0, ix.n, 0, 0);
-    const int lo =
-        (st.lcpL == l) ? bounded_search<W, false>(ix, q, l, st.Llt, st.L, st.lcpLlt, l, left, cnt) : st.R;
-    const int hi = (st.lcpR == l) ? bounded_search<W, true>(ix, q, l, st.R, st.Rlt, l, st.lcpRlt, left, cnt) : st.R;
-    if ((lo | hi) < 0) return deferred;
+    const int lo = (st.lcpL == l) ? bounded_search<W, false>(ix, q, l, st.Llt, st.L, st.lcpLlt, l, cnt) : st.R;
+    const int hi = (st.lcpR == l) ? bounded_search<W, true>(ix, q, l, st.R, st.Rlt, l, st.lcpRlt, cnt) : st.R;
     return make_int4(lo, hi, l, 0);
+}
+
+// One read: LB search of its ACGT prefix from its table entry or from the
+// root, then finish_read.  The empty prefix (an empty read, or one that
+// starts with a non-base) matches every suffix.
+template <int W, class Q, class Cnt>
+__device__ __forceinline__ int4 match_read(const DevIndex &ix, const uint64_t *s_key, const int32_t *s_sa, int levels,
+                           bool use_table, const Q &q, int m, int mv, Cnt &cnt) {
+    if (mv == 0) return make_int4(0, ix.n, 0, m == 0 ? (int)kHitExact : 0);
+    LbState st;
+    if (use_table && ix.ptab_k > 0 && mv >= ix.ptab_k) {
+        const PrefixEntry ent = table_entry(ix, (uint32_t)(q[0] >> (64 - 2 * ix.ptab_k)), cnt);
+        if (ent.size & kPtabAnswer) return make_int4(ent.pos, (int)ent.next, (int)(ent.size & ~kPtabAnswer), 0);
+        lb_search_table<W>(ix, ent, q, mv, st, cnt);
+    } else {
+        lb_search<W>(ix, s_key, s_sa, levels, q, mv, st, cnt);
+    }
+    return finish_read<W>(ix, q, m, mv, st, cnt);
 }
 
 template <int W>
@@ -537,7 +594,7 @@ __global__ void fill_prefix_entries_kernel(DevIndex ix, int k, int64_t first, in
     } else {
         const uint64_t q[1] = {(uint64_t)v << (64 - 2 * k)};
         NoCount none;
-        const int4 r = match_read<1>(ix, nullptr, nullptr, 0, false, q, k, k, kNoBudget, none);
+        const int4 r = match_read<1>(ix, nullptr, nullptr, 0, false, q, k, k, none);
         tab[v].size = kPtabAnswer | (uint32_t)r.z;
         tab[v].pos = r.x;
         tab[v].next = (uint32_t)r.y;
@@ -692,29 +749,33 @@ __device__ __forceinline__ uint32_t bad_nibble(uint32_t bad) {
 }
 
 // 16 bytes of ASCII (four little-endian dwords, the first byte lowest) to
-// 16 two-bit codes, the first base in the top bits of codes[c], and a flag
-// bit per byte that is not a base in badm[c] (bit i for byte i), with the
-// code of such a byte 0.  When every byte is a base (either case) -- a
-// byte-wise compare with "ACGT"[code] -- the codes of each dword are
-// gathered into a byte with two shift-ors and the sixteen pairs are put in
-// order by one bit reversal and a swap within each pair; otherwise the
-// flags are worked out byte by byte.  Returns whether a byte was not a base.
-__device__ __forceinline__ uint32_t gather4(uint32_t cd) {
-    const uint32_t x = cd | (cd >> 6);  // bits 0-3: codes of bytes 0, 1; bits 16-19: bytes 2, 3
-    return (x | (x >> 12)) & 0xFFu;     // byte i's code at bits 2i, 2i+1
+// 16 two-bit codes, the first base in the top bits; `bad` becomes nonzero
+// when a byte is not a base (its code is then of no meaning).  Bits 1 and 2
+// of a base's letter, in either case, count a, c, t, g as 0..3: a dot
+// product with the place values of four codes gathers them into a byte, a
+// byte permute looks up the letters they stand for to test the bytes, and
+// t and g are put in order at the end on all sixteen codes at once.  About
+// 30 instructions for 16 bases (shifts, masks and a bit reversal took 60).
+__device__ __forceinline__ uint32_t convert16(const uint4 &v, uint32_t &bad) {
+    const uint32_t d[4] = {v.x, v.y, v.z, v.w};
+    uint32_t w = 0, diff = 0;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const uint32_t r = (d[i] >> 1) & 0x03030303u;
+        diff |= (d[i] ^ __builtin_amdgcn_perm(0u, 0x47544341u, r)) & 0xDFDFDFDFu;
+        w = __builtin_amdgcn_udot4(r, 0x01041040u, w << 8, false);
+    }
+    bad = diff;
+    return w ^ ((w >> 1) & 0x55555555u);
 }
 
+// convert16 into codes[c], with a flag bit per byte that is not a base in
+// badm[c] (bit i for byte i) and the code of such a byte 0.  Returns
+// whether a byte was not a base.
 __device__ __forceinline__ bool convert_piece(const uint4 &v, uint32_t *codes, uint16_t *badm, int c) {
-    const uint32_t k0 = ((v.x >> 1) ^ (v.x >> 2)) & 0x03030303u, k1 = ((v.y >> 1) ^ (v.y >> 2)) & 0x03030303u;
-    const uint32_t k2 = ((v.z >> 1) ^ (v.z >> 2)) & 0x03030303u, k3 = ((v.w >> 1) ^ (v.w >> 2)) & 0x03030303u;
-    const uint32_t d0 = (v.x & 0xDFDFDFDFu) ^ __builtin_amdgcn_perm(0u, 0x54474341u, k0);
-    const uint32_t d1 = (v.y & 0xDFDFDFDFu) ^ __builtin_amdgcn_perm(0u, 0x54474341u, k1);
-    const uint32_t d2 = (v.z & 0xDFDFDFDFu) ^ __builtin_amdgcn_perm(0u, 0x54474341u, k2);
-    const uint32_t d3 = (v.w & 0xDFDFDFDFu) ^ __builtin_amdgcn_perm(0u, 0x54474341u, k3);
-    if ((d0 | d1 | d2 | d3) == 0) {
-        uint32_t w = gather4(k0) | (gather4(k1) << 8) | (gather4(k2) << 16) | (gather4(k3) << 24);
-        w = __builtin_bitreverse32(w);                          // base i's pair at bits 30-2i, 31-2i, swapped
-        w = ((w >> 1) & 0x55555555u) | ((w & 0x55555555u) << 1);  // base 0 in the top two bits
+    uint32_t any;
+    const uint32_t w = convert16(v, any);
+    if (any == 0) {
         codes[c] = w;
         badm[c] = 0;
         return false;
@@ -869,176 +930,8 @@ __device__ __forceinline__ void tuned_one(const DevIndex &ix, const uint64_t *s_
 #pragma unroll
     for (int k = 0; k < W; ++k)
         if (k < nw) cnt.touch(src + k, 8);
-    out[rid] = match_read<W>(ix, s_key, s_sa, levels, use_table, q, m, mv, kNoBudget, cnt);
+    out[rid] = match_read<W>(ix, s_key, s_sa, levels, use_table, q, m, mv, cnt);
     cnt.touch(out + rid, 16);
-}
-
-// tuned_one for a read whose packed words are already in registers, with
-// at most `budget` probes: returns true (and writes nothing) when the read
-// needs more.
-template <int W, int N, class Cnt>
-__device__ __forceinline__ bool tuned_regs(const DevIndex &ix, const uint64_t *s_key, const int32_t *s_sa,
-                                           int levels, bool use_table, const uint64_t (&w)[N], int rid, int m,
-                                           int mv, int budget, int4 *out, Cnt &cnt) {
-    if (m < 0) {
-        out[rid] = make_int4(0, 0, 0, (int)kHitTooLong);
-        return false;
-    }
-    uint64_t q[W];
-#pragma unroll
-    for (int k = 0; k < W; ++k) q[k] = w[k];
-    const int4 r = match_read<W>(ix, s_key, s_sa, levels, use_table, q, m, mv, budget, cnt);
-    if (r.w == (int)kHitDeferred) return true;
-    store_stream16(out + rid, r);
-    cnt.touch(out + rid, 16);
-    return false;
-}
-
-// Packing inside the search kernel, for reads in input order with CSR
-// offsets: a wave's 64 consecutive reads are one span of the ASCII buffer.
-// The wave converts the span with coalesced, aligned 16-byte loads into a
-// 2-bit code stream and non-base flags in its own LDS area (as the pack
-// kernel does for a workgroup), then each lane takes its read's words out
-// of the stream into registers.  A span longer than the area, and a read
-// outside its wave's span (offsets that go backwards), take the global
-// path.  Saves the pack kernel's writes of the packed words and lengths
-// and the search kernel's reads of them.  The loads are pipelined: a wave
-// loads the offsets of the chunk after next and the ASCII of the next
-// chunk (into registers) before it searches the current one.
-// The wave-uniform span of a chunk's reads: the aligned 16-byte pieces
-// [A0, A0 + 16 nvec) that hold bytes [s0, s1) of the read buffer; staged
-// when it fits the wave's packing area.
-struct Span {
-    uintptr_t A0;
-    int64_t s0, s1;
-    int nvec;
-    bool staged;
-};
-
-// Start and end of each read of chunk (none when chunk < 0): loads issued
-// here, used later.  Read j ends at offs[j + 1], or at ends[j] when an end
-// array is given (reads gathered from anywhere in the buffer).
-__device__ __forceinline__ void chunk_offsets(const int64_t *__restrict__ offs, const int64_t *__restrict__ ends,
-                                              int64_t chunk, int64_t nreads, int lane, int64_t &a, int64_t &e) {
-    const int64_t j = (chunk << 6) + lane;
-    const bool act = chunk >= 0 && j < nreads;
-    a = act ? offs[j] : 0;
-    e = act ? (ends ? ends[j] : offs[j + 1]) : 0;
-}
-
-// With an end array the span is staged only when the chunk's reads follow
-// each other (every read ends where the next starts), so that every staged
-// byte belongs to one of them; with CSR offsets the span lies between two
-// offsets of the one buffer.
-__device__ __forceinline__ Span chunk_span(const uint8_t *__restrict__ reads, bool gathered, int64_t chunk,
-                                           int64_t nreads, int lane, int64_t a, int64_t e, int max_vec) {
-    Span sp{0, 0, 0, 0, false};
-    if (chunk < 0) return sp;
-    const int last = (int)min_i(63, (int)(nreads - 1 - (chunk << 6)));
-    sp.s0 = __shfl(a, 0, 64);
-    sp.s1 = __shfl(e, last, 64);
-    bool joined = true;
-    if (gathered) {
-        const int64_t next_a = __shfl_down(a, 1, 64);
-        joined = __ballot(lane < last && e != next_a) == 0;
-    }
-    sp.A0 = (uintptr_t)(reads + sp.s0) & ~(uintptr_t)15;
-    const uintptr_t A1 = ((uintptr_t)(reads + sp.s1) + 15) & ~(uintptr_t)15;
-    sp.staged = joined && sp.s1 > sp.s0 && A1 - sp.A0 <= (uintptr_t)max_vec * 16u;
-    sp.nvec = sp.staged ? (int)((A1 - sp.A0) >> 4) : 0;
-    return sp;
-}
-
-// Pieces of a staged span a wave holds in registers between chunks (lane l
-// holds pieces l, l + 64, ...); the rest of a longer span is loaded when it
-// is converted.  Two for the 10-word kernel (on MI355X, 4 and 3 left it
-// more registers and a mixed 20-300-base batch 9 % and 5 % slower; 1 was
-// 1 % slower), one for the 5-word kernel.
-#ifndef SAMATCH_INLINE_AHEAD
-#define SAMATCH_INLINE_AHEAD 2
-#endif
-constexpr int kInlineAhead = SAMATCH_INLINE_AHEAD;
-
-template <int AHEAD, class Cnt>
-__device__ __forceinline__ void span_prefetch(const Span &sp, int lane, uint4 (&v)[AHEAD], Cnt &cnt) {
-    const uint4 *src = reinterpret_cast<const uint4 *>(sp.A0);
-#pragma unroll
-    for (int u = 0; u < AHEAD; ++u) {
-        const int c = 64 * u + lane;
-        if (c < sp.nvec) {
-            v[u] = load_stream16(src + c);
-            cnt.touch(src + c, 16);
-        }
-    }
-}
-
-// The staged span as codes and flags in the wave's area: the prefetched
-// pieces, then the rest (four loads in flight per lane).  Returns, the same
-// for every lane, whether any byte of the span was not a base.
-template <int AHEAD, class Cnt>
-__device__ __forceinline__ bool span_convert(const Span &sp, const uint4 (&v)[AHEAD], uint32_t *codes,
-                                             uint16_t *badm, int lane, Cnt &cnt) {
-    bool bad = false;
-#pragma unroll
-    for (int u = 0; u < AHEAD; ++u) {
-        const int c = 64 * u + lane;
-        if (c < sp.nvec) bad |= convert_piece(v[u], codes, badm, c);
-    }
-    const uint4 *src = reinterpret_cast<const uint4 *>(sp.A0);
-    for (int c0 = 64 * AHEAD; c0 < sp.nvec; c0 += 4 * 64) {
-        uint4 r[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const int c = c0 + 64 * u + lane;
-            if (c < sp.nvec) {
-                r[u] = load_stream16(src + c);
-                cnt.touch(src + c, 16);
-            }
-        }
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const int c = c0 + 64 * u + lane;
-            if (c < sp.nvec) bad |= convert_piece(r[u], codes, badm, c);
-        }
-    }
-    return __any(bad);
-}
-
-// The reads of a chunk of set-aside reads (lane l: m bases at reads[a..];
-// m = 0 for a lane without one) as codes and flags in the wave's area:
-// lane l's read takes slot l, pieces [l * S, (l + 1) * S) (S =
-// inline_slot(WQ)), starting (a & 15) bytes into the slot's first piece.
-// The wave loads the slots' pieces with its lanes side by side (pieces of
-// one read are neighbours in memory), four loads in flight per lane.
-// Returns, the same for every lane, whether any byte loaded was not a base.
-template <int WQ, class Cnt>
-__device__ __forceinline__ bool gather_convert(const uint8_t *__restrict__ reads, int64_t a, int m, uint32_t *codes,
-                                               uint16_t *badm, int lane, Cnt &cnt) {
-    constexpr int S = inline_slot(WQ);
-    const uintptr_t A0 = (uintptr_t)(reads + a) & ~(uintptr_t)15;
-    const int np = m > 0 ? (int)(((((uintptr_t)(reads + a) + (uintptr_t)m + 15) & ~(uintptr_t)15) - A0) >> 4) : 0;
-    bool bad = false;
-#pragma unroll 1
-    for (int c0 = 0; c0 < 64 * S; c0 += 4 * 64) {
-        uint4 r[4];
-        bool in[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const int c = c0 + 64 * u + lane;
-            const int owner = c / S, k = c - owner * S;
-            const uintptr_t base = (uintptr_t)__shfl((unsigned long long)A0, owner & 63, 64);
-            const int n_owner = __shfl(np, owner & 63, 64);
-            in[u] = c < 64 * S && k < n_owner;
-            if (in[u]) {
-                r[u] = load_stream16(reinterpret_cast<const uint4 *>(base) + k);
-                cnt.touch(reinterpret_cast<const uint4 *>(base) + k, 16);
-            }
-        }
-#pragma unroll
-        for (int u = 0; u < 4; ++u)
-            if (in[u]) bad |= convert_piece(r[u], codes, badm, c0 + 64 * u + lane);
-    }
-    return __any(bad);
 }
 
 // LDS written by this wave's lanes is visible to its other lanes.
@@ -1046,37 +939,6 @@ __device__ __forceinline__ void wave_lds_sync() {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
-// Words and first non-base of a read of m bases starting st0 bytes into a
-// staged code stream (scan = false: the span has no non-base byte).
-template <int N>
-__device__ __forceinline__ void inline_extract(const uint32_t *codes, const uint16_t *badm, uint32_t st0, int m,
-                                               uint64_t (&w)[N], int &mv, bool scan) {
-#pragma unroll
-    for (int k = 0; k < N; ++k) {
-        if (32 * k < m) {
-            const uint32_t bpos = st0 + 32u * (uint32_t)k, q = bpos >> 4, r = bpos & 15u;
-            const uint64_t hi = ((uint64_t)codes[q] << 32) | codes[q + 1];
-            uint64_t x = r ? (hi << (2 * r)) | (codes[q + 2] >> (32 - 2 * r)) : hi;
-            const int rem = m - 32 * k;
-            if (rem < 32) x &= ~0ull << (64 - 2 * rem);
-            w[k] = x;
-        }
-    }
-    mv = m;
-    if (scan && m > 0) {
-        const uint32_t q0 = st0 >> 4, q1 = (st0 + (uint32_t)m - 1) >> 4;
-        for (uint32_t q = q0; q <= q1; ++q) {
-            uint32_t bits = badm[q];
-            if (q == q0) bits &= 0xFFFFu << (st0 & 15u);
-            if (q == q1) bits &= (2u << ((st0 + (uint32_t)m - 1) & 15u)) - 1u;
-            if (bits) {
-                mv = (int)(q * 16u + (uint32_t)__builtin_ctz(bits) - st0);
-                break;
-            }
-        }
-    }
 }
 
 // Sum a per-lane 64-bit count over the wave and add it to a global counter.
@@ -1108,39 +970,44 @@ __device__ __forceinline__ int64_t workgroup_rank() {
     return (G % 8 == 0) ? (w % 8) * (G / 8) + w / 8 : w;
 }
 
+// The next chunk of this wave (-1 when the workgroup's blocks are done;
+// every later one lies further on).
+__device__ __forceinline__ int64_t take_chunk(unsigned *next, int group, int64_t G, int64_t rank, int lane,
+                                              int64_t nchunks) {
+    unsigned c = 0;
+    if (lane == 0) c = atomicAdd(next, 1u);
+    c = (unsigned)__builtin_amdgcn_readfirstlane((int)c);
+    const int64_t chunk = ((int64_t)(c / (unsigned)group) * G + rank) * group + (c % (unsigned)group);
+    return chunk < nchunks ? chunk : -1;
+}
+
+// The instrumented kernels' counts, summed over the wave.
+__device__ __forceinline__ void add_counts(unsigned long long *stats, const Count &cnt) {
+    wave_add(&stats[0], cnt.global);
+    wave_add(&stats[1], cnt.words);
+    wave_add(&stats[2], cnt.tile);
+    wave_add(&stats[5], cnt.keys);
+    wave_add(&stats[6], cnt.table);
+    wave_add64(&stats[7], cnt.touched);
+    wave_add64(&stats[8], cnt.scattered);
+    wave_add(&stats[9], cnt.index_loads);
+}
+
+// ---- reads packed by the pack kernel
+
 // Persistent kernel: each workgroup stages the top `levels` tree levels in
 // LDS once, then its waves take 64-read chunks until the workgroup's blocks
 // are done.  Each chunk runs the instantiation for the longest read it
 // holds.
-//
-// INLINE: the kernel packs its reads itself from the ASCII buffer and CSR
-// offsets (reads in input order; no pack kernel ran), each wave in its own
-// LDS area after the tile.  WQ: query words a read may hold in registers
-// (reads of up to 32 * WQ bases; longer ones are the long-read kernel's).
-// The 5-word instance keeps fewer registers live (and prefetches one piece
-// of the next chunk per lane), so that six waves fit each SIMD (the
-// counting instance is not held to that).  Each instance's packing area
-// holds the span of 64 reads of its longest length.
-template <int BLOCK, bool COUNT, bool INLINE, int WQ>
-__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(WQ < kWMax && !COUNT ? 6 : 1))) void search_tuned_kernel(DevIndex ix, int levels, int use_table_i, int group, int defer,
-                                                             BatchBuffers b, const uint32_t *__restrict__ order,
-                                                             const uint8_t *__restrict__ reads,
-                                                             const int64_t *__restrict__ offs,
-                                                             const int64_t *__restrict__ ends, int64_t nreads,
-                                                             int4 *__restrict__ out) {
+template <int BLOCK, bool COUNT>
+__global__ __launch_bounds__(BLOCK) void search_packed_kernel(DevIndex ix, int levels, int use_table_i, int group,
+                                                              BatchBuffers b, const uint32_t *__restrict__ order,
+                                                              int64_t nreads, int4 *__restrict__ out) {
     extern __shared__ uint64_t smem[];
     __shared__ unsigned s_next;
     const int nodes = (1 << levels) - 1;
     uint64_t *s_key = smem;
     int32_t *s_sa = reinterpret_cast<int32_t *>(smem + nodes);
-    uint32_t *w_codes = nullptr;
-    uint16_t *w_badm = nullptr;
-    if constexpr (INLINE) {
-        uint8_t *area = reinterpret_cast<uint8_t *>(smem) + inline_area_offset(levels) +
-                        (size_t)(threadIdx.x >> 6) * inline_wave_bytes(WQ);
-        w_codes = reinterpret_cast<uint32_t *>(area);
-        w_badm = reinterpret_cast<uint16_t *>(w_codes + inline_vec(WQ) + 4);
-    }
     if (threadIdx.x == 0) s_next = 0u;
     for (int i = threadIdx.x; i < nodes; i += BLOCK) {
         s_key[i] = ix.tile_key[i];
@@ -1154,139 +1021,8 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(WQ < kWMa
     const int lane = threadIdx.x & 63;
     const int64_t nchunks = (nreads + 63) >> 6;
     const int64_t G = gridDim.x, rank = workgroup_rank();
-    // the next chunk of this wave (-1 when the workgroup's blocks are done;
-    // every later one lies further on)
-    auto take = [&]() -> int64_t {
-        unsigned c = 0;
-        if (lane == 0) c = atomicAdd(&s_next, 1u);
-        c = __shfl(c, 0, 64);
-        const int64_t chunk = ((int64_t)(c / group) * G + rank) * group + (c % group);
-        return chunk < nchunks ? chunk : -1;
-    };
-    if constexpr (INLINE) {
-        int64_t c0 = take(), a0, e0;
-        chunk_offsets(offs, ends, c0, nreads, lane, a0, e0);
-        Span sp0 = chunk_span(reads, ends != nullptr, c0, nreads, lane, a0, e0, inline_vec(WQ));
-        constexpr int AHEAD = WQ < kWMax ? 1 : kInlineAhead;
-        constexpr int kMaxM = 32 * WQ;  // longest read searched here
-        uint4 v[AHEAD];
-        span_prefetch(sp0, lane, v, cnt);
-        int64_t c1 = c0 >= 0 ? take() : -1, a1, e1;
-        chunk_offsets(offs, ends, c1, nreads, lane, a1, e1);
-        // reads set aside (their searches ran out of `defer` probes) wait in
-        // the wave's queue; when 64 are waiting, or the chunks are done, the
-        // wave takes them as a chunk of its own and searches them without a
-        // limit, so that one long search does not hold up 63 idle lanes
-        uint32_t *w_queue = reinterpret_cast<uint32_t *>(reinterpret_cast<uint8_t *>(w_codes) + inline_codes_bytes(WQ));
-        const int budget = (defer > 0 && !COUNT) ? defer : kNoBudget;
-        int queued = 0;  // wave-uniform
-        while (c0 >= 0 || queued > 0) {
-            const bool drain = queued >= 64 || c0 < 0;
-            uint64_t w[WQ];
-#pragma unroll
-            for (int t = 0; t < WQ; ++t) w[t] = 0;
-            int rid, m;
-            bool short_read, from_lds, scan, synced;
-            uint32_t st0;
-            if (drain) {
-                const int n = min_i(queued, 64);
-                queued -= n;
-                short_read = lane < n;
-                rid = short_read ? (int)w_queue[queued + lane] : 0;
-                const int64_t a = short_read ? offs[rid] : 0;
-                const int64_t e = short_read ? (ends ? ends[rid] : offs[rid + 1]) : 0;
-                m = (int)(e - a);  // 1 .. kMaxM: the read was searched before
-                scan = gather_convert<WQ>(reads, a, m, w_codes, w_badm, lane, cnt);
-                wave_lds_sync();
-                from_lds = short_read;
-                synced = true;
-                st0 = (uint32_t)(lane * inline_slot(WQ) * 16) + (uint32_t)(a & 15);
-            } else {
-                const int64_t j = (c0 << 6) + lane;
-                const bool active = j < nreads;
-                if (COUNT && active) {
-                    cnt.touch(offs + j, ends ? 8 : 16);
-                    if (ends) cnt.touch(ends + j, 8);
-                }
-                const int64_t m64 = e0 - a0;
-                // m = -1: length out of range (the too-long result); long reads are the long kernel's
-                const bool long_read = active && m64 > kMaxM && m64 <= SA_MAX_READ;
-                m = (m64 >= 0 && m64 <= kMaxM) ? (int)m64 : -1;
-                if (long_read) b.stats[kLongFlag] = 1ull;
-                short_read = active && !long_read;
-                rid = (int)j;
-                scan = false;
-                if (sp0.staged) {
-                    scan = span_convert(sp0, v, w_codes, w_badm, lane, cnt);
-                    wave_lds_sync();
-                }
-                synced = sp0.staged;
-                from_lds = short_read && m > 0 && sp0.staged && a0 >= sp0.s0 && e0 <= sp0.s1;
-                st0 = (uint32_t)((uintptr_t)(reads + a0) - sp0.A0);
-            }
-            int mv = m;
-            if (from_lds) {
-                inline_extract(w_codes, w_badm, st0, m, w, mv, scan);
-            } else if (short_read && m > 0) {
-                uint64_t g[kWMax + 1];
-                pack_from_global(reads, a0, m, g, mv, g[kWMax]);
-#pragma unroll
-                for (int t = 0; t < WQ; ++t) w[t] = (32 * t < m) ? g[t] : 0;
-            }
-            if (synced) wave_lds_sync();  // every lane has its words before the area is reused
-            if (!drain) {
-                // loads for the chunks ahead, in flight during this chunk's searches
-                const Span sp1 = chunk_span(reads, ends != nullptr, c1, nreads, lane, a1, e1, inline_vec(WQ));
-                span_prefetch(sp1, lane, v, cnt);
-                const int64_t c2 = c1 >= 0 ? take() : -1;
-                int64_t a2, e2;
-                chunk_offsets(offs, ends, c2, nreads, lane, a2, e2);
-                c0 = c1;
-                a0 = a1;
-                e0 = e1;
-                sp0 = sp1;
-                c1 = c2;
-                a1 = a2;
-                e1 = e2;
-            }
-            const int wn = max_i(1, (m + 31) >> 5);
-            int wc = 1;
-#pragma unroll
-            for (int t = 2; t <= WQ; ++t)
-                if (wave_ballot(short_read && wn >= t)) wc = t;
-            const int lim = drain ? kNoBudget : budget;
-            bool later = false;
-            if (short_read) {
-                if (COUNT && m >= 0) { nsearched++; nqwords += wc; }
-                switch (wc) {
-                    case 1: later = tuned_regs<1>(ix, s_key, s_sa, levels, use_table, w, rid, m, mv, lim, out, cnt); break;
-                    case 2: later = tuned_regs<2>(ix, s_key, s_sa, levels, use_table, w, rid, m, mv, lim, out, cnt); break;
-                    case 3: later = tuned_regs<3>(ix, s_key, s_sa, levels, use_table, w, rid, m, mv, lim, out, cnt); break;
-                    case 4: later = tuned_regs<4>(ix, s_key, s_sa, levels, use_table, w, rid, m, mv, lim, out, cnt); break;
-                    case 5: later = tuned_regs<5>(ix, s_key, s_sa, levels, use_table, w, rid, m, mv, lim, out, cnt); break;
-                    default:
-                        if constexpr (WQ >= 10) {
-                            switch (wc) {
-                                case 6: later = tuned_regs<6>(ix, s_key, s_sa, levels, use_table, w, rid, m, mv, lim, out, cnt); break;
-                                case 7: later = tuned_regs<7>(ix, s_key, s_sa, levels, use_table, w, rid, m, mv, lim, out, cnt); break;
-                                case 8: later = tuned_regs<8>(ix, s_key, s_sa, levels, use_table, w, rid, m, mv, lim, out, cnt); break;
-                                case 9: later = tuned_regs<9>(ix, s_key, s_sa, levels, use_table, w, rid, m, mv, lim, out, cnt); break;
-                                default: later = tuned_regs<10>(ix, s_key, s_sa, levels, use_table, w, rid, m, mv, lim, out, cnt); break;
-                            }
-                        }
-                        break;
-                }
-            }
-            const uint64_t set_aside = wave_ballot(later);
-            if (set_aside) {
-                if (later) w_queue[queued + __popcll(set_aside & ((1ull << lane) - 1ull))] = (uint32_t)rid;
-                queued += __popcll(set_aside);
-                wave_lds_sync();
-            }
-        }
-    }
-    while (!INLINE) {  // reads packed by the pack kernel
-        const int64_t chunk = take();
+    for (;;) {
+        const int64_t chunk = take_chunk(&s_next, group, G, rank, lane, nchunks);
         if (chunk < 0) break;
         const int64_t j = (chunk << 6) + lane;
         const bool active = j < nreads;
@@ -1320,16 +1056,491 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(WQ < kWMa
         }
     }
     if constexpr (COUNT) {
-        wave_add(&b.stats[0], cnt.global);
-        wave_add(&b.stats[1], cnt.words);
-        wave_add(&b.stats[2], cnt.tile);
         wave_add(&b.stats[3], nsearched);
         wave_add(&b.stats[4], nqwords);
-        wave_add(&b.stats[5], cnt.keys);
-        wave_add(&b.stats[6], cnt.table);
-        wave_add64(&b.stats[7], cnt.touched);
-        wave_add64(&b.stats[8], cnt.scattered);
-        wave_add(&b.stats[9], cnt.index_loads);
+        add_counts(b.stats, cnt);
+    }
+}
+
+// ---- reads packed by the search kernel itself
+
+// Words of a queued read's record before its codes: read id, length and
+// leading bases, first row and size of its bracket (size 0: search from the
+// root).
+constexpr int kRecHead = 4;
+static_assert(kPoolWords >= kRecHead + SA_MAX_READ / 16, "any read's record fits the pool");
+
+// One wave's LDS area: the code stream (one dummy word, kStagePieces words of
+// 16 codes, three words of slack for reads past the last), a bit per piece
+// that holds a byte which is not a base, the offsets of the queued reads'
+// records, then the records (with two words of slack).
+struct WaveArea {
+    uint32_t *codes, *bad, *rec_at, *pool;
+};
+
+// A query in LDS: word k is 32 codes from code 32k of a stream of 16-code
+// words.  c points at the word before the one that holds the first code
+// when that one starts it (sh 0), else at the one that holds it: a code
+// stream word and the next joined by a right shift of 0..30 bits, so that no
+// shift by 32 arises.
+struct CodeQuery {
+    const uint32_t *c;
+    uint32_t sh;
+    __device__ __forceinline__ uint32_t half(int j) const { return __builtin_amdgcn_alignbit(c[j], c[j + 1], sh); }
+    __device__ __forceinline__ uint64_t operator[](int k) const {
+        const uint32_t c0 = c[2 * k], c1 = c[2 * k + 1], c2 = c[2 * k + 2];
+        return ((uint64_t)__builtin_amdgcn_alignbit(c0, c1, sh) << 32) | __builtin_amdgcn_alignbit(c1, c2, sh);
+    }
+};
+// The query that starts at code `at` of a stream whose first word (codes
+// 0..15) is words[1].
+__device__ __forceinline__ CodeQuery code_query(const uint32_t *words, uint32_t at) {
+    return CodeQuery{words + ((at + 15u) >> 4), 30u - 2u * ((at + 15u) & 15u)};
+}
+
+__device__ __forceinline__ int64_t lane_value(int64_t v, int lane) {
+    const uint32_t lo = __builtin_amdgcn_readlane((int)(uint32_t)v, lane);
+    const uint32_t hi = __builtin_amdgcn_readlane((int)(uint32_t)(v >> 32), lane);
+    return (int64_t)(((uint64_t)hi << 32) | lo);
+}
+
+// The largest of the values (below 128) of the lanes in `mask`, the same
+// for every lane.
+__device__ __forceinline__ int wave_max7(int v, uint64_t mask) {
+    int r = 0;
+#pragma unroll
+    for (int b = 6; b >= 0; --b) {
+        const uint64_t t = wave_ballot((v >> b) & 1) & mask;
+        if (t) {
+            mask = t;
+            r |= 1 << b;
+        }
+    }
+    return r;
+}
+
+// Start and end of each read of a chunk of 2^shift reads (none when chunk <
+// 0): loads issued here, used later.  Read j ends at offs[j + 1], or at
+// ends[j] when an end array is given (reads gathered from anywhere in the
+// buffer).
+__device__ __forceinline__ void chunk_offsets(const int64_t *__restrict__ offs, const int64_t *__restrict__ ends,
+                                              int64_t chunk, int shift, int64_t nreads, int lane, int64_t &a,
+                                              int64_t &e) {
+    const int64_t j = (chunk << shift) + lane;
+    const bool act = chunk >= 0 && lane < (1 << shift) && j < nreads;
+    a = act ? offs[j] : 0;
+    e = act ? (ends ? ends[j] : offs[j + 1]) : 0;
+}
+
+// First byte of reads[a .. a + m) that is not a base (m when all are), for a
+// read whose bytes lie at code `at` of the staged stream: only the pieces
+// flagged in `bad` are looked at again.
+__device__ __forceinline__ int first_non_base(const uint8_t *__restrict__ reads, int64_t a, int m, uint32_t at,
+                                              const uint32_t *bad) {
+    const uint32_t last = (at + (uint32_t)m - 1) >> 4;
+    for (uint32_t pc = at >> 4; pc <= last;) {
+        const uint32_t w = bad[pc >> 5] >> (pc & 31u);
+        if (w == 0) {
+            pc = (pc | 31u) + 1u;
+            continue;
+        }
+        pc += (uint32_t)__builtin_ctz(w);
+        if (pc > last) break;
+        const uint4 v = *reinterpret_cast<const uint4 *>(reads + a + (int64_t)(16u * pc) - (int64_t)at);
+        uint32_t b;
+        pack4_fast(v.x, 0xFFFFFFFFu, b);
+        uint32_t bits = bad_nibble(b);
+        pack4_fast(v.y, 0xFFFFFFFFu, b);
+        bits |= bad_nibble(b) << 4;
+        pack4_fast(v.z, 0xFFFFFFFFu, b);
+        bits |= bad_nibble(b) << 8;
+        pack4_fast(v.w, 0xFFFFFFFFu, b);
+        bits |= bad_nibble(b) << 12;
+        if (pc == at >> 4) bits &= 0xFFFFu << (at & 15u);
+        if (bits) {
+            const int i = (int)(16u * pc + (uint32_t)__builtin_ctz(bits) - at);
+            return i < m ? i : m;
+        }
+        ++pc;
+    }
+    return m;
+}
+
+// Stage `np` 16-byte pieces of ASCII from src as codes (codes[0] is the first
+// piece's word) and set the bits of those with a byte that is not a base
+// (the first piece is number `first`).  kStageRows loads in flight per lane.
+// Returns, the same for every lane, whether there was such a piece.
+constexpr int kStageRows = 4;
+
+template <class Cnt>
+__device__ __forceinline__ bool stage_pieces(const uint4 *__restrict__ src, int np, uint32_t *codes, uint32_t *bad,
+                                             int first, int lane, Cnt &cnt) {
+    bool any = false;
+#pragma unroll 1
+    for (int c0 = 0; c0 < np; c0 += 64 * kStageRows) {
+        uint4 r[kStageRows];
+#pragma unroll
+        for (int u = 0; u < kStageRows; ++u) {
+            const int c = c0 + 64 * u + lane;
+            if (c < np) {
+                r[u] = load_stream16(src + c);
+                cnt.touch(src + c, 16);
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < kStageRows; ++u) {
+            const int c = c0 + 64 * u + lane;
+            if (c < np) {
+                uint32_t b;
+                codes[c] = convert16(r[u], b);
+                if (b) {
+                    atomicOr(&bad[(first + c) >> 5], 1u << ((first + c) & 31));
+                    any = true;
+                }
+            }
+        }
+    }
+    return __any(any);
+}
+
+// Searches the wave's queued reads, each by a group of `size` neighbouring
+// lanes: as many as the wave has for each read (32 reads: two lanes each;
+// one read: all 64), the lanes of a group probing the interval between the
+// bounds at as many evenly spaced rows at a time.  A full queue thus takes
+// few loads per read, a short one few loads one after the other: with 8
+// lanes per read a bracket of 1000 rows takes 4 steps instead of 10, which is
+// what bounds small batches (16 Mbp, 20,000 reads of 150 bases: 15.4 us,
+// 24.6 with one lane per read; 64 reads of 30-300: 8.0 us, 11.2).  A group
+// goes through the searches of finish_read in turn (LB of P[0..v), then LB
+// and RB of P[0..l)) without waiting for the other groups.
+template <class Cnt>
+__device__ __forceinline__ void search_queued(const DevIndex &ix, const uint64_t *t_key, const int32_t *t_sa, int levels,
+                                              const WaveArea &w, int queued, int lane, int4 *__restrict__ out, Cnt &cnt) {
+    const int bits = 6 - (queued > 1 ? 32 - __builtin_clz((unsigned)queued - 1u) : 0);
+    const int size = 1 << bits, sub = lane & (size - 1), first_lane = lane - sub;
+    if ((lane >> bits) >= queued) return;
+    const uint64_t ones = size == 64 ? ~0ull : (1ull << size) - 1ull;
+    const uint32_t share = 0xFFFFFFFFu / (uint32_t)(size + 1) * (uint32_t)(sub + 1);  // of the rows inside, times 2^32
+    const uint32_t *r = w.pool + w.rec_at[lane >> bits];
+    const int id = (int)r[0], m = (int)(r[1] & 0xFFFFu), v = (int)(r[1] >> 16);
+    const CodeQuery q{r + kRecHead - 1, 0};
+    LbState st;
+    if (r[3]) {
+        open_bracket(ix, (int)r[2], (int)r[3], st);
+    } else {
+        lb_tile<kWordsInLds>(ix, t_key, t_sa, levels, q, v, st, cnt);
+    }
+    // phase 0: LB search of P[0..v), all of st in use; 1 and 2: LB and RB
+    // search of P[0..plen) between st.L and st.R
+    int phase = 0, plen = v, lo = 0, above = 0, above_lcp = 0;
+    for (;;) {
+        if (st.R == st.L + 1) {
+            if (phase == 0) {
+                const bool exact = v == m && st.lcpR == m;
+                const int l = max_i(st.lcpL, st.lcpR);
+                if (l == 0) {
+                    lo = 0;
+                    st.R = ix.n;
+                    plen = 0;
+                    break;
+                }
+                plen = l;
+                above = st.R;
+                above_lcp = st.lcpR;
+                lo = st.R;
+                phase = 1;
+                if (!exact && st.lcpL == l) {  // rows below the insertion point share P[0..l)
+                    st.R = st.L;
+                    st.lcpR = l;
+                    st.L = st.Llt;
+                    st.lcpL = st.lcpLlt;
+                    continue;
+                }
+            } else if (phase == 1) {
+                lo = st.R;
+            }
+            if (phase == 2) break;
+            if (above_lcp < plen) {  // no row above the insertion point does
+                st.R = above;
+                break;
+            }
+            phase = 2;
+            st.L = above;
+            st.lcpL = above_lcp;
+            st.R = st.Rlt;
+            st.lcpR = st.lcpRlt;
+            continue;
+        }
+        const int inside = st.R - st.L - 1;
+        const bool all = inside <= size;  // every row between the bounds at once
+        const int piv = st.L + 1 + (all ? sub : (int)__umulhi((uint32_t)inside, share));
+        const bool probe = !all || sub < inside;
+        int lcp = 0;
+        bool left = false;
+        if (probe) {
+            const RowHead row = row_head(ix.rows, piv);
+            cnt.index_touch(ix.rows + piv, 16);
+            cnt.key_probe();
+            const int sign = compare_row<kWordsInLds>(ix, q, plen, ix.rows + piv, row.pos, row.key0,
+                                                      min_i(st.lcpL, st.lcpR), lcp, cnt);
+            left = phase == 2 ? sign < 0 : sign <= 0;
+        }
+        // the group's first probe that moves R, and the one before it, which moves L
+        const int probes = all ? inside : size;
+        const uint64_t lefts = (wave_ballot(left) >> first_lane) & ones;
+        const int to_r = lefts ? (int)__builtin_ctzll(lefts) : probes;
+        const int lane_r = first_lane + min_i(to_r, size - 1), lane_l = first_lane + max_i(to_r - 1, 0);
+        const int piv_r = __shfl(piv, lane_r, 64), lcp_r = __shfl(lcp, lane_r, 64);
+        const int piv_l = __shfl(piv, lane_l, 64), lcp_l = __shfl(lcp, lane_l, 64);
+        if (phase == 0) {
+            // the last row on either side that shares fewer bases than the new bound
+            const uint64_t fewer_l = (wave_ballot(lcp < lcp_l) >> first_lane) & ones & ((1ull << max_i(to_r - 1, 0)) - 1ull);
+            const uint64_t fewer_r =
+                to_r < probes ? (wave_ballot(probe && lcp < lcp_r) >> first_lane) & ones & ~((2ull << to_r) - 1ull) : 0ull;
+            const int lane_fl = first_lane + (fewer_l ? 63 - (int)__builtin_clzll(fewer_l) : 0);
+            const int lane_fr = first_lane + (fewer_r ? (int)__builtin_ctzll(fewer_r) : 0);
+            const int piv_fl = __shfl(piv, lane_fl, 64), lcp_fl = __shfl(lcp, lane_fl, 64);
+            const int piv_fr = __shfl(piv, lane_fr, 64), lcp_fr = __shfl(lcp, lane_fr, 64);
+            if (to_r > 0) {
+                if (fewer_l) {
+                    st.Llt = piv_fl;
+                    st.lcpLlt = lcp_fl;
+                } else if (lcp_l > st.lcpL) {
+                    st.Llt = st.L;
+                    st.lcpLlt = st.lcpL;
+                }
+            }
+            if (to_r < probes) {
+                if (fewer_r) {
+                    st.Rlt = piv_fr;
+                    st.lcpRlt = lcp_fr;
+                } else if (lcp_r > st.lcpR) {
+                    st.Rlt = st.R;
+                    st.lcpRlt = st.lcpR;
+                }
+            }
+        }
+        if (to_r > 0) {
+            st.L = piv_l;
+            st.lcpL = lcp_l;
+        }
+        if (to_r < probes) {
+            st.R = piv_r;
+            st.lcpR = lcp_r;
+        }
+    }
+    if (sub == 0) {
+        store_stream16(out + id, make_int4(lo, st.R, plen, plen == m ? (int)kHitExact : 0));
+        cnt.touch(out + id, 16);
+    }
+}
+
+// The search kernel of a batch in input order: it takes the reads as they
+// lie in memory (ASCII, with CSR offsets or with an end array) and needs no
+// pass before or after it.
+//
+// Work: chunks of 2^shift consecutive reads, one read per lane, taken as in
+// search_packed_kernel; batches too small to give every wave 64 reads use
+// smaller chunks.  For a chunk the wave
+//   1. stages the reads' bytes as 2-bit codes in its LDS area: runs of reads
+//      that follow each other in memory, as many as fit (reads of up to
+//      SA_MAX_READ bases; what does not fit is the next turn's), with
+//      coalesced 16-byte loads.  The codes stay in LDS and the comparisons
+//      take them from there word by word, so that a query of any length
+//      costs no registers;
+//   2. looks up each read's prefix-table entry.  An entry that answers the
+//      read, or whose bracket is a single row (one comparison then gives the
+//      whole result), is finished here;
+//   3. queues every other read (brackets of more rows, reads shorter than
+//      the table's strings, and all reads when there is no table): its codes
+//      and its entry are copied into the wave's record pool.  When the pool
+//      is full, or after the last chunk (after each turn with defer == 0), the
+//      queued reads are searched together, so that long binary searches run
+//      with all lanes busy and hold up nobody (search_queued).
+//
+// What bounds it: scattered lines and their latency.  On MI355X a random
+// 16-byte load brings in a 128-byte line whatever the cache policy (loads of
+// both halves of a line run at the rate of one), at most 52-58 G lines/s;
+// the 250 Mbp / 64M x 150 batch takes 233 M line misses (3.6 per read: 1.2
+// of ASCII, the table entry, the text) at 48 G/s.  Measured before (words in
+// registers, a second kernel for long reads, set-aside reads read again) and
+// after: that batch 5.33 and 4.86 ms; 16 Mbp, 4M x 100 bases 393 and 292 us,
+// 4M x 20-300 580 and 390 us, 50,001 x 20-1024 264 and 39 us, 65,536 x 1024
+// (on 10 Mbp) 114 and 53 us, 64 x 30-300 36 and 9 us.  Vector instructions
+// per chunk of 64 fell to a third (965 for that first batch).
+template <bool COUNT, bool TILE>
+__global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(COUNT ? 1 : kSearchWavesPerSimd))) void search_reads_kernel(
+    DevIndex ix, int levels, int use_table_i, int group, int shift, int defer, InlineArea area,
+    unsigned long long *__restrict__ stats, const uint8_t *__restrict__ reads, const int64_t *__restrict__ offs,
+    const int64_t *__restrict__ ends, int64_t nreads, int4 *__restrict__ out) {
+    extern __shared__ uint64_t smem[];
+    __shared__ unsigned s_next;
+    const int lane = threadIdx.x & 63;
+    // the tree's top levels: in LDS when every search starts there (TILE),
+    // else read from memory by the few reads that need them
+    const uint64_t *t_key = ix.tile_key;
+    const int32_t *t_sa = ix.tile_sa;
+    if constexpr (TILE) {
+        const int nodes = (1 << levels) - 1;
+        uint64_t *s_key = smem;
+        int32_t *s_sa = reinterpret_cast<int32_t *>(smem + nodes);
+        for (int i = threadIdx.x; i < nodes; i += blockDim.x) {
+            s_key[i] = ix.tile_key[i];
+            s_sa[i] = ix.tile_sa[i];
+        }
+        t_key = s_key;
+        t_sa = s_sa;
+    }
+    if (threadIdx.x == 0) s_next = 0u;
+    __syncthreads();
+    WaveArea w;
+    w.codes = reinterpret_cast<uint32_t *>(smem) + area.first_word + (threadIdx.x >> 6) * area.wave_words;
+    w.bad = w.codes + kStagePieces + 4;
+    w.rec_at = w.bad + kStageBadWords;
+    w.pool = w.rec_at + kQueueReads;
+    using Cnt = typename std::conditional<COUNT, Count, NoCount>::type;
+    Cnt cnt;
+    uint32_t nsearched = 0, nqwords = 0;
+    const bool use_table = use_table_i != 0 && ix.ptab_k > 0;
+    const int K = ix.ptab_k;
+    const int64_t nchunks = (nreads + (1 << shift) - 1) >> shift;
+    const int64_t G = gridDim.x, rank = workgroup_rank();
+
+    int64_t c1 = take_chunk(&s_next, group, G, rank, lane, nchunks), a1, e1;
+    chunk_offsets(offs, ends, c1, shift, nreads, lane, a1, e1);
+    int64_t a = 0;         // this lane's read of the current chunk: where it starts, its length and its id
+    int m = 0, rid = 0;
+    uint64_t todo = 0;     // lanes of the current chunk whose reads are not staged yet
+    uint64_t pend = 0;     // lanes whose staged reads wait to be queued
+    int mv = 0;            // of a staged read: its leading bases, its place in the code stream, its bracket
+    uint32_t at = 0, row = 0, size = 0;
+    int queued = 0, used = 0;  // records in the pool, words of it in use (wave-uniform)
+    for (;;) {
+        if (pend) {
+            // as many as fit, each a record of 4 words and its codes
+            const CodeQuery q = code_query(w.codes, at);
+            const int nd = (mv + 15) >> 4;
+            const int ndmax = wave_max7(nd, pend), stride = kRecHead + ndmax;
+            const int room = min_i(kQueueReads - queued, (kPoolWords - used) / stride);
+            const int my = __popcll(pend & ((1ull << lane) - 1ull));
+            const bool mine = (pend >> lane) & 1ull;
+            const bool push = mine && my < room;
+            const int to = used + my * stride;
+            if (push) {
+                w.rec_at[queued + my] = (uint32_t)to;
+                uint32_t *r = w.pool + to;
+                r[0] = (uint32_t)rid;
+                r[1] = (uint32_t)m | ((uint32_t)mv << 16);
+                r[2] = row;
+                r[3] = size;
+            }
+            for (int t = 0; t < ndmax; ++t)
+                if (push && t < nd) w.pool[to + kRecHead + t] = q.half(t);
+            const uint64_t pushed = wave_ballot(push);
+            const int n = __popcll(pushed);
+            pend &= ~pushed;
+            queued += n;
+            used += n * stride;
+            wave_lds_sync();
+        }
+        const bool last = c1 < 0 && todo == 0;
+        if (pend || (queued > 0 && (last || defer == 0))) {
+            search_queued(ix, t_key, t_sa, levels, w, queued, lane, out, cnt);
+            wave_lds_sync();
+            queued = 0;
+            used = 0;
+            continue;
+        }
+        if (last) break;
+        if (todo == 0) {
+            // the next chunk; its successor's offsets are loaded meanwhile
+            a = a1;
+            const int64_t m64 = e1 - a1;
+            const int64_t j = (c1 << shift) + lane;
+            const bool active = lane < (1 << shift) && j < nreads;
+            rid = (int)j;
+            c1 = take_chunk(&s_next, group, G, rank, lane, nchunks);
+            chunk_offsets(offs, ends, c1, shift, nreads, lane, a1, e1);
+            const bool valid = active && m64 >= 0 && m64 <= SA_MAX_READ;
+            if (COUNT && active) {
+                cnt.touch(offs + j, ends ? 8 : 16);
+                if (ends) cnt.touch(ends + j, 8);
+                if (valid) {
+                    nsearched++;
+                    nqwords += (uint32_t)max_i(1, (int)((m64 + 31) >> 5));
+                }
+            }
+            if (active && (!valid || m64 == 0))
+                store_stream16(out + rid, valid ? make_int4(0, ix.n, 0, (int)kHitExact)
+                                                : make_int4(0, 0, 0, (int)kHitTooLong));
+            m = (int)m64;
+            todo = wave_ballot(valid && m64 > 0);
+            if (todo == 0) continue;
+        }
+        // stage as many of the reads as fit
+        if (lane < kStageBadWords) w.bad[lane] = 0;
+        wave_lds_sync();
+        int filled = 0;
+        uint64_t staged = 0;
+        bool any_bad = false;
+        do {
+            const int f = __ffsll((unsigned long long)todo) - 1;
+            const uint8_t *A0 = reinterpret_cast<const uint8_t *>((uintptr_t)(reads + lane_value(a, f)) & ~(uintptr_t)15);
+            // the run: lanes f, f + 1, ... while each read starts where the one before ends and still fits
+            const int64_t e = a + m, before = __shfl_up(e, 1, 64);
+            const int64_t stop = (int64_t)((((uintptr_t)(reads + e) + 15) & ~(uintptr_t)15) - (uintptr_t)A0);
+            const bool in = ((todo >> lane) & 1ull) != 0;
+            const bool ends_run = lane >= f && (!in || (lane > f && a != before) ||
+                                                stop > (int64_t)(kStagePieces - filled) * 16);
+            const uint64_t cut = wave_ballot(ends_run);
+            const int end = cut ? __ffsll((unsigned long long)cut) - 1 : 64;
+            if (end == f) break;  // no room for one more
+            const int np = (int)(lane_value(stop, end - 1) >> 4);
+            if (lane >= f && lane < end) at = 16u * (uint32_t)filled + (uint32_t)((uintptr_t)(reads + a) - (uintptr_t)A0);
+            any_bad |= stage_pieces(reinterpret_cast<const uint4 *>(A0), np, w.codes + 1 + filled, w.bad, filled, lane, cnt);
+            const uint64_t run = (end == 64 ? ~0ull : (1ull << end) - 1ull) & ~((1ull << f) - 1ull);
+            staged |= run;
+            todo &= ~run;
+            filled += np;
+        } while (todo);
+        wave_lds_sync();
+        const bool mine = (staged >> lane) & 1ull;
+        const CodeQuery q = code_query(w.codes, at);
+        mv = m;
+        if (any_bad && mine) mv = first_non_base(reads, a, m, at, w.bad);
+        size = 0;
+        bool queue = mine;
+        int4 hit = make_int4(0, ix.n, 0, 0);
+        if (mine && mv == 0) {
+            queue = false;
+        } else if (mine && use_table && mv >= K) {
+            const uint64_t q0 = q[0];
+            const PrefixEntry ent = table_entry(ix, (uint32_t)(q0 >> (64 - 2 * K)), cnt);
+            row = ent.row;
+            size = ent.size;
+            if (size & kPtabAnswer) {
+                hit = make_int4(ent.pos, (int)ent.next, (int)(size & ~kPtabAnswer), 0);
+                queue = false;
+            } else if (size == 1) {
+                // the bracket's one row is the pivot: what it shares with the read is the match
+                const uint64_t key = (q0 & ~(~0ull >> (2 * K))) | ((uint64_t)ent.next << (32 - 2 * K));
+                int lcp;
+                cnt.global_probe();
+                compare_row<kWordsInLds>(ix, q, mv, nullptr, ent.pos, key, 0, lcp, cnt, K + 16);
+                hit = make_int4((int)row, (int)row + 1, lcp, lcp == m ? (int)kHitExact : 0);
+                queue = false;
+            }
+        }
+        if (mine && !queue) {
+            store_stream16(out + rid, hit);
+            cnt.touch(out + rid, 16);
+        }
+        pend = wave_ballot(queue);
+    }
+    if constexpr (COUNT) {
+        wave_add(&stats[3], nsearched);
+        wave_add(&stats[4], nqwords);
+        add_counts(stats, cnt);
     }
 }
 
@@ -1411,36 +1622,21 @@ __global__ __launch_bounds__(256) void search_plain_kernel(DevIndex ix, BatchBuf
     }
 }
 
-// Dynamic LDS the inline-packing kernels may take (set by prepare_kernels
-// from the device's limit per workgroup).
+// Dynamic LDS a search kernel may take (set by prepare_kernels from the
+// device's limit per workgroup).
 std::atomic<size_t> g_inline_lds{0};
 
-template <int BLOCK, bool COUNT, bool INLINE, int WQ = kWMax>
-hipError_t allow_tile_lds(size_t inline_lds) {
-    return hipFuncSetAttribute(reinterpret_cast<const void *>(&search_tuned_kernel<BLOCK, COUNT, INLINE, WQ>),
-                               hipFuncAttributeMaxDynamicSharedMemorySize,
-                               INLINE ? (int)inline_lds : (int)tile_lds_bytes(kMaxTileLevels));
+template <class F>
+hipError_t allow_lds(F *kernel, size_t bytes) {
+    return hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
+                               (int)bytes);
 }
 
 template <int BLOCK, bool COUNT>
-hipError_t launch_tuned_block(const DevIndex &ix, int levels, int use_table, int group, int defer, int grid,
-                              const BatchBuffers &b,
-                              const uint32_t *order, const uint8_t *reads, const int64_t *offs, const int64_t *ends,
-                              int64_t nreads, int words, int4 *out, hipStream_t s) {
-    if (offs) {
-        const size_t lds = tuned_lds_bytes(levels, BLOCK, true, words);
-        if (lds > g_inline_lds.load()) return hipErrorInvalidValue;
-        if (words == kShortWords)
-            hipLaunchKernelGGL((search_tuned_kernel<BLOCK, COUNT, true, kShortWords>), dim3(grid), dim3(BLOCK), lds, s,
-                               ix, levels, use_table, group, defer, b, order, reads, offs, ends, nreads, out);
-        else
-            hipLaunchKernelGGL((search_tuned_kernel<BLOCK, COUNT, true, kWMax>), dim3(grid), dim3(BLOCK), lds, s, ix,
-                               levels, use_table, group, defer, b, order, reads, offs, ends, nreads, out);
-    } else {
-        hipLaunchKernelGGL((search_tuned_kernel<BLOCK, COUNT, false, kWMax>), dim3(grid), dim3(BLOCK),
-                           tile_lds_bytes(levels), s, ix, levels, use_table, group, 0, b, order, reads, offs, ends,
-                           nreads, out);
-    }
+hipError_t launch_packed_block(const DevIndex &ix, int levels, int use_table, int group, int grid,
+                               const BatchBuffers &b, const uint32_t *order, int64_t nreads, int4 *out, hipStream_t s) {
+    hipLaunchKernelGGL((search_packed_kernel<BLOCK, COUNT>), dim3(grid), dim3(BLOCK), tile_lds_bytes(levels), s, ix,
+                       levels, use_table, group, b, order, nreads, out);
     return hipGetLastError();
 }
 
@@ -1553,9 +1749,7 @@ __global__ __launch_bounds__(64) void search_long_kernel(DevIndex ix, const uint
                                                          const uint32_t *__restrict__ order,
                                                          const uint32_t *__restrict__ sorted_key, int key_shift,
                                                          uint32_t key_mask, uint32_t long_field, int use_table_i,
-                                                         int lengths_from_offs, int long_min,
-                                                         const int64_t *__restrict__ ends, int64_t nreads,
-                                                         int4 *__restrict__ out) {
+                                                         int64_t nreads, int4 *__restrict__ out) {
     __shared__ uint64_t slot[64][kLongWords];
     __shared__ int64_t s_first;
     const int lane = threadIdx.x;
@@ -1583,18 +1777,10 @@ __global__ __launch_bounds__(64) void search_long_kernel(DevIndex ix, const uint
         const int64_t j = first + (c << 6) + lane;
         const bool act = j < nreads;
         const int rid = act ? (order ? (int)order[j] : (int)j) : 0;
-        ReadLen lm;
-        if (lengths_from_offs) {  // input order, CSR offsets: a read of long_min+1 .. SA_MAX_READ bases is long
-            const int64_t m64 = act ? (ends ? ends[rid] : offs[rid + 1]) - offs[rid] : -1;
-            const bool lng = m64 > long_min && m64 <= SA_MAX_READ;
-            lm = decode_len(encode_len(lng ? (int)m64 : -1, lng ? -1 : 0, 0));
-            if (COUNT && act) cnt.touch(offs + rid, 16);
-        } else {
-            lm = decode_len(act ? b.qlm[rid] : encode_len(-1, 0, 0));
-            if (COUNT && act) {
-                if (order) cnt.touch(order + j, 4);
-                cnt.touch(b.qlm + rid, 8);
-            }
+        const ReadLen lm = decode_len(act ? b.qlm[rid] : encode_len(-1, 0, 0));
+        if (COUNT && act) {
+            if (order) cnt.touch(order + j, 4);
+            cnt.touch(b.qlm + rid, 8);
         }
         const bool is_long = act && lm.m >= 0 && lm.mv < 0;
         uint64_t todo = wave_ballot(is_long);
@@ -1605,22 +1791,15 @@ __global__ __launch_bounds__(64) void search_long_kernel(DevIndex ix, const uint
         if (is_long) {
             const LdsQuery q{slot[lane]};
             if (COUNT) { nsearched++; nqwords += (uint32_t)((lm.m + 31) >> 5); }
-            out[rid] = match_read<kLongWords>(ix, nullptr, nullptr, 0, use_table, q, lm.m, mv_mine, kNoBudget, cnt);
+            out[rid] = match_read<kWordsInLds>(ix, nullptr, nullptr, 0, use_table, q, lm.m, mv_mine, cnt);
             cnt.touch(out + rid, 16);
         }
         __syncthreads();  // before the next chunk rewrites the slots
     }
     if constexpr (COUNT) {
-        wave_add(&b.stats[0], cnt.global);
-        wave_add(&b.stats[1], cnt.words);
-        wave_add(&b.stats[2], cnt.tile);
         wave_add(&b.stats[3], nsearched);
         wave_add(&b.stats[4], nqwords);
-        wave_add(&b.stats[5], cnt.keys);
-        wave_add(&b.stats[6], cnt.table);
-        wave_add64(&b.stats[7], cnt.touched);
-        wave_add64(&b.stats[8], cnt.scattered);
-        wave_add(&b.stats[9], cnt.index_loads);
+        add_counts(b.stats, cnt);
     }
 }
 
@@ -1732,18 +1911,15 @@ hipError_t prepare_kernels() {
         return e;
     // room for the kernels' static LDS
     const size_t inline_lds = std::min(kLdsBytes, per_block > 256 ? (size_t)per_block - 256 : (size_t)0);
-    if ((e = allow_tile_lds<256, false, false>(inline_lds)) != hipSuccess ||
-        (e = allow_tile_lds<512, false, false>(inline_lds)) != hipSuccess ||
-        (e = allow_tile_lds<1024, false, false>(inline_lds)) != hipSuccess ||
-        (e = allow_tile_lds<256, true, false>(inline_lds)) != hipSuccess ||
-        (e = allow_tile_lds<256, false, true>(inline_lds)) != hipSuccess ||
-        (e = allow_tile_lds<512, false, true>(inline_lds)) != hipSuccess ||
-        (e = allow_tile_lds<1024, false, true>(inline_lds)) != hipSuccess ||
-        (e = allow_tile_lds<256, true, true>(inline_lds)) != hipSuccess ||
-        (e = allow_tile_lds<256, false, true, kShortWords>(inline_lds)) != hipSuccess ||
-        (e = allow_tile_lds<512, false, true, kShortWords>(inline_lds)) != hipSuccess ||
-        (e = allow_tile_lds<1024, false, true, kShortWords>(inline_lds)) != hipSuccess ||
-        (e = allow_tile_lds<256, true, true, kShortWords>(inline_lds)) != hipSuccess)
+    const size_t tile = tile_lds_bytes(kMaxTileLevels);
+    if ((e = allow_lds(search_packed_kernel<256, false>, tile)) != hipSuccess ||
+        (e = allow_lds(search_packed_kernel<512, false>, tile)) != hipSuccess ||
+        (e = allow_lds(search_packed_kernel<1024, false>, tile)) != hipSuccess ||
+        (e = allow_lds(search_packed_kernel<256, true>, tile)) != hipSuccess ||
+        (e = allow_lds(search_reads_kernel<false, false>, inline_lds)) != hipSuccess ||
+        (e = allow_lds(search_reads_kernel<false, true>, inline_lds)) != hipSuccess ||
+        (e = allow_lds(search_reads_kernel<true, false>, inline_lds)) != hipSuccess ||
+        (e = allow_lds(search_reads_kernel<true, true>, inline_lds)) != hipSuccess)
         return e;
     g_inline_lds.store(inline_lds);
     return hipSuccess;
@@ -1787,28 +1963,68 @@ hipError_t launch_sort(const BatchBuffers &b, int64_t nreads, int lo_bit, int hi
                                       hi_bit, which, s);
 }
 
-hipError_t launch_search_tuned(const DevIndex &ix, int levels, int use_table, int block, int grid, int group,
-                               int defer, const BatchBuffers &b, const uint32_t *order, const uint8_t *reads,
-                               const int64_t *offs, const int64_t *ends, int64_t nreads, int words, void *out,
-                               bool count, hipStream_t s) {
+hipError_t launch_search_packed(const DevIndex &ix, int levels, int use_table, int block, int grid, int group,
+                                const BatchBuffers &b, const uint32_t *order, int64_t nreads, void *out, bool count,
+                                hipStream_t s) {
     int4 *o = static_cast<int4 *>(out);
-    if (group < 1 || (offs && order)) return hipErrorInvalidValue;
-    if (words != kShortWords && words != kWMax) return hipErrorInvalidValue;
+    if (group < 1) return hipErrorInvalidValue;
     if (count)  // counts do not depend on the workgroup shape or the work split
-        return launch_tuned_block<256, true>(ix, levels, use_table, group, defer, grid * (block / 256), b, order, reads, offs,
-                                             ends, nreads, words, o, s);
+        return launch_packed_block<256, true>(ix, levels, use_table, group, grid * (block / 256), b, order, nreads, o, s);
     switch (block) {
-        case 256:
-            return launch_tuned_block<256, false>(ix, levels, use_table, group, defer, grid, b, order, reads, offs, ends, nreads,
-                                                   words, o, s);
-        case 512:
-            return launch_tuned_block<512, false>(ix, levels, use_table, group, defer, grid, b, order, reads, offs, ends, nreads,
-                                                   words, o, s);
-        case 1024:
-            return launch_tuned_block<1024, false>(ix, levels, use_table, group, defer, grid, b, order, reads, offs, ends, nreads,
-                                                   words, o, s);
+        case 256: return launch_packed_block<256, false>(ix, levels, use_table, group, grid, b, order, nreads, o, s);
+        case 512: return launch_packed_block<512, false>(ix, levels, use_table, group, grid, b, order, nreads, o, s);
+        case 1024: return launch_packed_block<1024, false>(ix, levels, use_table, group, grid, b, order, nreads, o, s);
         default: return hipErrorInvalidValue;
     }
+}
+
+hipError_t launch_search_reads(const DevIndex &ix, int levels, int use_table, int block, int blocks_per_cu, int cus,
+                               int group, int defer, unsigned long long *stats, const uint8_t *reads,
+                               const int64_t *offs, const int64_t *ends, int64_t nreads, void *out, bool count,
+                               hipStream_t s) {
+    int4 *o = static_cast<int4 *>(out);
+    if (group < 1 || block < 64 || block > 1024) return hipErrorInvalidValue;
+    // without a prefix table every search starts at the root: stage the tile, when it fits beside the waves' areas
+    const bool table = use_table && ix.ptab_k > 0;
+    InlineArea area = inline_area(0);
+    bool tile = !table;
+    if (tile) {
+        area = inline_area(levels);
+        tile = inline_lds_bytes(area, block) <= g_inline_lds.load();
+        if (!tile) area = inline_area(0);
+    }
+    while (block > 256 && inline_lds_bytes(area, block) > g_inline_lds.load()) {
+        block /= 2;
+        blocks_per_cu *= 2;
+    }
+    const size_t lds = inline_lds_bytes(area, block);
+    if (lds > g_inline_lds.load()) return hipErrorInvalidValue;
+    // Persistent workgroups, no more than there are chunks for.  A batch too
+    // small to give half of the waves a chunk of 64 reads is cut into smaller
+    // chunks, down to one read: a wave's time grows with its longest search
+    // and with the bytes it stages, so few reads a wave are done sooner (64
+    // reads of 30-300 bases: 8 us as 64 chunks, 18 as one).  For all waves
+    // rather than half, launching them costs more than their smaller chunks
+    // save (100,000 reads of 25 bases: 13.0 against 10.0 us).
+    const int64_t waves = (int64_t)cus * blocks_per_cu * (block / 64);
+    int shift = 6;
+    while (shift > 0 && (nreads >> shift) < waves / 2) --shift;
+    const int64_t chunks = (nreads + (1 << shift) - 1) >> shift;
+    const int64_t gmax = (int64_t)cus * blocks_per_cu, per = block / 64;
+    group = (int)std::max<int64_t>(1, std::min<int64_t>(group, chunks / gmax));
+    const unsigned grid = (unsigned)std::min<int64_t>(gmax, (chunks + group * per - 1) / (group * per));
+#define SAMATCH_LAUNCH(C, T)                                                                                      \
+    hipLaunchKernelGGL((search_reads_kernel<C, T>), dim3(grid), dim3(block), lds, s, ix, levels, use_table, group, shift, \
+                       defer, area, stats, reads, offs, ends, nreads, o)
+    if (count) {
+        if (tile) SAMATCH_LAUNCH(true, true);
+        else SAMATCH_LAUNCH(true, false);
+    } else {
+        if (tile) SAMATCH_LAUNCH(false, true);
+        else SAMATCH_LAUNCH(false, false);
+    }
+#undef SAMATCH_LAUNCH
+    return hipGetLastError();
 }
 
 hipError_t launch_build_prefix_table(const DevIndex &ix, int k, PrefixEntry *tab, hipStream_t s) {
@@ -1832,18 +2048,16 @@ hipError_t launch_build_prefix_table(const DevIndex &ix, int k, PrefixEntry *tab
 
 hipError_t launch_search_long(const DevIndex &ix, const uint8_t *reads, const int64_t *offs, const BatchBuffers &b,
                               const uint32_t *order, const uint32_t *sorted_key, int key_shift, uint32_t key_mask,
-                              uint32_t long_field, int use_table, bool lengths_from_offs, int long_min,
-                              const int64_t *ends, int grid, int64_t nreads, void *out, bool count, hipStream_t s) {
+                              uint32_t long_field, int use_table, int grid, int64_t nreads, void *out, bool count,
+                              hipStream_t s) {
     int4 *o = static_cast<int4 *>(out);
     const dim3 g((unsigned)(grid > 0 ? grid : 1));
-    if (lengths_from_offs && order) return hipErrorInvalidValue;
-    const int lfo = lengths_from_offs ? 1 : 0;
     if (count)
         hipLaunchKernelGGL(search_long_kernel<true>, g, dim3(64), 0, s, ix, reads, offs, b, order, sorted_key,
-                           key_shift, key_mask, long_field, use_table, lfo, long_min, ends, nreads, o);
+                           key_shift, key_mask, long_field, use_table, nreads, o);
     else
         hipLaunchKernelGGL(search_long_kernel<false>, g, dim3(64), 0, s, ix, reads, offs, b, order, sorted_key,
-                           key_shift, key_mask, long_field, use_table, lfo, long_min, ends, nreads, o);
+                           key_shift, key_mask, long_field, use_table, nreads, o);
     return hipGetLastError();
 }
 

@@ -187,6 +187,15 @@ std::vector<sa_match_cfg> stage1_candidates(const sa_dindex *d) {
                 c.blocks_per_cu = per_cu;
                 out.push_back(c);
             }
+    // the shape that fills the compute unit's LDS with the search kernel's waves
+    for (int lv : levels) {
+        sa_match_cfg c = base_cfg(d);
+        c.tile_levels = lv;
+        c.block = 512;
+        c.blocks_per_cu = 3;
+        c.max_words = kShortWords;
+        out.push_back(c);
+    }
     return out;
 }
 
@@ -218,11 +227,10 @@ std::vector<sa_match_cfg> stage1b_candidates(const sa_dindex *d, const sa_match_
     return out;
 }
 
-// Stage 1c, when nearly every read of the batch fits kShortWords words
-// (the rest go to the long-read kernel): the register-light search kernel
-// in the workgroup shapes that fill its six waves per SIMD, around the best
-// so far, with a tile of at most 8 levels when the index has a prefix
-// table (so that the workgroups' LDS lets that many waves in).
+// Stage 1c, when nearly every read of the batch fits kShortWords words: the
+// workgroup shapes that fill the search kernel's six waves per SIMD, around
+// the best so far, with a tile of at most 8 levels when the index has a
+// prefix table.
 std::vector<sa_match_cfg> stage1c_candidates(const sa_dindex *d, const sa_match_cfg &top,
                                              const std::vector<int64_t> &hist) {
     std::vector<sa_match_cfg> out;
@@ -244,17 +252,13 @@ std::vector<sa_match_cfg> stage1c_candidates(const sa_dindex *d, const sa_match_
 }
 
 // Stage 1d, around the best so far, when the search kernel packs its reads:
-// the probe budget after which a read is set aside for a chunk of such
-// reads (0 = never).
+// reads of more than one comparison set aside, or searched at once (0).
 std::vector<sa_match_cfg> stage1d_candidates(const sa_match_cfg &top) {
     std::vector<sa_match_cfg> out;
     if (top.sort != 0 || !top.inline_pack) return out;
-    for (int b : {0, 2, 3, 4, 6, 8}) {
-        if (b == top.defer) continue;
-        sa_match_cfg c = top;
-        c.defer = b;
-        out.push_back(c);
-    }
+    sa_match_cfg c = top;
+    c.defer = top.defer ? 0 : kDefaultDefer;
+    out.push_back(c);
     return out;
 }
 
