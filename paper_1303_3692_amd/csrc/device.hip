@@ -176,12 +176,25 @@ bool packs_inline(const sa_match_cfg &c) {
            tuned_lds_bytes(c.tile_levels, c.count ? 256 : c.block, c.max_words) <= inline_lds_limit();
 }
 
+// A batch whose settings sort it is searched in input order all the same when
+// the text is too short for a prefix table (below 4096 bases): its row
+// records (64 KB) stay in every cache, where lanes that share pivots gain
+// nothing, and the sort is a dozen launches (MI355X, 3,000 bases: 20,000 reads
+// of 150 bases 19 against 106 us, 1M of 20-300 175 against 208, 4M of 30-100
+// 456 against 467; with 65,536 bases that last one is 577 against 530).
+bool searches_inline(const sa_dindex *d, const sa_match_cfg &c) {
+    if (packs_inline(c)) return true;
+    sa_match_cfg u = c;
+    u.sort = 0;
+    return c.sort != 0 && d->n < kMinTableText && packs_inline(u);
+}
+
 // Enqueue the whole device pipeline for one batch: pack, optional prefix
 // sort, search.  All launches go to stream s.  d_ends may be NULL (CSR
 // offsets) or give each read's end (reads scattered over d_reads).
 int enqueue_batch(sa_dindex *d, Workspace *ws, const uint8_t *d_reads, const int64_t *d_offs, const int64_t *d_ends,
                   int64_t nreads, sa_hit *d_out, hipStream_t s, const sa_match_cfg &c) {
-    int rc = ws->reserve(nreads, !packs_inline(c));
+    int rc = ws->reserve(nreads, !searches_inline(d, c));
     if (rc) return rc;
     rc = enqueue_pipeline(d, ws->b, c.profile ? ws->ev : nullptr, d_reads, d_offs, d_ends, nreads, d_out, s, c);
     if (rc) return rc;
@@ -197,7 +210,7 @@ int enqueue_pipeline(sa_dindex *d, const BatchBuffers &b, const hipEvent_t *ev, 
     hipError_t e = hipSuccess;
     if (prof && (e = hipEventRecord(ev[0], s)) != hipSuccess) return hip_fail(e, "event record");
     // reads in input order: one kernel packs and searches them
-    const bool inl = packs_inline(c);
+    const bool inl = searches_inline(d, c);
     if (inl) {
         if (c.count && (e = launch_clear_stats(b, s)) != hipSuccess) return hip_fail(e, "stats clear launch");
     } else {
@@ -268,7 +281,7 @@ int run_batch(sa_dindex *d, Workspace *ws, const uint8_t *d_reads, const int64_t
     // the null stream cannot be captured; profiling and counting need eager launches
     if (!c.use_graph || !s || c.profile || c.count)
         return enqueue_batch(d, ws, d_reads, d_offs, d_ends, nreads, d_out, s, c);
-    int rc = ws->reserve(nreads, !packs_inline(c));  // no allocation may happen during capture
+    int rc = ws->reserve(nreads, !searches_inline(d, c));  // no allocation may happen during capture
     if (rc) return rc;
     for (GraphEntry &g : ws->graphs) {
         if (g.reads == d_reads && g.offs == d_offs && g.ends == d_ends && g.out == d_out && g.nreads == nreads &&
@@ -318,7 +331,7 @@ namespace {
 // about 11-15 % (k = 14: 6.47 ms, 15: 6.05, 16: 5.40); for a 16 Mbp
 // reference k = 13 and 14 gained 8 % and 3 %.
 int default_prefix_bases(int64_t n, size_t free_bytes) {
-    if (n < 4096) return 0;
+    if (n < kMinTableText) return 0;
     int k = std::max(4, std::min(kMaxPrefixBases, (int)std::lround(std::log2((double)n) / 2.0) + 2));
     while (k > 4 && (((size_t)1 << (2 * k)) + 1) * sizeof(PrefixEntry) > free_bytes / 4) k--;
     return k;
@@ -504,7 +517,7 @@ extern "C" int sa_set_prefix_table(sa_dindex *d, int k) {
     clear_error();
     if (!d) return fail(SA_EINVAL, "NULL argument");
     if (k < 0 || (k > 0 && k < 4) || k > kMaxPrefixBases) return fail(SA_EINVAL, "prefix bases must be 0 or 4.." + std::to_string(kMaxPrefixBases));
-    if (k > 0 && d->n < 4096) return fail(SA_EINVAL, "a prefix table needs a text of at least 4096 bases");
+    if (k > 0 && d->n < kMinTableText) return fail(SA_EINVAL, "a prefix table needs a text of at least 4096 bases");
     DeviceGuard g(d->device);
     if (!g.ok) return fail(SA_EDEVICE, "hipSetDevice failed");
     return set_prefix_table(d, k);
@@ -620,7 +633,7 @@ extern "C" int match_batch(const sa_dindex *dc, const char *reads, const int64_t
         most = std::max(most, r1 - r0);
         cuts.push_back(r1);
     }
-    if ((rc = ws->reserve(most, !packs_inline(c)))) return rc;  // no scratch growth between chunks
+    if ((rc = ws->reserve(most, !searches_inline(d, c)))) return rc;  // no scratch growth between chunks
     const size_t nchunks = cuts.size() - 1;
     auto finish = [&](size_t k) -> int {
         HostSlot &hs = ws->host[k & 1];

@@ -85,6 +85,8 @@ int enqueue_pipeline(sa_dindex *d, const BatchBuffers &b, const hipEvent_t *ev, 
 // Whether c's tuned search packs reads in input order itself (no pack pass,
 // no sort): then the pipeline's only scratch is b.stats.
 bool packs_inline(const sa_match_cfg &c);
+// Whether a batch with these settings takes that path on this index.
+bool searches_inline(const sa_dindex *d, const sa_match_cfg &c);
 // enqueue_batch through a captured graph when c.use_graph asks for it (and
 // the stream can be captured), else directly.
 int run_batch(sa_dindex *d, Workspace *ws, const uint8_t *d_reads, const int64_t *d_offs, const int64_t *d_ends,

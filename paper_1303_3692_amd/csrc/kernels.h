@@ -80,6 +80,7 @@ struct DevIndex {
 // Longest prefix a table may index: an entry holds the 16 bases after its
 // k, which must lie in the suffix's first 32 (4^16 + 1 entries: 64 GiB).
 constexpr int kMaxPrefixBases = 16;
+constexpr int64_t kMinTableText = 4096;  // shortest text that has a table
 
 struct BucketTable {
     int count;     // 1..8

@@ -1984,21 +1984,21 @@ hipError_t launch_search_reads(const DevIndex &ix, int levels, int use_table, in
                                hipStream_t s) {
     int4 *o = static_cast<int4 *>(out);
     if (group < 1 || block < 64 || block > 1024) return hipErrorInvalidValue;
-    // without a prefix table every search starts at the root: stage the tile, when it fits beside the waves' areas
-    const bool table = use_table && ix.ptab_k > 0;
-    InlineArea area = inline_area(0);
-    bool tile = !table;
+    const size_t limit = g_inline_lds.load();
+    if (inline_lds_bytes(inline_area(0), block) > limit) return hipErrorInvalidValue;
+    // Without a prefix table every search starts at the root: stage the tile,
+    // as deep as asked for while it does not cost a workgroup per compute
+    // unit its place (3,000 bases, 1M reads of 20-300 in three workgroups of
+    // 512 threads: 176 us with 8 levels, 226 with 10, which leave room for
+    // two).
+    const bool tile = !(use_table && ix.ptab_k > 0);
     if (tile) {
-        area = inline_area(levels);
-        tile = inline_lds_bytes(area, block) <= g_inline_lds.load();
-        if (!tile) area = inline_area(0);
+        const size_t fit = std::min<size_t>((size_t)blocks_per_cu, limit / inline_lds_bytes(inline_area(0), block));
+        while (levels > 1 && inline_lds_bytes(inline_area(levels), block) * fit > limit) --levels;
     }
-    while (block > 256 && inline_lds_bytes(area, block) > g_inline_lds.load()) {
-        block /= 2;
-        blocks_per_cu *= 2;
-    }
+    const InlineArea area = inline_area(tile ? levels : 0);
     const size_t lds = inline_lds_bytes(area, block);
-    if (lds > g_inline_lds.load()) return hipErrorInvalidValue;
+    if (lds > limit) return hipErrorInvalidValue;
     // Persistent workgroups, no more than there are chunks for.  A batch too
     // small to give half of the waves a chunk of 64 reads is cut into smaller
     // chunks, down to one read: a wave's time grows with its longest search
