@@ -374,9 +374,25 @@ int set_prefix_table(sa_dindex *d, int k) {
     return SA_OK;
 }
 
-// Device index from the packed text and either a host suffix array
-// (host_sa) or one built here on the device.
-int make_dindex(int device, int64_t n, const std::vector<uint64_t> &packed, const int32_t *host_sa,
+// Copies the text's bytes into `scratch` (device memory of at least n bytes
+// rounded up to 16), packs them into d_text and checks them.
+int pack_on_device(const char *ascii, int64_t n, uint8_t *scratch, uint64_t *d_text, int64_t words) {
+    unsigned long long *flag = nullptr, first_bad = ~0ull;
+    hipError_t e = hipMalloc((void **)&flag, sizeof *flag);
+    if (e == hipSuccess) e = hipMemcpy(scratch, ascii, (size_t)n, hipMemcpyHostToDevice);
+    if (e == hipSuccess) e = hipMemcpy(flag, &first_bad, sizeof first_bad, hipMemcpyHostToDevice);
+    if (e == hipSuccess) e = launch_pack_text(scratch, n, d_text, words, flag, nullptr);
+    if (e == hipSuccess) e = hipMemcpy(&first_bad, flag, sizeof first_bad, hipMemcpyDeviceToHost);
+    if (flag) (void)hipFree(flag);
+    if (e != hipSuccess) return hip_fail(e, "text packing");
+    if (first_bad != ~0ull) return fail_alphabet((int64_t)first_bad);
+    return SA_OK;
+}
+
+// Device index from a host index's packed text and suffix array, or, when
+// ascii is given, from the text's bytes alone: packed, checked and sorted
+// here on the device.
+int make_dindex(int device, int64_t n, const uint64_t *packed, const int32_t *host_sa, const char *ascii,
                 sa_dindex **out) {
     *out = nullptr;
     int ndev = 0;
@@ -393,7 +409,8 @@ int make_dindex(int device, int64_t n, const std::vector<uint64_t> &packed, cons
     if ((e = prepare_kernels()) != hipSuccess) return hip_fail(e, "kernel attributes");
     d->cu_count = prop.multiProcessorCount;
     std::snprintf(d->arch, sizeof d->arch, "%s", prop.gcnArchName);
-    const size_t text_bytes = sizeof(uint64_t) * packed.size();
+    const int64_t words = (n + 31) / 32 + kPadWords;
+    const size_t text_bytes = sizeof(uint64_t) * (size_t)words;
     const size_t sa_bytes = sizeof(int32_t) * (size_t)n;
     int levels = 0;
     while (levels < kMaxTileLevels && ((int64_t)1 << levels) - 1 < n) levels++;
@@ -405,8 +422,12 @@ int make_dindex(int device, int64_t n, const std::vector<uint64_t> &packed, cons
         (e = hipMalloc((void **)&d->d_tile_sa, nodes * sizeof(int32_t))) != hipSuccess ||
         (e = hipMalloc((void **)&d->d_rows, sizeof(RowRec) * (size_t)n)) != hipSuccess)
         return hip_fail(e, "index allocation");
-    if ((e = hipMemcpy(d->d_text, packed.data(), text_bytes, hipMemcpyHostToDevice)) != hipSuccess)
+    if (ascii) {
+        // the row records' memory (16 bytes a base) holds the bytes until the records are built
+        if (int rc = pack_on_device(ascii, n, reinterpret_cast<uint8_t *>(d->d_rows), d->d_text, words)) return rc;
+    } else if ((e = hipMemcpy(d->d_text, packed, text_bytes, hipMemcpyHostToDevice)) != hipSuccess) {
         return hip_fail(e, "index upload");
+    }
     if (host_sa) {
         if ((e = hipMemcpy(d->d_sa, host_sa, sa_bytes, hipMemcpyHostToDevice)) != hipSuccess)
             return hip_fail(e, "index upload");
@@ -459,22 +480,23 @@ int make_dindex(int device, int64_t n, const std::vector<uint64_t> &packed, cons
 extern "C" int sa_upload(const sa_index *ix, int device, sa_dindex **out) {
     clear_error();
     if (!ix || !out) return fail(SA_EINVAL, "NULL argument");
-    return make_dindex(device, ix->n, ix->packed, ix->sa.data(), out);
+    return make_dindex(device, ix->n, ix->packed.data(), ix->sa.data(), nullptr, out);
 }
 
 extern "C" int sa_build_device(const char *text, int64_t n, int device, sa_dindex **out) {
     clear_error();
     if (!out) return fail(SA_EINVAL, "NULL argument");
     *out = nullptr;
-    int rc = check_text(text, n);
+    int rc = check_text_size(text, n);
     if (rc) return rc;
-    std::vector<uint64_t> packed;
-    try {
-        pack_text(text, n, packed);
-    } catch (const std::bad_alloc &) {
-        return fail(SA_ENOMEM, "packing");
+    rc = make_dindex(device, n, nullptr, nullptr, text, out);
+    if (rc && rc != SA_EALPHABET) {
+        // a text that is not one is reported before any failure of the device
+        const std::string why = sa_last_error();
+        if (int bad = check_text(text, n)) return bad;
+        return fail(rc, why);
     }
-    return make_dindex(device, n, packed, nullptr, out);
+    return rc;
 }
 
 extern "C" int sa_download(const sa_dindex *d, sa_index **out) {

@@ -26,13 +26,21 @@ uint64_t fnv1a(uint64_t h, const void *p, size_t len) {
 
 namespace samatch {
 
-int check_text(const char *text, int64_t n) {
+int fail_alphabet(int64_t at) {
+    return fail(SA_EALPHABET, "reference byte " + std::to_string(at) + " is outside ACGT");
+}
+
+int check_text_size(const char *text, int64_t n) {
     if (!text) return fail(SA_EINVAL, "text is NULL");
     if (n < 1) return fail(SA_EINVAL, "reference length must be at least 1");
     if (n > 2147483647LL) return fail(SA_ETOOBIG, "reference longer than 2^31-1 bases");
+    return SA_OK;
+}
+
+int check_text(const char *text, int64_t n) {
+    if (int rc = check_text_size(text, n)) return rc;
     for (int64_t i = 0; i < n; i++)
-        if (base_code((unsigned char)text[i]) < 0)
-            return fail(SA_EALPHABET, "reference byte " + std::to_string(i) + " is outside ACGT");
+        if (base_code((unsigned char)text[i]) < 0) return fail_alphabet(i);
     return SA_OK;
 }
 

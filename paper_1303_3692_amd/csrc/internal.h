@@ -33,8 +33,12 @@ inline int base_code(unsigned char c) {
     }
 }
 
-// Validates a reference (1 <= n <= 2^31-1, bytes ACGT in either case).
+// Validates a reference (1 <= n <= 2^31-1, bytes ACGT in either case), or its
+// pointer and size alone.
 int check_text(const char *text, int64_t n);
+int check_text_size(const char *text, int64_t n);
+// The error for a reference whose byte `at` is not a base.
+int fail_alphabet(int64_t at);
 // Packs text[0..n) into ceil(n/32) + kPadWords words.
 void pack_text(const char *text, int64_t n, std::vector<uint64_t> &out);
 

@@ -104,6 +104,13 @@ struct BatchBuffers {
 // the tuned kernel use the LDS of the deepest tile.
 hipError_t prepare_kernels();
 
+// The text's n ASCII bytes (16-byte aligned, readable up to the next multiple
+// of 16) to `words` packed words: 2 bits per base, zero past the end.
+// *first_bad becomes the position of the first byte outside ACGTacgt (set it
+// to all ones before).
+hipError_t launch_pack_text(const uint8_t *ascii, int64_t n, uint64_t *text, int64_t words,
+                            unsigned long long *first_bad, hipStream_t s);
+
 hipError_t launch_build_rows(const uint64_t *text, const int32_t *sa, int32_t n, RowRec *rows, hipStream_t s);
 
 // Fills the 4^k + 1 entries of a prefix table (see PrefixEntry); ix.rows
