@@ -546,59 +546,150 @@ __global__ void build_rows_kernel(const uint64_t *__restrict__ text, const int32
 // + 1 for a suffix of at least k bases, without the +1 for a shorter one (it
 // sorts before every k-base string it is a proper prefix of).  It does not
 // decrease along the suffix array.
-__device__ __forceinline__ uint64_t row_order_key(const DevIndex &ix, int k, int r) {
-    const RowHead row = row_head(ix.rows, r);
+__device__ __forceinline__ uint64_t row_order_key(const RowHead &row, int k) {
     return 2 * (row.key0 >> (64 - 2 * k)) + (row.len >= k ? 1u : 0u);
 }
 
-// T[v] = first row whose order key reaches 2v + 1 (binary search per entry).
-__global__ void build_prefix_table_kernel(DevIndex ix, int k, int64_t first, int64_t end,
-                                          PrefixEntry *__restrict__ tab) {
-    const int64_t v = first + (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (v >= end) return;
-    const uint64_t target = 2 * (uint64_t)v + 1;
+// First row whose order key reaches `target`, found by the whole wave, 64 rows
+// at a time.
+__device__ __forceinline__ int first_row_from(const DevIndex &ix, int k, uint64_t target, int lane) {
     int lo = 0, hi = ix.n;
+    const uint32_t share = 0xFFFFFFFFu / 65u * (uint32_t)(lane + 1);
     while (lo < hi) {
-        const int mid = lo + ((hi - lo) >> 1);
-        if (row_order_key(ix, k, mid) >= target) hi = mid;
-        else lo = mid + 1;
+        const int rows = hi - lo;
+        const int piv = lo + (rows <= 64 ? lane : (int)__umulhi((uint32_t)rows, share));
+        const bool at = piv < hi;
+        const bool reached = at && row_order_key(row_head(ix.rows, piv), k) >= target;
+        const uint64_t r = wave_ballot(reached);
+        const int probes = min_i(rows, 64), to = r ? (int)__builtin_ctzll(r) : probes;
+        const int above = __shfl(piv, min_i(to, 63), 64), below = __shfl(piv, max_i(to - 1, 0), 64);
+        if (to < probes) hi = above;
+        if (to > 0) lo = below + 1;
     }
-    tab[v].row = (uint32_t)lo;
+    return lo;
 }
 
-// Second pass (after every T[v] is written): each entry's bracket size
-// and first pivot suffix, or, for a string v no suffix starts with, the
-// result of a search for v itself from the root (any read starting with v
-// has it: its longest matched prefix is shorter than v).
-__global__ void fill_prefix_entries_kernel(DevIndex ix, int k, int64_t first, int64_t end, int64_t entries,
-                                           PrefixEntry *__restrict__ tab) {
-    const int64_t v = first + (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (v >= end) return;
-    if (v == entries - 1) {  // T[4^k] = n closes the last bracket; it is never looked up
-        tab[v].size = 0;
-        tab[v].pos = 0;
-        tab[v].next = 0;
-        return;
+// The prefix table, 4^bases entries (those of one string of k - bases bases)
+// per workgroup.  Their rows are neighbours: the workgroup
+// finds the first and the last of them, marks in LDS where each string's
+// rows start and end, and takes for every string the first row not below it
+// (T) by a running minimum from the end.  A string v with rows gets its
+// bracket and the suffix at its first pivot.  For one without, the longest
+// prefix of v that occurs is the longest that has rows, found by comparing T
+// at the ends of ever larger aligned groups of entries, and T there bounds
+// its rows.  Two cases search from the root instead: strings of a workgroup
+// without any row (all have one answer), and those of a workgroup near
+// whose rows a suffix shorter than k sorts (its rows are not aligned to the
+// groups; at most k - 1 suffixes are that short).  Bound by the table's
+// bytes: 16 Mbp (268 M entries, 4.3 GB) took 16.7 ms as a binary search per
+// entry for T and a second pass from the root for the strings without rows,
+// 1.9 ms now.
+constexpr int kTabThreads = 512;  // at most: a workgroup has no more threads than entries
+constexpr int kTabBases = 6;
+constexpr int kTabSpan = 1 << (2 * kTabBases);
+constexpr int kTabRows = 4;  // entries per thread whose pivots' loads are in flight together
+
+__global__ __launch_bounds__(kTabThreads) void build_prefix_table_kernel(DevIndex ix, int k, int bases,
+                                                                         PrefixEntry *__restrict__ tab) {
+    __shared__ uint32_t first[kTabSpan + 1];  // a string's first row, then T
+    __shared__ uint32_t last[kTabSpan];       // the row after a string's last one, 0 without rows
+    __shared__ uint32_t wave_min[kTabThreads / 64];
+    __shared__ int bound[2];
+    __shared__ int near_short;
+    const int t = threadIdx.x, lane = t & 63, wave = t >> 6, threads = blockDim.x;
+    const int span = 1 << (2 * bases);  // a multiple of the threads, which are full waves
+    const uint64_t v0 = (uint64_t)blockIdx.x << (2 * bases);
+    if (t == 0) near_short = 0;
+    if (wave < 2) {
+        const int r = first_row_from(ix, k, 2 * (v0 + (wave ? (uint64_t)span : 0u)) + 1, lane);
+        if (lane == 0) bound[wave] = r;
     }
-    const int lo = (int)tab[v].row;
-    // rows [lo, T[v+1]) have order key 2v + 1 (suffixes that start with v),
-    // then 2v + 2 (suffixes shorter than k, at most k - 1, that are proper
-    // prefixes of v + 1 padded with a's); the bracket ends before the latter
-    int hi = (int)tab[v + 1].row;
-    while (hi > lo && row_head(ix.rows, hi - 1).len < k) --hi;
-    if (hi > lo) {
-        const RowHead h = row_head(ix.rows, midpoint(lo - 1, hi));
-        tab[v].size = (uint32_t)(hi - lo);
-        tab[v].pos = h.pos;
-        tab[v].next = (uint32_t)(h.key0 >> (32 - 2 * k));
-    } else {
-        const uint64_t q[1] = {(uint64_t)v << (64 - 2 * k)};
-        NoCount none;
-        const int4 r = match_read<1>(ix, nullptr, nullptr, 0, false, q, k, k, none);
-        tab[v].size = kPtabAnswer | (uint32_t)r.z;
-        tab[v].pos = r.x;
-        tab[v].next = (uint32_t)r.y;
+    __syncthreads();
+    const int r0 = bound[0], r1 = bound[1];
+    for (int i = t; i < span; i += threads) {
+        first[i] = (uint32_t)r1;
+        last[i] = 0;
     }
+    if (t == 0) first[span] = (uint32_t)r1;
+    __syncthreads();
+    for (int r = r0 + t; r < r1; r += threads) {
+        const uint64_t key = row_order_key(row_head(ix.rows, r), k);
+        const int i = (int)((key >> 1) - v0);
+        if (key & 1) {
+            if (r == r0 || row_order_key(row_head(ix.rows, r - 1), k) != key) atomicMin(&first[i], (uint32_t)r);
+            if (r + 1 == r1 || row_order_key(row_head(ix.rows, r + 1), k) != key) last[i] = (uint32_t)r + 1;
+        } else {  // below its padded string, above the one before
+            atomicMin(&first[i - 1], (uint32_t)r);
+            near_short = 1;
+        }
+    }
+    if (t < k && r0 - 1 - t >= 0 && row_head(ix.rows, r0 - 1 - t).len < k) near_short = 1;
+    __syncthreads();
+    uint32_t carry = (uint32_t)r1;
+    for (int base = span - threads; base >= 0; base -= threads) {
+        uint32_t x = first[base + t];
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            const uint32_t y = __shfl_down(x, o, 64);
+            if (lane + o < 64) x = x < y ? x : y;
+        }
+        if (lane == 0) wave_min[wave] = x;
+        __syncthreads();
+        uint32_t later = carry;  // the least of the waves after this one and of the rounds before
+        for (int u = 0; u < threads / 64; ++u) {
+            const uint32_t y = wave_min[u];
+            if (u > wave) later = later < y ? later : y;
+            carry = carry < y ? carry : y;
+        }
+        first[base + t] = x < later ? x : later;
+        __syncthreads();
+    }
+    const bool none = r0 == r1, search = near_short != 0;
+    int4 ans = make_int4(0, 0, 0, 0);
+    if (search || none) {
+        for (int i = t; i < (search ? span : threads); i += threads) {
+            if (last[i]) continue;
+            const uint64_t q[1] = {(v0 + (uint64_t)i) << (64 - 2 * k)};
+            NoCount cnt;
+            ans = match_read<1>(ix, nullptr, nullptr, 0, false, q, k, k, cnt);
+            if (search)
+                store_stream16(reinterpret_cast<int4 *>(tab + v0) + i,
+                               make_int4((int)first[i], (int)(kPtabAnswer | (uint32_t)ans.z), ans.x, ans.y));
+        }
+    }
+    for (int i0 = t; i0 < span; i0 += kTabRows * threads) {
+        RowHead h[kTabRows];
+#pragma unroll
+        for (int u = 0; u < kTabRows; ++u) {
+            const int i = i0 + u * threads;
+            if (i < span && last[i]) h[u] = row_head(ix.rows, midpoint((int)first[i] - 1, (int)last[i]));
+        }
+#pragma unroll
+        for (int u = 0; u < kTabRows; ++u) {
+            const int i = i0 + u * threads;
+            if (i >= span) break;
+            const uint32_t row = first[i], end = last[i];
+            int4 e = make_int4((int)row, (int)(end - row), h[u].pos, (int)(uint32_t)(h[u].key0 >> (32 - 2 * k)));
+            if (!end) {
+                if (search) continue;  // written above
+                if (!none) {
+                    int g = 0;
+                    uint32_t lo, hi;
+                    do {
+                        ++g;
+                        const int x = i & ~((1 << (2 * g)) - 1);
+                        lo = first[x];
+                        hi = first[x + (1 << (2 * g))];
+                    } while (lo == hi);
+                    ans = make_int4((int)lo, (int)hi, k - g, 0);
+                }
+                e = make_int4((int)row, (int)(kPtabAnswer | (uint32_t)ans.z), ans.x, ans.y);
+            }
+            store_stream16(reinterpret_cast<int4 *>(tab + v0) + i, e);
+        }
+    }
+    if (blockIdx.x == gridDim.x - 1 && t == 0)  // T[4^k] = n closes the table; it is never looked up
+        store_stream16(reinterpret_cast<int4 *>(tab + v0) + span, make_int4(ix.n, 0, 0, 0));
 }
 
 // ------------------------------------------------------------------ tile
@@ -2067,21 +2158,11 @@ hipError_t launch_search_reads(const DevIndex &ix, int levels, int use_table, in
 }
 
 hipError_t launch_build_prefix_table(const DevIndex &ix, int k, PrefixEntry *tab, hipStream_t s) {
-    // one work-item per entry, in slices of 2^30 entries (a dispatch holds
-    // fewer than 2^32 work-items); every T[v] is written before any entry
-    // is filled, since the second pass reads T[v + 1]
-    const int64_t entries = ((int64_t)1 << (2 * k)) + 1;
-    const int64_t slice = (int64_t)1 << 30;
-    for (int64_t first = 0; first < entries; first += slice) {
-        const int64_t end = std::min(entries, first + slice);
-        hipLaunchKernelGGL(build_prefix_table_kernel, dim3((unsigned)((end - first + 255) / 256)), dim3(256), 0, s,
-                           ix, k, first, end, tab);
-    }
-    for (int64_t first = 0; first < entries; first += slice) {
-        const int64_t end = std::min(entries, first + slice);
-        hipLaunchKernelGGL(fill_prefix_entries_kernel, dim3((unsigned)((end - first + 255) / 256)), dim3(256), 0, s,
-                           ix, k, first, end, entries, tab);
-    }
+    // a small table in smaller groups, so that every compute unit has some
+    int bases = std::min(k, kTabBases);
+    while (bases > 4 && (k - bases) < 5) --bases;
+    hipLaunchKernelGGL(build_prefix_table_kernel, dim3(1u << (2 * (k - bases))),
+                       dim3(std::min(kTabThreads, 1 << (2 * bases))), 0, s, ix, k, bases, tab);
     return hipGetLastError();
 }
 

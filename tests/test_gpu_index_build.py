@@ -33,3 +33,35 @@ def test_text_is_packed_and_checked(n, tmp_path):
             with pytest.raises(S.SaError) as e:
                 S.sa_build_device(bad, 0)
             assert e.value.code == S.SA_EALPHABET and f"byte {at} " in str(e.value)
+
+
+@pytest.mark.parametrize("kind", ["iid", "a", "tandem", "two letters"])
+@pytest.mark.parametrize("k", [4, 5, 6, 7, 8, 11])
+def test_prefix_table_entries(kind, k):
+    """Every k-base string, as a read, gets from the table what a search from
+    the root gives it, and so do the strings with two bases more: tables of
+    one and of several workgroups, workgroups without rows and with all of
+    them, and the suffixes shorter than k at the text's end."""
+    print("case: table", kind, k, flush=True)
+    n = 5_000
+    rng = np.random.default_rng(k)
+    text = {"iid": rng.integers(0, 4, n), "a": np.zeros(n, int), "tandem": np.tile(rng.integers(0, 4, 5), n // 5),
+            "two letters": rng.integers(0, 2, n) * 3}[kind]
+    d = S.sa_build_device(np.frombuffer(b"ACGT", dtype=np.uint8)[text], 0)
+    d.set_prefix_table(k)
+    for extra in (0, 2):
+        m = k + extra
+        count = 4 ** m
+        v = torch.arange(count, device="cuda")
+        if count > 1 << 20:
+            v = torch.cat([v[:: count >> 18], v[-5000:], v[:5000]])
+        digits = (v[:, None] >> (2 * torch.arange(m - 1, -1, -1, device="cuda"))) & 3
+        reads = torch.tensor(list(b"ACGT"), dtype=torch.uint8, device="cuda")[digits].reshape(-1).contiguous()
+        offs = torch.arange(len(v) + 1, device="cuda") * m
+        outs = []
+        for table in (1, 0):
+            out = torch.full((len(v), 4), -7, dtype=torch.int32, device="cuda")
+            S.match_batch_dev(d, reads, offs, out, config=S.cfg(d, prefix_table=table, sort=0))
+            torch.cuda.synchronize()
+            outs.append(out)
+        assert torch.equal(*outs), (kind, k, extra)
