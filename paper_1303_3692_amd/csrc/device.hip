@@ -320,6 +320,8 @@ int run_batch(sa_dindex *d, Workspace *ws, const uint8_t *d_reads, const int64_t
 
 namespace {
 
+size_t table_bytes(int k) { return (((size_t)1 << (2 * k)) + 1) * sizeof(PrefixEntry); }
+
 // Prefix-table length of a text of n bases: round(log4 n) + 2, so that a
 // table entry's bracket holds about a sixteenth of a row (most lookups then
 // need at most the one probe whose suffix travels with the entry, and its
@@ -333,8 +335,22 @@ namespace {
 int default_prefix_bases(int64_t n, size_t free_bytes) {
     if (n < kMinTableText) return 0;
     int k = std::max(4, std::min(kMaxPrefixBases, (int)std::lround(std::log2((double)n) / 2.0) + 2));
-    while (k > 4 && (((size_t)1 << (2 * k)) + 1) * sizeof(PrefixEntry) > free_bytes / 4) k--;
+    while (k > 4 && table_bytes(k) > free_bytes / 4) k--;
     return k;
+}
+
+// Fills d->d_ptab, memory for a table of k bases, and makes it d's.
+int fill_prefix_table(sa_dindex *d, int k) {
+    DevIndex v = d->view;
+    v.ptab = d->d_ptab;
+    v.ptab_k = k;
+    hipError_t e;
+    if ((e = launch_build_prefix_table(v, k, d->d_ptab, nullptr)) != hipSuccess ||
+        (e = hipDeviceSynchronize()) != hipSuccess)
+        return hip_fail(e, "prefix table build");
+    d->view = v;
+    d->ptab_bytes = (int64_t)table_bytes(k);
+    return SA_OK;
 }
 
 // (Re)build the prefix table of d with k bases (0: none).  Captured graphs
@@ -357,17 +373,9 @@ int set_prefix_table(sa_dindex *d, int k) {
         }
     }
     if (k > 0) {
-        const size_t entries = ((size_t)1 << (2 * k)) + 1;
-        if ((e = hipMalloc((void **)&d->d_ptab, entries * sizeof(PrefixEntry))) != hipSuccess)
+        if ((e = hipMalloc((void **)&d->d_ptab, table_bytes(k))) != hipSuccess)
             return hip_fail(e, "prefix table allocation");
-        DevIndex v = d->view;
-        v.ptab = d->d_ptab;
-        v.ptab_k = k;
-        if ((e = launch_build_prefix_table(v, k, d->d_ptab, nullptr)) != hipSuccess ||
-            (e = hipDeviceSynchronize()) != hipSuccess)
-            return hip_fail(e, "prefix table build");
-        d->view = v;
-        d->ptab_bytes = (int64_t)(entries * sizeof(PrefixEntry));
+        if (int rc = fill_prefix_table(d, k)) return rc;
     }
     d->defaults.prefix_table = k > 0 ? 1 : 0;
     d->defaults.sort = k > 0 ? 0 : 1;
@@ -428,17 +436,24 @@ int make_dindex(int device, int64_t n, const uint64_t *packed, const int32_t *ho
     } else if ((e = hipMemcpy(d->d_text, packed, text_bytes, hipMemcpyHostToDevice)) != hipSuccess) {
         return hip_fail(e, "index upload");
     }
+    // the table's memory, in which the suffixes are sorted before the table is filled
+    size_t free_bytes = 0, total_bytes = 0;
+    if ((e = hipMemGetInfo(&free_bytes, &total_bytes)) != hipSuccess) return hip_fail(e, "device memory query");
+    const int k = default_prefix_bases(n, free_bytes);
+    if (k > 0 && (e = hipMalloc((void **)&d->d_ptab, table_bytes(k))) != hipSuccess)
+        return hip_fail(e, "prefix table allocation");
     if (host_sa) {
         if ((e = hipMemcpy(d->d_sa, host_sa, sa_bytes, hipMemcpyHostToDevice)) != hipSuccess)
             return hip_fail(e, "index upload");
     } else {
-        int rc = build_sa_device(d->d_text, n, d->d_sa, nullptr, nullptr, &d->built);
+        int rc = build_sa_device(d->d_text, n, d->d_sa, nullptr, d->d_ptab, k > 0 ? table_bytes(k) : 0, nullptr,
+                                 &d->built);
         if (rc) return rc;
     }
     if ((e = launch_build_rows(d->d_text, d->d_sa, (int32_t)n, d->d_rows, nullptr)) != hipSuccess ||
         (e = launch_build_tile(d->d_text, d->d_sa, (int32_t)n, d->tile_levels, d->d_tile_key, d->d_tile_sa,
                                nullptr)) != hipSuccess ||
-        (e = hipDeviceSynchronize()) != hipSuccess)
+        (k == 0 && (e = hipDeviceSynchronize()) != hipSuccess))
         return hip_fail(e, "tile build");
     DevIndex v{};
     v.text = d->d_text;
@@ -448,9 +463,8 @@ int make_dindex(int device, int64_t n, const uint64_t *packed, const int32_t *ho
     v.rows = d->d_rows;
     v.n = (int32_t)n;
     d->view = v;
-    size_t free_bytes = 0, total_bytes = 0;
-    if ((e = hipMemGetInfo(&free_bytes, &total_bytes)) != hipSuccess) return hip_fail(e, "device memory query");
-    if (int rc = set_prefix_table(d.get(), default_prefix_bases(n, free_bytes))) return rc;
+    if (k > 0)
+        if (int rc = fill_prefix_table(d.get(), k)) return rc;
     sa_match_cfg &c = d->defaults;
     std::memset(&c, 0, sizeof c);
     c.kernel = SA_KERNEL_TUNED;

@@ -97,8 +97,8 @@ struct SaBuildInfo {
     int steps = 0;             // sorting rounds: the 21-base keys, then each doubling
     int64_t sorted_elems = 0;  // (key, value) pairs sorted over all rounds
 };
-int build_sa_device(const uint64_t *d_text, int64_t n, int32_t *d_sa, uint32_t *rank_out, hipStream_t s,
-                    SaBuildInfo *info);
+int build_sa_device(const uint64_t *d_text, int64_t n, int32_t *d_sa, uint32_t *rank_out, void *scratch,
+                    size_t scratch_bytes, hipStream_t s, SaBuildInfo *info);
 
 }  // namespace samatch
 

@@ -95,10 +95,12 @@ __global__ __launch_bounds__(256) void sort_scan_kernel(uint32_t *hist, int nblo
     __shared__ uint32_t lds[4];
     __shared__ uint32_t carry;
     const int d = blockIdx.x;
-    if (threadIdx.x == 0) {
-        uint32_t base = 0;
-        for (int e = 0; e < d; ++e) base += digit_total[e];
-        carry = base;
+    {
+        // the keys with smaller digits, one digit per thread
+        uint32_t unused;
+        const uint32_t base =
+            block_exclusive_scan((int)threadIdx.x < d ? digit_total[threadIdx.x] : 0u, unused, lds);
+        if (threadIdx.x == 0) carry = base;
     }
     __syncthreads();
     for (int b0 = 0; b0 < nblocks; b0 += 256) {

@@ -221,9 +221,11 @@ __global__ __launch_bounds__(kScanBlock) void sa_flags_apply_kernel(
 
 // Builds sa[0..n) of the packed text d_text (with zero pad words after the
 // text) on stream s; rank_out (nullable, n entries) receives 1 + the row of
-// each text position.  Allocates its scratch and frees it before returning.
-int build_sa_device(const uint64_t *d_text, int64_t n, int32_t *d_sa, uint32_t *rank_out, hipStream_t s,
-                    SaBuildInfo *info) {
+// each text position.  Works in the device memory [scratch, scratch +
+// scratch_bytes) when that is enough (about 29 bytes per base), else in
+// memory that it allocates and frees.
+int build_sa_device(const uint64_t *d_text, int64_t n, int32_t *d_sa, uint32_t *rank_out, void *scratch,
+                    size_t scratch_bytes, hipStream_t s, SaBuildInfo *info) {
     if (n < 1 || n > INT32_MAX) return fail(SA_EINVAL, "text length out of range for device construction");
     const int64_t tiles_scan = (n + kScanTile - 1) / kScanTile;
     uint64_t *key[2] = {nullptr, nullptr};
@@ -234,21 +236,34 @@ int build_sa_device(const uint64_t *d_text, int64_t n, int32_t *d_sa, uint32_t *
     while (((int64_t)1 << bits) <= n) bits++;  // ranks are at most n < 2^bits
     int rc = SA_OK;
     hipError_t e = hipSuccess;
-    auto alloc = [&](void **p, size_t bytes) {
-        if (e == hipSuccess) e = hipMalloc(p, bytes);
+    // one block for all of it: each allocation and release is tens to hundreds
+    // of microseconds, and there were fourteen (2 ms of 10 for 16 Mbp)
+    size_t used = 0;
+    char *base = nullptr;
+    auto take = [&](size_t bytes) {
+        char *p = base ? base + used : nullptr;
+        used += (bytes + 255) & ~(size_t)255;
+        return (void *)p;
     };
-    for (int k = 0; k < 2; ++k) {
-        alloc((void **)&key[k], sizeof(uint64_t) * (size_t)n);
-        alloc((void **)&val[k], sizeof(uint32_t) * (size_t)n);
-        alloc((void **)&row[k], sizeof(uint32_t) * (size_t)n);
-    }
-    if (rank_out) rank = rank_out;
-    else alloc((void **)&rank, sizeof(uint32_t) * (size_t)n);
-    alloc((void **)&hist, sizeof(uint32_t) * sort_hist_words<uint64_t>(n));
-    alloc((void **)&digit_total, sizeof(uint32_t) * 256);
-    alloc((void **)&tmax, sizeof(uint32_t) * (size_t)tiles_scan);
-    alloc((void **)&tsum, sizeof(uint32_t) * (size_t)tiles_scan);
-    alloc((void **)&kept_d, sizeof(uint32_t));
+    auto lay_out = [&] {
+        used = 0;
+        for (int k = 0; k < 2; ++k) {
+            key[k] = (uint64_t *)take(sizeof(uint64_t) * (size_t)n);
+            val[k] = (uint32_t *)take(sizeof(uint32_t) * (size_t)n);
+            row[k] = (uint32_t *)take(sizeof(uint32_t) * (size_t)n);
+        }
+        rank = rank_out ? rank_out : (uint32_t *)take(sizeof(uint32_t) * (size_t)n);
+        hist = (uint32_t *)take(sizeof(uint32_t) * sort_hist_words<uint64_t>(n));
+        digit_total = (uint32_t *)take(sizeof(uint32_t) * 256);
+        tmax = (uint32_t *)take(sizeof(uint32_t) * (size_t)tiles_scan);
+        tsum = (uint32_t *)take(sizeof(uint32_t) * (size_t)tiles_scan);
+        kept_d = (uint32_t *)take(sizeof(uint32_t));
+    };
+    lay_out();
+    void *own = nullptr;
+    if (scratch && used <= scratch_bytes) base = (char *)scratch;
+    else if ((e = hipMalloc(&own, used)) == hipSuccess) base = (char *)own;
+    lay_out();
     if (e == hipSuccess) e = hipHostMalloc((void **)&kept_h, sizeof(uint32_t), hipHostMallocDefault);
     if (e != hipSuccess) rc = hip_fail(e, "suffix array scratch allocation");
 
@@ -312,12 +327,7 @@ int build_sa_device(const uint64_t *d_text, int64_t n, int32_t *d_sa, uint32_t *
         info->steps = steps;
         info->sorted_elems += n;
     }
-    for (int k = 0; k < 2; ++k)
-        for (void *p : {(void *)key[k], (void *)val[k], (void *)row[k]})
-            if (p) (void)hipFree(p);
-    if (!rank_out && rank) (void)hipFree(rank);
-    for (void *p : {(void *)hist, (void *)digit_total, (void *)tmax, (void *)tsum, (void *)kept_d})
-        if (p) (void)hipFree(p);
+    if (own) (void)hipFree(own);
     if (kept_h) (void)hipHostFree(kept_h);
     return rc;
 }
