@@ -21,6 +21,7 @@ SOURCES = [
     "kernels.hip",
     "sa_construct.hip",
     "device.hip",
+    "devmem.hip",
     "noalloc.hip",
     "locate.hip",
     "tune.hip",

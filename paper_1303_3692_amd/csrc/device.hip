@@ -13,6 +13,7 @@
 #include "internal.h"
 #include "kernels.h"
 #include "device_state.h"
+#include "devmem.h"
 
 using namespace samatch;
 
@@ -359,7 +360,7 @@ int set_prefix_table(sa_dindex *d, int k) {
     hipError_t e;
     if (d->d_ptab) {
         if ((e = hipDeviceSynchronize()) != hipSuccess) return hip_fail(e, "prefix table release");
-        (void)hipFree(d->d_ptab);
+        dev_free(d->d_ptab);
         d->d_ptab = nullptr;
     }
     d->view.ptab = nullptr;
@@ -373,7 +374,7 @@ int set_prefix_table(sa_dindex *d, int k) {
         }
     }
     if (k > 0) {
-        if ((e = hipMalloc((void **)&d->d_ptab, table_bytes(k))) != hipSuccess)
+        if ((e = dev_alloc((void **)&d->d_ptab, table_bytes(k))) != hipSuccess)
             return hip_fail(e, "prefix table allocation");
         if (int rc = fill_prefix_table(d, k)) return rc;
     }
@@ -424,11 +425,11 @@ int make_dindex(int device, int64_t n, const uint64_t *packed, const int32_t *ho
     while (levels < kMaxTileLevels && ((int64_t)1 << levels) - 1 < n) levels++;
     d->tile_levels = std::max(1, levels);
     const size_t nodes = ((size_t)1 << d->tile_levels) - 1;
-    if ((e = hipMalloc((void **)&d->d_text, text_bytes)) != hipSuccess ||
-        (e = hipMalloc((void **)&d->d_sa, sa_bytes)) != hipSuccess ||
-        (e = hipMalloc((void **)&d->d_tile_key, nodes * sizeof(uint64_t))) != hipSuccess ||
-        (e = hipMalloc((void **)&d->d_tile_sa, nodes * sizeof(int32_t))) != hipSuccess ||
-        (e = hipMalloc((void **)&d->d_rows, sizeof(RowRec) * (size_t)n)) != hipSuccess)
+    if ((e = dev_alloc((void **)&d->d_text, text_bytes)) != hipSuccess ||
+        (e = dev_alloc((void **)&d->d_sa, sa_bytes)) != hipSuccess ||
+        (e = dev_alloc((void **)&d->d_tile_key, nodes * sizeof(uint64_t))) != hipSuccess ||
+        (e = dev_alloc((void **)&d->d_tile_sa, nodes * sizeof(int32_t))) != hipSuccess ||
+        (e = dev_alloc((void **)&d->d_rows, sizeof(RowRec) * (size_t)n)) != hipSuccess)
         return hip_fail(e, "index allocation");
     if (ascii) {
         // the row records' memory (16 bytes a base) holds the bytes until the records are built
@@ -439,8 +440,8 @@ int make_dindex(int device, int64_t n, const uint64_t *packed, const int32_t *ho
     // the table's memory, in which the suffixes are sorted before the table is filled
     size_t free_bytes = 0, total_bytes = 0;
     if ((e = hipMemGetInfo(&free_bytes, &total_bytes)) != hipSuccess) return hip_fail(e, "device memory query");
-    const int k = default_prefix_bases(n, free_bytes);
-    if (k > 0 && (e = hipMalloc((void **)&d->d_ptab, table_bytes(k))) != hipSuccess)
+    const int k = default_prefix_bases(n, free_bytes + dev_kept(device));
+    if (k > 0 && (e = dev_alloc((void **)&d->d_ptab, table_bytes(k))) != hipSuccess)
         return hip_fail(e, "prefix table allocation");
     if (host_sa) {
         if ((e = hipMemcpy(d->d_sa, host_sa, sa_bytes, hipMemcpyHostToDevice)) != hipSuccess)
@@ -572,7 +573,7 @@ sa_dindex::~sa_dindex() {
     ws.clear();
     for (void *p : {(void *)d_text, (void *)d_sa, (void *)d_tile_key, (void *)d_tile_sa, (void *)d_rows,
                     (void *)d_ptab})
-        if (p) (void)hipFree(p);
+        dev_free(p);
 }
 
 extern "C" void sa_dfree(sa_dindex *d) { delete d; }

@@ -26,6 +26,7 @@
 #include <vector>
 
 #include "device_state.h"
+#include "devmem.h"
 #include "radix_sort.h"
 
 namespace samatch {
@@ -262,7 +263,7 @@ int build_sa_device(const uint64_t *d_text, int64_t n, int32_t *d_sa, uint32_t *
     lay_out();
     void *own = nullptr;
     if (scratch && used <= scratch_bytes) base = (char *)scratch;
-    else if ((e = hipMalloc(&own, used)) == hipSuccess) base = (char *)own;
+    else if ((e = dev_alloc(&own, used)) == hipSuccess) base = (char *)own;
     lay_out();
     if (e == hipSuccess) e = hipHostMalloc((void **)&kept_h, sizeof(uint32_t), hipHostMallocDefault);
     if (e != hipSuccess) rc = hip_fail(e, "suffix array scratch allocation");
@@ -327,7 +328,7 @@ int build_sa_device(const uint64_t *d_text, int64_t n, int32_t *d_sa, uint32_t *
         info->steps = steps;
         info->sorted_elems += n;
     }
-    if (own) (void)hipFree(own);
+    dev_free(own);
     if (kept_h) (void)hipHostFree(kept_h);
     return rc;
 }

@@ -65,3 +65,52 @@ def test_prefix_table_entries(kind, k):
             torch.cuda.synchronize()
             outs.append(out)
         assert torch.equal(*outs), (kind, k, extra)
+
+
+def test_memory_of_a_freed_index_is_used_again_safely():
+    """An index freed with a batch of it still running, the next one built at
+    once (in the freed one's memory), also from several threads: every result
+    is the one an index of its own gives."""
+    import threading
+
+    rng = np.random.default_rng(3)
+    letters = np.frombuffer(b"ACGT", dtype=np.uint8)
+    texts = [rng.choice(letters, 300_000) for _ in range(4)]
+    count, m = 200_000, 60
+    start = rng.integers(0, 300_000 - m, count)
+    batches = []
+    for t in texts:
+        data = torch.from_numpy(t[start[:, None] + np.arange(m)].reshape(-1)).cuda()
+        batches.append(data)
+    offs = torch.arange(count + 1, device="cuda") * m
+    keep = [S.sa_build_device(t, 0) for t in texts]
+    want = []
+    for d, data in zip(keep, batches):
+        out = torch.zeros((count, 4), dtype=torch.int32, device="cuda")
+        S.match_batch_dev(d, data, offs, out)
+        torch.cuda.synchronize()
+        want.append(out)
+    del keep
+
+    failures = []
+
+    def work(which):
+        stream = torch.cuda.Stream()
+        for _ in range(3):
+            for i in which:
+                out = torch.full((count, 4), -7, dtype=torch.int32, device="cuda")
+                torch.cuda.synchronize()
+                d = S.sa_build_device(texts[i], 0)
+                S.match_batch_dev(d, batches[i], offs, out, stream=stream)
+                d.free()
+                stream.synchronize()
+                if not torch.equal(out, want[i]):
+                    failures.append(i)
+
+    work([0, 1, 2, 3])
+    threads = [threading.Thread(target=work, args=([k, (k + 1) % 4],)) for k in range(4)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not failures
