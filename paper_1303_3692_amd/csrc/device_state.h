@@ -49,6 +49,24 @@ struct HostSlot {
     hipEvent_t done = nullptr;  // recorded after the slot's last chunk came back to h_out
 };
 
+// What a locate call's kernels hand to the host (in pinned memory that
+// the device writes): the call's number last.
+struct LocateTotal {
+    int64_t total;
+    uint64_t bad;
+    uint64_t call;
+};
+
+// Scratch of sa_locate_dev, for calls that follow each other on one stream.
+struct LocateScratch {
+    ~LocateScratch();
+    int reserve(int64_t ntiles);
+    int64_t *dev = nullptr;      // tile sums, then two words
+    int64_t cap = 0;             // tiles dev has room for
+    LocateTotal *host = nullptr, *host_dev = nullptr;
+    uint64_t calls = 0;
+};
+
 struct Workspace {
     ~Workspace();
     // counters and events, and with pack_pass the arrays that hold nreads packed reads
@@ -68,6 +86,7 @@ struct Workspace {
     bool profiled = false, counted = false;
     // host batches: chunks alternate between the two slots
     HostSlot host[2];
+    LocateScratch locate;
 };
 
 Workspace *workspace_for(sa_dindex *d, hipStream_t s);
