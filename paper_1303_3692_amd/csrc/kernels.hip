@@ -228,30 +228,20 @@ __device__ __forceinline__ RowHead row_head(const RowRec *__restrict__ rows, int
 // templates otherwise counts words held in registers).
 constexpr int kWordsInLds = 0;
 
-// compare_row for a query whose words are read from LDS as they are needed:
-// a loop over two query words at a time, so that it holds few registers and
+// Compares the query P[0..plen) with the suffix at text position p from word k
+// on (the words before are known to match); returns and sets what
+// compare_from does.  For a query whose words are read as they are needed: a
+// loop over two query words at a time, so that it holds few registers and
 // stops at the first difference whatever the read's length.  The text words
 // of the second of them are loaded together with those of the first (one
 // latency for up to 96 bases), and words stay in registers from one turn
-// to the next: each text word is loaded once.  key0 holds the suffix's
-// first key_bases bases (at least 20, at most 32).
+// to the next: each text word is loaded once.
 template <class Q, class Cnt>
-__device__ __forceinline__ int compare_lds(const DevIndex &ix, const Q &q, int plen, int32_t p, uint64_t key0, int h,
-                                           int &lcp, Cnt &cnt, int key_bases) {
+__device__ __forceinline__ int compare_text(const DevIndex &ix, const Q &q, int plen, int32_t p, int k, int &lcp,
+                                            Cnt &cnt) {
     const int lim = min_i(plen, ix.n - p);
     const int at_end = (lim == plen) ? 0 : 1;
     lcp = lim;
-    int k = h >> 5;
-    if (k == 0) {
-        const uint64_t q0 = q[0], x = q0 ^ key0;
-        const int mm = x ? (int)(__clzll((long long)x) >> 1) : 32;
-        if (mm < min_i(key_bases, lim)) {
-            lcp = mm;
-            return q0 > key0 ? 1 : -1;
-        }
-        k = key_bases >= 32 ? 1 : 0;
-        if (lim <= key_bases) return at_end;
-    }
     if ((k << 5) >= lim) return at_end;
     const uint64_t *tp = ix.text + ((uint32_t)p >> 5) + k;
     const uint32_t sh = ((uint32_t)p & 31u) << 1;
@@ -292,6 +282,28 @@ __device__ __forceinline__ int compare_lds(const DevIndex &ix, const Q &q, int p
     lcp = res;
     cnt.text_words(first, (uint32_t)p + (uint32_t)min_i(lim, res + 1));
     return sign;
+}
+
+// compare_row for a query whose words are read from LDS: key0 holds the
+// suffix's first key_bases bases (at least 20, at most 32).
+template <class Q, class Cnt>
+__device__ __forceinline__ int compare_lds(const DevIndex &ix, const Q &q, int plen, int32_t p, uint64_t key0, int h,
+                                           int &lcp, Cnt &cnt, int key_bases) {
+    const int lim = min_i(plen, ix.n - p);
+    const int at_end = (lim == plen) ? 0 : 1;
+    lcp = lim;
+    int k = h >> 5;
+    if (k == 0) {
+        const uint64_t q0 = q[0], x = q0 ^ key0;
+        const int mm = x ? (int)(__clzll((long long)x) >> 1) : 32;
+        if (mm < min_i(key_bases, lim)) {
+            lcp = mm;
+            return q0 > key0 ? 1 : -1;
+        }
+        k = key_bases >= 32 ? 1 : 0;
+        if (lim <= key_bases) return at_end;
+    }
+    return compare_text(ix, q, plen, p, k, lcp, cnt);
 }
 
 // Probe of one suffix (text position p) whose first key_bases bases (key0,
@@ -1187,6 +1199,13 @@ __global__ __launch_bounds__(BLOCK) void search_packed_kernel(DevIndex ix, int l
 
 // ---- reads packed by the search kernel itself
 
+// Rows of a bracket that are looked at together, in one turn, instead of
+// queued: as many records as a line holds.  More than half of the brackets of
+// several rows have no more (16 Mbp: 4M reads of 100 bases 292 us with none,
+// 264 with 2, 261 with 8 or 16; 100,000 of 25 bases 10.0, 9.6, 7.4; 250 Mbp /
+// 64M reads 4.79, 4.63, 4.61 ms).
+constexpr int kFewRows = 8;
+
 // Words of a queued read's record before its codes: read id, length and
 // leading bases, first row and size of its bracket (size 0: search from the
 // root).
@@ -1644,14 +1663,53 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(COUNT ? 1 
             if (size & kPtabAnswer) {
                 hit = make_int4(ent.pos, (int)ent.next, (int)(size & ~kPtabAnswer), 0);
                 queue = false;
-            } else if (size == 1) {
-                // the bracket's one row is the pivot: what it shares with the read is the match
-                const uint64_t key = (q0 & ~(~0ull >> (2 * K))) | ((uint64_t)ent.next << (32 - 2 * K));
-                int lcp;
-                cnt.global_probe();
-                compare_row<kWordsInLds>(ix, q, mv, nullptr, ent.pos, key, 0, lcp, cnt, K + 16);
-                hit = make_int4((int)row, (int)row + 1, lcp, lcp == m ? (int)kHitExact : 0);
+            } else if (size <= kFewRows) {
+                // one row: it is the entry's pivot, whose next 16 bases came along; more: their first 32
+                // bases from their records, which lie in a line or two
+                int from = 0, lcp = 0;  // the candidate's text is compared from this word on
+                int32_t pos = ent.pos;
+                int first = (int)row, end = (int)row + 1;
+                bool text = true;
                 queue = false;
+                if (size == 1) {
+                    cnt.global_probe();
+                    const int lim = min_i(mv, ix.n - pos);
+                    const uint32_t x = (uint32_t)((q0 << (2 * K)) >> 32) ^ ent.next;
+                    const int same = K + (x ? (int)(__clz((int)x) >> 1) : 16);
+                    from = K == 16 ? 1 : 0;
+                    lcp = min_i(same, lim);
+                    text = same == K + 16 && lim > same;
+                } else {
+                    first = end = 0;
+#pragma unroll 1
+                    for (int r = 0; r < (int)size; r += 2) {
+                        RowHead h[2];
+#pragma unroll
+                        for (int i = 0; i < 2; ++i)
+                            if (r + i < (int)size) {
+                                h[i] = row_head(ix.rows, (int)row + r + i);
+                                cnt.index_touch(ix.rows + row + r + i, 16);
+                                cnt.key_probe();
+                            }
+#pragma unroll
+                        for (int i = 0; i < 2; ++i)
+                            if (r + i < (int)size) {
+                                const uint64_t x = q0 ^ h[i].key0;
+                                const int same = min_i(x ? (int)(__clzll((long long)x) >> 1) : 32, min_i(mv, h[i].len));
+                                if (same > lcp) {
+                                    lcp = same;
+                                    first = (int)row + r + i;
+                                    pos = h[i].pos;
+                                }
+                                if (same == lcp) end = (int)row + r + i + 1;
+                            }
+                    }
+                    from = 1;
+                    text = lcp == 32 && mv > 32;
+                    queue = text && end - first > 1;  // several rows share all 32 bases
+                }
+                if (text && !queue) compare_text(ix, q, mv, pos, from, lcp, cnt);
+                hit = make_int4(first, end, lcp, lcp == m ? (int)kHitExact : 0);
             }
         }
         if (mine && !queue) {
