@@ -1345,6 +1345,50 @@ __device__ __forceinline__ bool stage_pieces(const uint4 *__restrict__ src, int 
     return __any(any);
 }
 
+// The same for reads that lie apart: lane l's first `np` pieces (none: 0) go to
+// pieces off, off + 1, ... of the area (off: the sum of np over the lanes
+// before), `total` in all.  Each piece's read is found by a binary search over
+// the lanes' offsets, so that the loads of all reads are in flight together.
+constexpr int kApartRows = 1;  // loads in flight per lane (2 or 3 spill registers and gain nothing)
+
+template <class Cnt>
+__device__ __forceinline__ bool stage_reads(const uint8_t *__restrict__ reads, int64_t a, int off, int total,
+                                            uint32_t *codes, uint32_t *bad, int lane, Cnt &cnt) {
+    const uint64_t A0 = (uint64_t)(uintptr_t)(reads + a) & ~(uint64_t)15;
+    bool any = false;
+#pragma unroll 1
+    for (int c0 = 0; c0 < total; c0 += 64 * kApartRows) {
+        uint4 r[kApartRows];
+#pragma unroll
+        for (int u = 0; u < kApartRows; ++u) {
+            const int c = c0 + 64 * u + lane;
+            int owner = 0;
+#pragma unroll
+            for (int step = 32; step > 0; step >>= 1)
+                if (__shfl(off, owner + step, 64) <= c) owner += step;
+            const int k = c - __shfl(off, owner, 64);
+            const uint4 *src = reinterpret_cast<const uint4 *>((uintptr_t)__shfl((unsigned long long)A0, owner, 64)) + k;
+            if (c < total) {
+                r[u] = load_stream16(src);
+                cnt.touch(src, 16);
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < kApartRows; ++u) {
+            const int c = c0 + 64 * u + lane;
+            if (c < total) {
+                uint32_t b;
+                codes[c] = convert16(r[u], b);
+                if (b) {
+                    atomicOr(&bad[c >> 5], 1u << (c & 31));
+                    any = true;
+                }
+            }
+        }
+    }
+    return __any(any);
+}
+
 // Searches the wave's queued reads, each by a group of `size` neighbouring
 // lanes: as many as the wave has for each read (32 reads: two lanes each;
 // one read: all 64), the lanes of a group probing the interval between the
@@ -1364,21 +1408,22 @@ __device__ __forceinline__ void search_queued(const DevIndex &ix, const uint64_t
     const uint64_t ones = size == 64 ? ~0ull : (1ull << size) - 1ull;
     const uint32_t share = 0xFFFFFFFFu / (uint32_t)(size + 1) * (uint32_t)(sub + 1);  // of the rows inside, times 2^32
     const uint32_t *r = w.pool + w.rec_at[lane >> bits];
-    const int id = (int)r[0], m = (int)(r[1] & 0xFFFFu), v = (int)(r[1] >> 16);
     const CodeQuery q{r + kRecHead - 1, 0};
+    // phase 0: LB search of P[0..plen), all of st in use; 1 and 2: LB and RB
+    // search of P[0..plen) between st.L and st.R
+    int phase = 0, plen = (int)(r[1] >> 16), lo = 0, above = 0, above_lcp = 0;
     LbState st;
     if (r[3]) {
         open_bracket(ix, (int)r[2], (int)r[3], st);
     } else {
-        lb_tile<kWordsInLds>(ix, t_key, t_sa, levels, q, v, st, cnt);
+        lb_tile<kWordsInLds>(ix, t_key, t_sa, levels, q, plen, st, cnt);
     }
-    // phase 0: LB search of P[0..v), all of st in use; 1 and 2: LB and RB
-    // search of P[0..plen) between st.L and st.R
-    int phase = 0, plen = v, lo = 0, above = 0, above_lcp = 0;
     for (;;) {
         if (st.R == st.L + 1) {
             if (phase == 0) {
-                const bool exact = v == m && st.lcpR == m;
+                // (the record is read again rather than held in registers through the loop)
+                __asm__ volatile("" ::: "memory");
+                const bool exact = plen == (int)(r[1] & 0xFFFFu) && st.lcpR == plen;
                 const int l = max_i(st.lcpL, st.lcpR);
                 if (l == 0) {
                     lo = 0;
@@ -1471,11 +1516,45 @@ __device__ __forceinline__ void search_queued(const DevIndex &ix, const uint64_t
             st.lcpR = lcp_r;
         }
     }
+    __asm__ volatile("" ::: "memory");
     if (sub == 0) {
+        const int id = (int)r[0], m = (int)(r[1] & 0xFFFFu);
         store_stream16(out + id, make_int4(lo, st.R, plen, plen == m ? (int)kHitExact : 0));
         cnt.touch(out + id, 16);
     }
 }
+
+// Pieces of ASCII (aligned 16 bytes) that hold bytes of reads[a .. a + m).
+__device__ __forceinline__ int piece_count(const uint8_t *reads, int64_t a, int m) {
+    return (int)((((uintptr_t)(reads + a) & 15) + (uint32_t)m + 15) >> 4);
+}
+
+// The sum of v over the lanes before this one; total: over all.
+__device__ __forceinline__ int wave_excl_sum(int v, int lane, int &total) {
+    int x = v;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const int y = __shfl_up(x, o, 64);
+        if (lane >= o) x += y;
+    }
+    total = __builtin_amdgcn_readlane(x, 63);
+    return x - v;
+}
+
+// A chunk with reads of more than kLongRead bases that does not fit the
+// staging area is first staged only kProbePieces (up to twice that, if there
+// is room) pieces a read: most reads are settled by their first bases (those
+// that are not from this reference by the table's k, those with an error by
+// the first one), and the rest of their bytes is never read.  What matches
+// as far as it was staged is staged whole in the turns after.
+// 16 Mbp, 400,000 reads of 800 bases 195 us without it, 134 with it; 200,000
+// of 20-1024 87 and 70; 1M of 400 178 and 168; 65,536 of 1024 on 10 Mbp 52.6
+// and 45.4.  From 200 bases on it costs more than it saves (4M of 20-300: 393
+// against 338 us): neighbouring reads share their lines.
+constexpr int kLongRead = 320;
+constexpr int kProbePieces = 11;
+static_assert(64 * kProbePieces <= kStagePieces && 16 * (kProbePieces - 1) >= kMaxPrefixBases,
+              "a chunk's first pieces fit, and hold a table's string");
 
 // The search kernel of a batch in input order: it takes the reads as they
 // lie in memory (ASCII, with CSR offsets or with an end array) and needs no
@@ -1550,12 +1629,13 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(COUNT ? 1 
 
     int64_t c1 = take_chunk(&s_next, group, G, rank, lane, nchunks), a1, e1;
     chunk_offsets(offs, ends, c1, shift, nreads, lane, a1, e1);
-    int64_t a = 0;         // this lane's read of the current chunk: where it starts, its length and its id
-    int m = 0, rid = 0;
+    int64_t a = 0;         // this lane's read of the current chunk: where it starts, its length
+    int m = 0, id0 = 0;    // (and lane 0's id)
     uint64_t todo = 0;     // lanes of the current chunk whose reads are not staged yet
     uint64_t pend = 0;     // lanes whose staged reads wait to be queued
     int mv = 0;            // of a staged read: its leading bases, its place in the code stream, its bracket
     uint32_t at = 0, row = 0, size = 0;
+    int probes = 0;        // of the current chunk (see kLongRead): 2 before the turn of first pieces, 1 after it
     int queued = 0, used = 0;  // records in the pool, words of it in use (wave-uniform)
     for (;;) {
         if (pend) {
@@ -1571,7 +1651,7 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(COUNT ? 1 
             if (push) {
                 w.rec_at[queued + my] = (uint32_t)to;
                 uint32_t *r = w.pool + to;
-                r[0] = (uint32_t)rid;
+                r[0] = (uint32_t)(id0 + lane);
                 r[1] = (uint32_t)m | ((uint32_t)mv << 16);
                 r[2] = row;
                 r[3] = size;
@@ -1600,7 +1680,7 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(COUNT ? 1 
             const int64_t m64 = e1 - a1;
             const int64_t j = (c1 << shift) + lane;
             const bool active = lane < (1 << shift) && j < nreads;
-            rid = (int)j;
+            id0 = (int)(c1 << shift);
             c1 = take_chunk(&s_next, group, G, rank, lane, nchunks);
             chunk_offsets(offs, ends, c1, shift, nreads, lane, a1, e1);
             const bool valid = active && m64 >= 0 && m64 <= SA_MAX_READ;
@@ -1613,19 +1693,43 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(COUNT ? 1 
                 }
             }
             if (active && (!valid || m64 == 0))
-                store_stream16(out + rid, valid ? make_int4(0, ix.n, 0, (int)kHitExact)
+                store_stream16(out + (id0 + lane), valid ? make_int4(0, ix.n, 0, (int)kHitExact)
                                                 : make_int4(0, 0, 0, (int)kHitTooLong));
             m = (int)m64;
-            todo = wave_ballot(valid && m64 > 0);
+            const bool in = valid && m64 > 0;
+            todo = wave_ballot(in);
             if (todo == 0) continue;
+            probes = 0;
+            if (use_table && wave_ballot(in && m > kLongRead)) {
+                int total = 0;
+                (void)wave_excl_sum(in ? piece_count(reads, a, m) : 0, lane, total);
+                probes = total > kStagePieces ? 2 : 0;
+            }
         }
         // stage as many of the reads as fit
         if (lane < kStageBadWords) w.bad[lane] = 0;
         wave_lds_sync();
-        int filled = 0;
         uint64_t staged = 0;
         bool any_bad = false;
-        do {
+        int have = m;  // bases of this lane's read that get staged
+        if (probes) {
+            const int limit = probes > 1 ? max_i(kProbePieces, min_i(2 * kProbePieces, kStagePieces / __popcll(todo)))
+                                      : kStagePieces;
+            int total;
+            const bool in = ((todo >> lane) & 1ull) != 0;
+            const int np = in ? min_i(piece_count(reads, a, m), limit) : 0;
+            const int off = wave_excl_sum(np, lane, total);
+            staged = wave_ballot(in && off + np <= kStagePieces);
+            total = min_i(total, __builtin_amdgcn_readlane(off + np, 63 - (int)__builtin_clzll(staged)));
+            any_bad = stage_reads(reads, a, off, total, w.codes + 1, w.bad, lane, cnt);
+            const int skew = (int)((uintptr_t)(reads + a) & 15);
+            at = 16u * (uint32_t)off + (uint32_t)skew;
+            have = min_i(m, 16 * np - skew);
+            todo &= ~staged;
+            probes = 1;
+        }
+        int filled = 0;
+        while (!probes && todo) {
             const int f = __ffsll((unsigned long long)todo) - 1;
             const uint8_t *A0 = reinterpret_cast<const uint8_t *>((uintptr_t)(reads + lane_value(a, f)) & ~(uintptr_t)15);
             // the run: lanes f, f + 1, ... while each read starts where the one before ends and still fits
@@ -1644,12 +1748,12 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(COUNT ? 1 
             staged |= run;
             todo &= ~run;
             filled += np;
-        } while (todo);
+        }
         wave_lds_sync();
         const bool mine = (staged >> lane) & 1ull;
         const CodeQuery q = code_query(w.codes, at);
-        mv = m;
-        if (any_bad && mine) mv = first_non_base(reads, a, m, at, w.bad);
+        mv = have;
+        if (any_bad && mine) mv = first_non_base(reads, a, have, at, w.bad);
         size = 0;
         bool queue = mine;
         int4 hit = make_int4(0, ix.n, 0, 0);
@@ -1712,11 +1816,14 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(COUNT ? 1 
                 hit = make_int4(first, end, lcp, lcp == m ? (int)kHitExact : 0);
             }
         }
-        if (mine && !queue) {
-            store_stream16(out + rid, hit);
-            cnt.touch(out + rid, 16);
+        // a read that matches as far as it was staged, or needs a longer search, is staged whole
+        const bool more = mine && have < m && mv == have && (queue || hit.z == mv);
+        if (mine && !queue && !more) {
+            store_stream16(out + (id0 + lane), hit);
+            cnt.touch(out + (id0 + lane), 16);
         }
-        pend = wave_ballot(queue);
+        pend = wave_ballot(queue && !more);
+        todo |= wave_ballot(more);
     }
     if constexpr (COUNT) {
         wave_add(&stats[3], nsearched);

@@ -100,3 +100,40 @@ def test_reads_out_of_range_and_out_of_order():
         else:
             want = oracle.match(text, sa, data[offs[i]:offs[i + 1]], np.array([0, m], dtype=np.int64))
             assert (got[i] == want[0]).all(), (i, m)
+
+
+@pytest.mark.parametrize("kind,n", [("copies", 60_000), ("tandem", 40_000), ("iid", 3_500)])
+def test_long_reads_in_full_chunks(kind, n):
+    """Chunks of 64 (and 16) reads of 20-1024 bases, which are staged by their
+    first pieces first: reads settled there, reads that match just up to, up to
+    and past what was staged, and non-bases on either side of it."""
+    if not torch.cuda.is_available():
+        pytest.skip("no HIP device")
+    print("case: long reads,", kind, n, flush=True)
+    rng = np.random.default_rng(n)
+    text = text_of(kind, n, rng)
+    count = 33_000
+    lengths = rng.choice([20, 100, 161, 320, 321, 400, 700, 1023, 1024], count)
+    offs = 5 + np.concatenate([[0], np.cumsum(lengths)]).astype(np.int64)
+    start = rng.integers(0, n - 1024, count)
+    data = np.full(int(offs[-1]) + 1, ord("A"), np.uint8)
+    owner = np.repeat(np.arange(count), lengths)
+    within = np.arange(int(offs[-1]) - 5) - (offs[:-1] - 5)[owner]
+    data[5:-1] = text[start[owner] + within]
+    for i in np.nonzero(rng.random(count) < 0.7)[0]:  # a change, a non-base, or neither
+        at = int(rng.choice([0, 5, 15, 100, 158, 159, 160, 161, 170, 175, 176, 177, 300, 351, 352, 353, 900]))
+        if at < lengths[i]:
+            data[offs[i] + at] = rng.choice(np.frombuffer(b"ACGTNn", dtype=np.uint8))
+    for i in np.nonzero(rng.random(count) < 0.2)[0]:  # unrelated
+        data[offs[i]:offs[i + 1]] = rng.choice(np.frombuffer(b"ACGT", dtype=np.uint8), lengths[i])
+    want = oracle.match(text, oracle.sa_build(text), data, offs)
+    d = S.sa_build_device(text, 0)
+    dev = torch.device("cuda:0")
+    d_reads, d_offs = torch.from_numpy(data).to(dev), torch.from_numpy(offs).to(dev)
+    for some in (count, 9_001):
+        for kw in (dict(block=256, blocks_per_cu=1), dict(block=256, blocks_per_cu=1, defer=0),
+                   dict(block=256, blocks_per_cu=1, sort=0, prefix_table=0), {}):
+            out = torch.full((some, 4), -7, dtype=torch.int32, device=dev)
+            S.match_batch_dev(d, d_reads, d_offs, out, nreads=some, config=S.cfg(d, **kw))
+            torch.cuda.synchronize()
+            assert (out.cpu().numpy() == want[:some]).all(), f"{some} reads, {kw}"
