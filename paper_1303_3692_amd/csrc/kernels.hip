@@ -1105,15 +1105,20 @@ __device__ __forceinline__ int64_t workgroup_rank() {
     return (G % 8 == 0) ? (w % 8) * (G / 8) + w / 8 : w;
 }
 
-// The next chunk of this wave (-1 when the workgroup's blocks are done;
-// every later one lies further on).
+// The workgroup's chunk number c (-1 when its blocks are done; every later one
+// lies further on).
+__device__ __forceinline__ int64_t nth_chunk(unsigned c, int group, int64_t G, int64_t rank, int64_t nchunks) {
+    const int64_t chunk = group == 1 ? (int64_t)c * G + rank
+                                     : ((int64_t)(c / (unsigned)group) * G + rank) * group + (c % (unsigned)group);
+    return chunk < nchunks ? chunk : -1;
+}
+
+// The next chunk of this wave.
 __device__ __forceinline__ int64_t take_chunk(unsigned *next, int group, int64_t G, int64_t rank, int lane,
                                               int64_t nchunks) {
     unsigned c = 0;
     if (lane == 0) c = atomicAdd(next, 1u);
-    c = (unsigned)__builtin_amdgcn_readfirstlane((int)c);
-    const int64_t chunk = ((int64_t)(c / (unsigned)group) * G + rank) * group + (c % (unsigned)group);
-    return chunk < nchunks ? chunk : -1;
+    return nth_chunk((unsigned)__builtin_amdgcn_readfirstlane((int)c), group, G, rank, nchunks);
 }
 
 // The instrumented kernels' counts, summed over the wave.
@@ -1261,15 +1266,15 @@ __device__ __forceinline__ int wave_max7(int v, uint64_t mask) {
     return r;
 }
 
-// Start and end of each read of a chunk of 2^shift reads (none when chunk <
+// Start and end of each read of a chunk of `per` reads (none when chunk <
 // 0): loads issued here, used later.  Read j ends at offs[j + 1], or at
 // ends[j] when an end array is given (reads gathered from anywhere in the
 // buffer).
 __device__ __forceinline__ void chunk_offsets(const int64_t *__restrict__ offs, const int64_t *__restrict__ ends,
-                                              int64_t chunk, int shift, int64_t nreads, int lane, int64_t &a,
+                                              int64_t chunk, int per, int64_t nreads, int lane, int64_t &a,
                                               int64_t &e) {
-    const int64_t j = (chunk << shift) + lane;
-    const bool act = chunk >= 0 && lane < (1 << shift) && j < nreads;
+    const int64_t j = chunk * per + lane;
+    const bool act = chunk >= 0 && lane < per && j < nreads;
     a = act ? offs[j] : 0;
     e = act ? (ends ? ends[j] : offs[j + 1]) : 0;
 }
@@ -1560,7 +1565,7 @@ static_assert(64 * kProbePieces <= kStagePieces && 16 * (kProbePieces - 1) >= kM
 // lie in memory (ASCII, with CSR offsets or with an end array) and needs no
 // pass before or after it.
 //
-// Work: chunks of 2^shift consecutive reads, one read per lane, taken as in
+// Work: chunks of `per` consecutive reads, one read per lane, taken as in
 // search_packed_kernel; batches too small to give every wave 64 reads use
 // smaller chunks.  For a chunk the wave
 //   1. stages the reads' bytes as 2-bit codes in its LDS area: runs of reads
@@ -1591,12 +1596,12 @@ static_assert(64 * kProbePieces <= kStagePieces && 16 * (kProbePieces - 1) >= kM
 // per chunk of 64 fell to a third (965 for that first batch).
 template <bool COUNT, bool TILE>
 __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(COUNT ? 1 : kSearchWavesPerSimd))) void search_reads_kernel(
-    DevIndex ix, int levels, int use_table_i, int group, int shift, int defer, InlineArea area,
+    DevIndex ix, int levels, int use_table_i, int group, int per, int64_t nchunks, int defer, InlineArea area,
     unsigned long long *__restrict__ stats, const uint8_t *__restrict__ reads, const int64_t *__restrict__ offs,
     const int64_t *__restrict__ ends, int64_t nreads, int4 *__restrict__ out) {
     extern __shared__ uint64_t smem[];
     __shared__ unsigned s_next;
-    const int lane = threadIdx.x & 63;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     // the tree's top levels: in LDS when every search starts there (TILE),
     // else read from memory by the few reads that need them
     const uint64_t *t_key = ix.tile_key;
@@ -1612,10 +1617,9 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(COUNT ? 1 
         t_key = s_key;
         t_sa = s_sa;
     }
-    if (threadIdx.x == 0) s_next = 0u;
-    __syncthreads();
+    if (threadIdx.x == 0) s_next = blockDim.x >> 6;
     WaveArea w;
-    w.codes = reinterpret_cast<uint32_t *>(smem) + area.first_word + (threadIdx.x >> 6) * area.wave_words;
+    w.codes = reinterpret_cast<uint32_t *>(smem) + area.first_word + wave * area.wave_words;
     w.bad = w.codes + kStagePieces + 4;
     w.rec_at = w.bad + kStageBadWords;
     w.pool = w.rec_at + kQueueReads;
@@ -1624,11 +1628,12 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(COUNT ? 1 
     uint32_t nsearched = 0, nqwords = 0;
     const bool use_table = use_table_i != 0 && ix.ptab_k > 0;
     const int K = ix.ptab_k;
-    const int64_t nchunks = (nreads + (1 << shift) - 1) >> shift;
     const int64_t G = gridDim.x, rank = workgroup_rank();
 
-    int64_t c1 = take_chunk(&s_next, group, G, rank, lane, nchunks), a1, e1;
-    chunk_offsets(offs, ends, c1, shift, nreads, lane, a1, e1);
+    // each wave's first chunk goes by its number, so that its loads need not wait for the counter
+    int64_t c1 = nth_chunk((unsigned)wave, group, G, rank, nchunks), a1, e1;
+    chunk_offsets(offs, ends, c1, per, nreads, lane, a1, e1);
+    __syncthreads();  // the counter and the tile are in place
     int64_t a = 0;         // this lane's read of the current chunk: where it starts, its length
     int m = 0, id0 = 0;    // (and lane 0's id)
     uint64_t todo = 0;     // lanes of the current chunk whose reads are not staged yet
@@ -1678,11 +1683,11 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(COUNT ? 1 
             // the next chunk; its successor's offsets are loaded meanwhile
             a = a1;
             const int64_t m64 = e1 - a1;
-            const int64_t j = (c1 << shift) + lane;
-            const bool active = lane < (1 << shift) && j < nreads;
-            id0 = (int)(c1 << shift);
+            const int64_t j = c1 * per + lane;
+            const bool active = lane < per && j < nreads;
+            id0 = (int)(c1 * per);
             c1 = take_chunk(&s_next, group, G, rank, lane, nchunks);
-            chunk_offsets(offs, ends, c1, shift, nreads, lane, a1, e1);
+            chunk_offsets(offs, ends, c1, per, nreads, lane, a1, e1);
             const bool valid = active && m64 >= 0 && m64 <= SA_MAX_READ;
             if (COUNT && active) {
                 cnt.touch(offs + j, ends ? 8 : 16);
@@ -2301,15 +2306,23 @@ hipError_t launch_search_reads(const DevIndex &ix, int levels, int use_table, in
     // reads of 30-300 bases: 8 us as 64 chunks, 18 as one).  For all waves
     // rather than half, launching them costs more than their smaller chunks
     // save (100,000 reads of 25 bases: 13.0 against 10.0 us).
+    // A larger one is cut evenly: into as many reads a chunk as give every
+    // wave the same number of chunks, so that the last round of them is not
+    // nearly empty (4M reads: 11 rounds of 60 reads rather than 10 of 64 and
+    // a sixth of one).
     const int64_t waves = (int64_t)cus * blocks_per_cu * (block / 64);
-    int shift = 6;
-    while (shift > 0 && (nreads >> shift) < waves / 2) --shift;
-    const int64_t chunks = (nreads + (1 << shift) - 1) >> shift;
-    const int64_t gmax = (int64_t)cus * blocks_per_cu, per = block / 64;
+    int per = 64;
+    while (per > 1 && nreads / per < waves / 2) per /= 2;
+    if (per == 64) {
+        const int64_t rounds = (nreads + 64 * waves - 1) / (64 * waves);
+        per = (int)((nreads + waves * rounds - 1) / (waves * rounds));
+    }
+    const int64_t chunks = (nreads + per - 1) / per;
+    const int64_t gmax = (int64_t)cus * blocks_per_cu, wg = block / 64;
     group = (int)std::max<int64_t>(1, std::min<int64_t>(group, chunks / gmax));
-    const unsigned grid = (unsigned)std::min<int64_t>(gmax, (chunks + group * per - 1) / (group * per));
+    const unsigned grid = (unsigned)std::min<int64_t>(gmax, (chunks + group * wg - 1) / (group * wg));
 #define SAMATCH_LAUNCH(C, T)                                                                                      \
-    hipLaunchKernelGGL((search_reads_kernel<C, T>), dim3(grid), dim3(block), lds, s, ix, levels, use_table, group, shift, \
+    hipLaunchKernelGGL((search_reads_kernel<C, T>), dim3(grid), dim3(block), lds, s, ix, levels, use_table, group, per, chunks, \
                        defer, area, stats, reads, offs, ends, nreads, o)
     if (count) {
         if (tile) SAMATCH_LAUNCH(true, true);
