@@ -1354,12 +1354,11 @@ __device__ __forceinline__ bool stage_pieces(const uint4 *__restrict__ src, int 
 // pieces off, off + 1, ... of the area (off: the sum of np over the lanes
 // before), `total` in all.  Each piece's read is found by a binary search over
 // the lanes' offsets, so that the loads of all reads are in flight together.
-constexpr int kApartRows = 1;  // loads in flight per lane (2 or 3 spill registers and gain nothing)
+constexpr int kApartRows = 2;  // loads in flight per lane (4 spill registers and gain nothing)
 
 template <class Cnt>
 __device__ __forceinline__ bool stage_reads(const uint8_t *__restrict__ reads, int64_t a, int off, int total,
                                             uint32_t *codes, uint32_t *bad, int lane, Cnt &cnt) {
-    const uint64_t A0 = (uint64_t)(uintptr_t)(reads + a) & ~(uint64_t)15;
     bool any = false;
 #pragma unroll 1
     for (int c0 = 0; c0 < total; c0 += 64 * kApartRows) {
@@ -1372,7 +1371,8 @@ __device__ __forceinline__ bool stage_reads(const uint8_t *__restrict__ reads, i
             for (int step = 32; step > 0; step >>= 1)
                 if (__shfl(off, owner + step, 64) <= c) owner += step;
             const int k = c - __shfl(off, owner, 64);
-            const uint4 *src = reinterpret_cast<const uint4 *>((uintptr_t)__shfl((unsigned long long)A0, owner, 64)) + k;
+            const uint4 *src =
+                reinterpret_cast<const uint4 *>((uintptr_t)(reads + __shfl(a, owner, 64)) & ~(uintptr_t)15) + k;
             if (c < total) {
                 r[u] = load_stream16(src);
                 cnt.touch(src, 16);
@@ -1547,15 +1547,16 @@ __device__ __forceinline__ int wave_excl_sum(int v, int lane, int &total) {
 }
 
 // A chunk with reads of more than kLongRead bases that does not fit the
-// staging area is first staged only kProbePieces (up to twice that, if there
-// is room) pieces a read: most reads are settled by their first bases (those
-// that are not from this reference by the table's k, those with an error by
-// the first one), and the rest of their bytes is never read.  What matches
-// as far as it was staged is staged whole in the turns after.
-// 16 Mbp, 400,000 reads of 800 bases 195 us without it, 134 with it; 200,000
-// of 20-1024 87 and 70; 1M of 400 178 and 168; 65,536 of 1024 on 10 Mbp 52.6
-// and 45.4.  From 200 bases on it costs more than it saves (4M of 20-300: 393
-// against 338 us): neighbouring reads share their lines.
+// staging area is first staged only kProbePieces pieces a read: most reads are
+// settled by their first bases (those that are not from this reference by the
+// table's k, those with an error by the first one), and the rest of their
+// bytes is never read.  What matches as far as it was staged is staged whole
+// in the turns after.  16 Mbp, 400,000 reads of 800 bases 195 us without it,
+// 103 with it; 200,000 of 20-1024 87 and 55; 1M of 400 178 and 160; 65,536 of
+// 1024 on 10 Mbp 52.6 and 41.6.  From 200 bases on it costs more than it saves
+// (4M of 20-300: 393 against 338 us: neighbouring reads share their lines),
+// and so it does for chunks that fit half of the area (50,001 of 20-1024:
+// 40.3 against 37.2).
 constexpr int kLongRead = 320;
 constexpr int kProbePieces = 11;
 static_assert(64 * kProbePieces <= kStagePieces && 16 * (kProbePieces - 1) >= kMaxPrefixBases,
@@ -1718,8 +1719,7 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(COUNT ? 1 
         bool any_bad = false;
         int have = m;  // bases of this lane's read that get staged
         if (probes) {
-            const int limit = probes > 1 ? max_i(kProbePieces, min_i(2 * kProbePieces, kStagePieces / __popcll(todo)))
-                                      : kStagePieces;
+            const int limit = probes > 1 ? kProbePieces : kStagePieces;
             int total;
             const bool in = ((todo >> lane) & 1ull) != 0;
             const int np = in ? min_i(piece_count(reads, a, m), limit) : 0;
