@@ -124,7 +124,8 @@ int sa_build_device(const char *text, int64_t n, int device, sa_dindex **out);
 
 /* Device bytes of a resident index by part: bytes[0] packed text (with its
  * padding words), bytes[1] suffix array, bytes[2] row records, bytes[3]
- * prefix table (0 without one), bytes[4] LDS tile table.  The plain kernel
+ * prefix table (0 without one), bytes[4] LDS tile table (with, for a text of
+ * less than 4096 bases, the small table its searches start from).  The plain kernel
  * reads the first two; the tuned kernels all of them. */
 int sa_dindex_bytes(const sa_dindex *d, int64_t bytes[5]);
 

@@ -178,11 +178,10 @@ bool packs_inline(const sa_match_cfg &c) {
 }
 
 // A batch whose settings sort it is searched in input order all the same when
-// the text is too short for a prefix table (below 4096 bases): its row
-// records (64 KB) stay in every cache, where lanes that share pivots gain
-// nothing, and the sort is a dozen launches (MI355X, 3,000 bases: 20,000 reads
-// of 150 bases 19 against 106 us, 1M of 20-300 175 against 208, 4M of 30-100
-// 456 against 467; with 65,536 bases that last one is 577 against 530).
+// the text is below 4096 bases: its searches start from a table that caches
+// hold whole, where lanes that share pivots gain nothing, and the sort is a
+// dozen launches (MI355X, 3,000 bases: 20,000 reads of 150 bases 8 against 106
+// us, 1M of 20-300 66 against 208, 4M of 30-100 142 against 467).
 bool searches_inline(const sa_dindex *d, const sa_match_cfg &c) {
     if (packs_inline(c)) return true;
     sa_match_cfg u = c;
@@ -248,7 +247,12 @@ int enqueue_pipeline(sa_dindex *d, const BatchBuffers &b, const hipEvent_t *ev, 
         e = launch_search_plain(d->view, b, nreads, d_out, c.count != 0, s);
         if (e != hipSuccess) return hip_fail(e, "plain search launch");
     } else if (inl) {
-        e = launch_search_reads(d->view, c.tile_levels, c.prefix_table, c.block, c.blocks_per_cu, d->cu_count, c.group,
+        DevIndex v = d->view;
+        if (d->short_k) {
+            v.ptab = d->d_short;
+            v.ptab_k = d->short_k;
+        }
+        e = launch_search_reads(v, c.tile_levels, c.prefix_table || d->short_k, c.block, c.blocks_per_cu, d->cu_count, c.group,
                                 c.defer, b.stats, d_reads, d_offs, d_ends, nreads, d_out, c.count != 0, s);
         if (e != hipSuccess) return hip_fail(e, "search launch");
     } else {
@@ -323,6 +327,11 @@ namespace {
 
 size_t table_bytes(int k) { return (((size_t)1 << (2 * k)) + 1) * sizeof(PrefixEntry); }
 
+// Strings of the table of a text of n bases, memory aside.
+int table_bases(int64_t n) {
+    return std::max(4, std::min(kMaxPrefixBases, (int)std::lround(std::log2((double)n) / 2.0) + 2));
+}
+
 // Prefix-table length of a text of n bases: round(log4 n) + 2, so that a
 // table entry's bracket holds about a sixteenth of a row (most lookups then
 // need at most the one probe whose suffix travels with the entry, and its
@@ -335,7 +344,7 @@ size_t table_bytes(int k) { return (((size_t)1 << (2 * k)) + 1) * sizeof(PrefixE
 // reference k = 13 and 14 gained 8 % and 3 %.
 int default_prefix_bases(int64_t n, size_t free_bytes) {
     if (n < kMinTableText) return 0;
-    int k = std::max(4, std::min(kMaxPrefixBases, (int)std::lround(std::log2((double)n) / 2.0) + 2));
+    int k = table_bases(n);
     while (k > 4 && table_bytes(k) > free_bytes / 4) k--;
     return k;
 }
@@ -466,6 +475,18 @@ int make_dindex(int device, int64_t n, const uint64_t *packed, const int32_t *ho
     d->view = v;
     if (k > 0)
         if (int rc = fill_prefix_table(d.get(), k)) return rc;
+    if (n < kMinTableText) {
+        // At most 1 MiB, and no setting of a batch's: walking down the tree
+        // instead, with the tile in LDS, took 19 us for 20,000 reads of 150
+        // bases on 3,000 and 175 us for 1M of 20-300; from the table 8 and 66.
+        const int ks = table_bases(n);
+        if ((e = dev_alloc((void **)&d->d_short, table_bytes(ks))) != hipSuccess)
+            return hip_fail(e, "short table allocation");
+        if ((e = launch_build_prefix_table(d->view, ks, d->d_short, nullptr)) != hipSuccess ||
+            (e = hipDeviceSynchronize()) != hipSuccess)
+            return hip_fail(e, "short table build");
+        d->short_k = ks;
+    }
     sa_match_cfg &c = d->defaults;
     std::memset(&c, 0, sizeof c);
     c.kernel = SA_KERNEL_TUNED;
@@ -547,6 +568,7 @@ extern "C" int sa_dindex_bytes(const sa_dindex *d, int64_t bytes[5]) {
     bytes[2] = (int64_t)sizeof(RowRec) * n;
     bytes[3] = d->ptab_bytes;
     bytes[4] = (int64_t)((((size_t)1 << d->tile_levels) - 1) * (sizeof(uint64_t) + sizeof(int32_t)));
+    if (d->short_k) bytes[4] += (int64_t)table_bytes(d->short_k);
     return SA_OK;
 }
 
@@ -572,7 +594,7 @@ sa_dindex::~sa_dindex() {
     DeviceGuard g(device);
     ws.clear();
     for (void *p : {(void *)d_text, (void *)d_sa, (void *)d_tile_key, (void *)d_tile_sa, (void *)d_rows,
-                    (void *)d_ptab})
+                    (void *)d_ptab, (void *)d_short})
         dev_free(p);
 }
 

@@ -134,6 +134,9 @@ struct sa_dindex {
     samatch::RowRec *d_rows = nullptr;
     samatch::PrefixEntry *d_ptab = nullptr;
     int64_t ptab_bytes = 0;
+    // of a text below kMinTableText bases: the table every search in input order starts from
+    samatch::PrefixEntry *d_short = nullptr;
+    int short_k = 0;
     int tile_levels = 0;  // levels stored (the kernel may use fewer)
     samatch::SaBuildInfo built{};  // when the suffix array was built on the device
     samatch::DevIndex view{};
