@@ -113,9 +113,10 @@ typedef uint64_t u64x2_a8 __attribute__((ext_vector_type(2), aligned(8)));
 __device__ __forceinline__ u64x2_a8 load_u64x2(const uint64_t *p) { return *reinterpret_cast<const u64x2_a8 *>(p); }
 
 // 16 bytes read once: a non-temporal load, so that the caches keep lines
-// that are used again (the text) rather than prefix-table entries, row
-// records and ASCII reads, which a search touches once (on MI355X this took
-// the 250 Mbp / 64M-read batch from 6.47 to 5.93 ms, results unchanged).
+// that are used again (the text, and the row records of repeats) rather than
+// prefix-table entries and ASCII reads, which a search touches once (on
+// MI355X this took the 250 Mbp / 64M-read batch from 6.47 to 5.93 ms; row
+// records loaded like that too made it 4.70 instead of 4.28 ms).
 __device__ __forceinline__ uint4 load_stream16(const void *p) {
     typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
     const u32x4 v = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(p));
@@ -216,7 +217,7 @@ struct RowHead {
 };
 
 __device__ __forceinline__ RowHead row_head(const RowRec *__restrict__ rows, int r) {
-    const uint4 v = load_stream16(rows + r);
+    const uint4 v = *reinterpret_cast<const uint4 *>(rows + r);
     RowHead h;
     h.pos = (int32_t)v.x;
     h.len = (int32_t)v.y;
@@ -453,10 +454,18 @@ __device__ __forceinline__ void lb_search(const DevIndex &ix, const uint64_t *s_
 // does not start with v after them is above it, so the LB search of P runs
 // inside the bracket of rows that start with v (see PrefixEntry).
 
-// The entry of the read's first K bases (one 16-byte load).
+// The entry of the read's first K bases (one 16-byte load).  A table of up
+// to kCachedBases bases (1 GiB) is small enough for a batch to come back to its
+// lines while caches hold them; a larger one is read past the caches, which
+// leaves them to rows and text (MI355X, 4M reads of 100 bases on 1 Mbp, k = 12:
+// 191 us cached, 226 not; on 4 Mbp, k = 13: 217 and 232; on 16 Mbp, k = 14: 246
+// and 241).
+constexpr int kCachedBases = 13;
+
 template <class Cnt>
 __device__ __forceinline__ PrefixEntry table_entry(const DevIndex &ix, uint32_t v, Cnt &cnt) {
-    const uint4 e = load_stream16(ix.ptab + v);
+    const uint4 e = ix.ptab_k <= kCachedBases ? *reinterpret_cast<const uint4 *>(ix.ptab + v)
+                                              : load_stream16(ix.ptab + v);
     cnt.index_touch(ix.ptab + v, 16);
     cnt.table_probe();
     return PrefixEntry{e.x, e.y, (int32_t)e.z, e.w};
