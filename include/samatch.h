@@ -147,8 +147,8 @@ int sa_set_prefix_table(sa_dindex *d, int k);
  * save one built on the device with sa_save.  Free with sa_free. */
 int sa_download(const sa_dindex *d, sa_index **out);
 
-/* For an index from sa_build_device: *steps = sorting rounds (the 21-base
- * keys, then one per doubling), *sorted_pairs = (key, value) pairs sorted
+/* For an index from sa_build_device: *steps = sorting rounds (the first
+ * bases, then one per doubling), *sorted_pairs = (key, value) pairs sorted
  * over all rounds.  Both 0 for an index from sa_upload.  Nullable outputs. */
 int sa_dindex_build_info(const sa_dindex *d, int *steps, int64_t *sorted_pairs);
 

@@ -113,7 +113,7 @@ int run_batch(sa_dindex *d, Workspace *ws, const uint8_t *d_reads, const int64_t
 
 // Suffix array construction on the device (sa_construct.hip).
 struct SaBuildInfo {
-    int steps = 0;             // sorting rounds: the 21-base keys, then each doubling
+    int steps = 0;             // sorting rounds: the first bases, then each doubling
     int64_t sorted_elems = 0;  // (key, value) pairs sorted over all rounds
 };
 int build_sa_device(const uint64_t *d_text, int64_t n, int32_t *d_sa, uint32_t *rank_out, void *scratch,

@@ -5,14 +5,17 @@
 // The paper builds it with DC3 on the host.  Here the device sorts by
 // prefix doubling, which maps onto the radix sort the batch path already
 // has:
-//   step 0   every position gets a 63-bit key, its first 21 bases as 3-bit
-//            codes (0 past the text end, 1..4 for a, c, g, t), and the
-//            (key, position) pairs are radix sorted.  rank[i] = 1 + the
-//            first row of i's group of equal keys.
-//   step h   (h = 21, 42, 84, ...) only suffixes in groups of two or more
-//            are kept.  Each gets the key rank[i] * 2^B + rank[i+h]
-//            (0 past the end), the kept pairs are sorted, and each old group
-//            splits into groups of equal keys, ranked by their first row.
+//   step 0   every position gets its first h bases (12 to 24, with the text's
+//            length: 4^h is well above n) as 2-bit codes, zero past the text
+//            end, and the (key, position) pairs are radix sorted.  rank[i] = 1
+//            + the first row of i's group of equal keys.
+//   step h   (doubling) only suffixes in groups of two or more are kept.  Each
+//            gets the key (rank[i], rank[i+h] + h), or (rank[i], n - i) when
+//            fewer than h bases are left: members of a group that end inside
+//            the h bases they share are each a prefix of the longer ones, so
+//            they come first, the shortest first.  The kept pairs are sorted,
+//            and each old group splits into groups of equal keys, ranked by
+//            their first row.
 // A group of one is final.  Groups are contiguous runs of rows, so the kept
 // list, taken in row order, stays sorted by group; after the sort each
 // member goes back to one of its group's rows, the same rows in the same
@@ -23,6 +26,7 @@
 // sort histograms 256 x 4 x ceil(n / 2048) bytes.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <vector>
 
 #include "device_state.h"
@@ -32,13 +36,22 @@
 namespace samatch {
 namespace {
 
-constexpr int kInitBases = 21;  // 3-bit codes in a 63-bit key
 constexpr int kScanBlock = 256;
 constexpr int kScanItems = 16;
 constexpr int kScanTile = kScanBlock * kScanItems;
 
-// Step 0 keys: first 21 bases of the suffix at i as 3-bit codes, MSB first.
-__global__ __launch_bounds__(256) void sa_init_keys_kernel(const uint64_t *__restrict__ text, int64_t n,
+// Bases of the step 0 keys: four above the strings of the prefix table, so
+// that few suffixes of an ordinary text share them, rounded up to whole 8-bit
+// digits.  Each digit is a pass over all pairs: 16 Mbp take 5 passes of 20
+// bases (21 bases with an end symbol, 3 bits each, took 8).
+int init_bases(int64_t n) {
+    int k = 4;
+    while (k < 24 && ((int64_t)1 << (2 * (k - 2))) < n) ++k;
+    return std::max(12, (k + 4 + 3) & ~3);
+}
+
+// Step 0 keys: first `bases` bases of the suffix at i, first base highest.
+__global__ __launch_bounds__(256) void sa_init_keys_kernel(const uint64_t *__restrict__ text, int64_t n, int bases,
                                                            uint64_t *__restrict__ key, uint32_t *__restrict__ val) {
     const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (i >= n) return;
@@ -46,20 +59,12 @@ __global__ __launch_bounds__(256) void sa_init_keys_kernel(const uint64_t *__res
     const unsigned sh = (unsigned)(i & 31) * 2u;
     const uint64_t lo = text[w], hi = text[w + 1];  // the text carries zero pad words
     const uint64_t x = sh ? (lo << sh) | (hi >> (64u - sh)) : lo;
-    const int64_t left = n - i;
-    const int take = left < kInitBases ? (int)left : kInitBases;
-    uint64_t k = 0;
-#pragma unroll
-    for (int j = 0; j < kInitBases; ++j) {
-        const uint64_t c = j < take ? ((x >> (62 - 2 * j)) & 3u) + 1u : 0u;
-        k = (k << 3) | c;
-    }
-    key[i] = k;
+    key[i] = x >> (64 - 2 * bases);
     val[i] = (uint32_t)i;
 }
 
-// Step h keys for the kept suffixes: rank of the suffix, then rank of the
-// suffix h further on (0 past the end).
+// Step h keys for the kept suffixes: rank of the suffix, then h + rank of the
+// suffix h further on, or, where the text ends before that, what is left.
 __global__ __launch_bounds__(256) void sa_pair_keys_kernel(const uint32_t *__restrict__ rank,
                                                            const uint32_t *__restrict__ suf, int64_t u_count,
                                                            int64_t n, int64_t h, int bits,
@@ -67,8 +72,48 @@ __global__ __launch_bounds__(256) void sa_pair_keys_kernel(const uint32_t *__res
     const int64_t u = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (u >= u_count) return;
     const int64_t s = suf[u];
-    const uint64_t r2 = s + h < n ? rank[s + h] : 0u;
+    const uint64_t r2 = s + h < n ? (uint64_t)rank[s + h] + (uint64_t)h : (uint64_t)(n - s);
     key[u] = ((uint64_t)rank[s] << bits) | r2;
+}
+
+// Sorts up to kFewPairs pairs by key in one workgroup (bitonic, in LDS; equal
+// keys in any order, which the next step does not mind).  The last doublings
+// of a text, and all of a small one's, have few pairs left: a radix sort's 28
+// launches for them are most of what such a build takes.
+constexpr int kFewPairs = 4096;
+constexpr int kFewThreads = 1024;
+
+__global__ __launch_bounds__(kFewThreads) void sort_few_kernel(uint64_t *__restrict__ key, uint32_t *__restrict__ val,
+                                                               int count) {
+    __shared__ uint64_t k[kFewPairs];
+    __shared__ uint32_t v[kFewPairs];
+    int size = 64;
+    while (size < count) size *= 2;
+    for (int i = threadIdx.x; i < size; i += kFewThreads) {
+        k[i] = i < count ? key[i] : ~0ull;  // no key has all bits set: its second half is at most n + h
+        v[i] = i < count ? val[i] : 0u;
+    }
+    __syncthreads();
+    for (int run = 2; run <= size; run *= 2) {
+        for (int gap = run / 2; gap > 0; gap /= 2) {
+            for (int t = threadIdx.x; t < size / 2; t += kFewThreads) {
+                const int i = 2 * t - (t & (gap - 1)), j = i + gap;
+                const uint64_t a = k[i], b = k[j];
+                if ((a > b) == ((i & run) == 0)) {
+                    k[i] = b;
+                    k[j] = a;
+                    const uint32_t x = v[i];
+                    v[i] = v[j];
+                    v[j] = x;
+                }
+            }
+            __syncthreads();
+        }
+    }
+    for (int i = threadIdx.x; i < count; i += kFewThreads) {
+        key[i] = k[i];
+        val[i] = v[i];
+    }
 }
 
 // Per sorted element u of the current list (sorted keys `key`, row of slot
@@ -233,8 +278,11 @@ int build_sa_device(const uint64_t *d_text, int64_t n, int32_t *d_sa, uint32_t *
     uint32_t *val[2] = {nullptr, nullptr}, *row[2] = {nullptr, nullptr};
     uint32_t *rank = nullptr, *hist = nullptr, *digit_total = nullptr, *tmax = nullptr, *tsum = nullptr;
     uint32_t *kept_d = nullptr, *kept_h = nullptr;
-    int bits = 1;
-    while (((int64_t)1 << bits) <= n) bits++;  // ranks are at most n < 2^bits
+    auto bits_of = [](int64_t most) {
+        int bits = 1;
+        while (((int64_t)1 << bits) <= most) bits++;
+        return bits;
+    };
     int rc = SA_OK;
     hipError_t e = hipSuccess;
     // one block for all of it: each allocation and release is tens to hundreds
@@ -271,6 +319,12 @@ int build_sa_device(const uint64_t *d_text, int64_t n, int32_t *d_sa, uint32_t *
     // sort (keys, values) in the pair (key[c], val[c]); returns the buffer
     // index holding the result
     auto sort = [&](int c, int64_t count, int hi_bit, int *out) {
+        if (count <= kFewPairs) {
+            hipLaunchKernelGGL(sort_few_kernel, dim3(1), dim3(kFewThreads), 0, s, key[c], val[c], (int)count);
+            e = hipGetLastError();
+            *out = c;
+            return;
+        }
         int which = 0;
         e = radix_sort_pairs<uint64_t>(key[c], val[c], key[c ^ 1], val[c ^ 1], hist, digit_total, count, 0, hi_bit,
                                        &which, s);
@@ -294,21 +348,23 @@ int build_sa_device(const uint64_t *d_text, int64_t n, int32_t *d_sa, uint32_t *
     int64_t count = n, kept = 0;
     int c = 0, rsel = 0, steps = 0;
     if (rc == SA_OK) {
-        hipLaunchKernelGGL(sa_init_keys_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, d_text, n,
+        const int bases = init_bases(n);
+        hipLaunchKernelGGL(sa_init_keys_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, d_text, n, bases,
                            key[0], val[0]);
-        if ((e = hipGetLastError()) == hipSuccess) sort(0, n, 3 * kInitBases, &c);
+        if ((e = hipGetLastError()) == hipSuccess) sort(0, n, 2 * bases, &c);
         if (e == hipSuccess) apply(c, nullptr, row[0], n, &kept);
         steps = 1;
         // the next list is in (val[c ^ 1], row[0])
-        int64_t h = kInitBases;
+        int64_t h = bases;
         while (e == hipSuccess && kept > 0) {
             count = kept;
             c ^= 1;
+            const int bits = bits_of(n + h);  // of the second half
             hipLaunchKernelGGL(sa_pair_keys_kernel, dim3((unsigned)((count + 255) / 256)), dim3(256), 0, s, rank,
                                val[c], count, n, h, bits, key[c]);
             if ((e = hipGetLastError()) != hipSuccess) break;
             int sorted = c;
-            sort(c, count, 2 * bits, &sorted);
+            sort(c, count, bits_of(n) + bits, &sorted);
             if (e != hipSuccess) break;
             c = sorted;
             apply(c, row[rsel], row[rsel ^ 1], count, &kept);
@@ -316,7 +372,7 @@ int build_sa_device(const uint64_t *d_text, int64_t n, int32_t *d_sa, uint32_t *
             steps++;
             h *= 2;
             if (info) info->sorted_elems += count;
-            if (h > 2 * n + kInitBases) {  // every group is a single suffix long before this
+            if (kept > 0 && h > 2 * n + bases) {  // every group is a single suffix long before this
                 rc = fail(SA_EDEVICE, "suffix sorting did not converge");
                 break;
             }
