@@ -96,7 +96,8 @@ int HostSlot::reserve(int64_t nreads, int64_t nbytes) {
         if (h_reads) (void)hipHostFree(h_reads);
         h_reads = nullptr;
         bytes_cap = 0;
-        if ((e = hipHostMalloc((void **)&h_reads, (size_t)c, hipHostMallocDefault)) != hipSuccess)
+        if ((e = hipHostMalloc((void **)&h_reads, (size_t)c, hipHostMallocMapped)) != hipSuccess ||
+            (e = hipHostGetDevicePointer((void **)&m_reads, h_reads, 0)) != hipSuccess)
             return hip_fail(e, "pinned staging");
         if ((e = grow((void **)&d_reads, (size_t)c)) != hipSuccess) return hip_fail(e, "staging");
         bytes_cap = c;
@@ -108,8 +109,10 @@ int HostSlot::reserve(int64_t nreads, int64_t nbytes) {
         h_offs = nullptr;
         h_out = nullptr;
         reads_cap = 0;
-        if ((e = hipHostMalloc((void **)&h_offs, sizeof(int64_t) * (size_t)(c + 1), hipHostMallocDefault)) != hipSuccess ||
-            (e = hipHostMalloc((void **)&h_out, sizeof(sa_hit) * (size_t)c, hipHostMallocDefault)) != hipSuccess)
+        if ((e = hipHostMalloc((void **)&h_offs, sizeof(int64_t) * (size_t)(c + 1), hipHostMallocMapped)) != hipSuccess ||
+            (e = hipHostMalloc((void **)&h_out, sizeof(sa_hit) * (size_t)c, hipHostMallocMapped)) != hipSuccess ||
+            (e = hipHostGetDevicePointer((void **)&m_offs, h_offs, 0)) != hipSuccess ||
+            (e = hipHostGetDevicePointer((void **)&m_out, h_out, 0)) != hipSuccess)
             return hip_fail(e, "pinned staging");
         if ((e = grow((void **)&d_offs, sizeof(int64_t) * (size_t)(c + 1))) != hipSuccess ||
             (e = grow((void **)&d_out, sizeof(sa_hit) * (size_t)c)) != hipSuccess)
@@ -630,6 +633,12 @@ extern "C" int match_batch_dev(const sa_dindex *dc, const uint8_t *d_reads, cons
 // Host batches stream through pinned staging in chunks of whole reads.
 constexpr int64_t kHostChunkBytes = (int64_t)32 << 20;
 constexpr int64_t kHostChunkReads = (int64_t)1 << 19;
+// Chunks of at most this many bytes (reads, offsets and results) are not copied
+// to the device and back: the search kernel reads and writes the pinned buffers
+// over the bus, each byte once, as a copy would (MI355X, 16 Mbp, reads of 150
+// bases: one 22 against 27 us, 1,000 34 against 43, 10,000 115 against 133,
+// 30,000 232 against 256; larger ones within 3 % either way).
+constexpr int64_t kDirectBytes = (int64_t)4 << 20;
 
 // memcpy split over a few threads (one copy thread moves ~10 GB/s; the
 // staging copies would otherwise bound a host batch below the bus rate).
@@ -714,13 +723,19 @@ extern "C" int match_batch(const sa_dindex *dc, const char *reads, const int64_t
         host_copy(hs.h_reads, reads + b0, (size_t)nb);
         for (int64_t i = 0; i <= n; i++) hs.h_offs[i] = offs[r0 + i] - b0;
         hipError_t e;
-        if ((e = hipMemcpyAsync(hs.d_reads, hs.h_reads, (size_t)nb, hipMemcpyHostToDevice, s)) != hipSuccess ||
-            (e = hipMemcpyAsync(hs.d_offs, hs.h_offs, sizeof(int64_t) * (size_t)(n + 1), hipMemcpyHostToDevice, s)) !=
-                hipSuccess)
+        // a small batch is read from the pinned buffers by the search kernel
+        // itself, which writes its results there: one launch and no copies
+        const bool direct = kDirectBytes >= nb + (int64_t)(sizeof(int64_t) + sizeof(sa_hit)) * n && searches_inline(d, c);
+        if (!direct &&
+            ((e = hipMemcpyAsync(hs.d_reads, hs.h_reads, (size_t)nb, hipMemcpyHostToDevice, s)) != hipSuccess ||
+             (e = hipMemcpyAsync(hs.d_offs, hs.h_offs, sizeof(int64_t) * (size_t)(n + 1), hipMemcpyHostToDevice, s)) !=
+                 hipSuccess))
             return bail(hip_fail(e, "batch upload"));
-        if ((rc = enqueue_batch(d, ws, hs.d_reads, hs.d_offs, nullptr, n, hs.d_out, s, c))) return bail(rc);
-        if ((e = hipMemcpyAsync(hs.h_out, hs.d_out, sizeof(sa_hit) * (size_t)n, hipMemcpyDeviceToHost, s)) !=
-                hipSuccess ||
+        if ((rc = enqueue_batch(d, ws, direct ? hs.m_reads : hs.d_reads, direct ? hs.m_offs : hs.d_offs, nullptr, n,
+                                direct ? hs.m_out : hs.d_out, s, c)))
+            return bail(rc);
+        if ((!direct && (e = hipMemcpyAsync(hs.h_out, hs.d_out, sizeof(sa_hit) * (size_t)n, hipMemcpyDeviceToHost, s)) !=
+                            hipSuccess) ||
             (e = hipEventRecord(hs.done, s)) != hipSuccess)
             return bail(hip_fail(e, "batch download"));
     }

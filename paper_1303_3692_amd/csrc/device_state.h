@@ -43,6 +43,9 @@ struct HostSlot {
     char *h_reads = nullptr;
     int64_t *h_offs = nullptr;
     sa_hit *h_out = nullptr;
+    uint8_t *m_reads = nullptr;  // the pinned buffers as the device addresses them
+    int64_t *m_offs = nullptr;
+    sa_hit *m_out = nullptr;
     uint8_t *d_reads = nullptr;
     int64_t *d_offs = nullptr;
     sa_hit *d_out = nullptr;
