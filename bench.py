@@ -372,7 +372,7 @@ def main():
     log(f"random 16-byte loads: {ceiling / 1e9:.1f} G/s; search scattered segments {scattered_rate / 1e9:.1f} G/s")
     roofline = {"bound": "hbm", "achieved": round(achieved, 2), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                 "frac": round(achieved / HBM_PEAK_GBS, 5), "traffic": traffic, "l2_hit_rate": l2_hit,
-                "kernel": "search_tuned_kernel", "packs_reads": packs_inline(cfg),
+                "kernel": "search_reads_kernel", "packs_reads": packs_inline(cfg),
                 "alg_bytes_per_launch": B, "alg_bytes_per_read": round(B / N, 2),
                 # the same with the input counted as the fused kernel reads it (ASCII + offsets)
                 "ingest_alg_bytes_per_launch": B_ingest,

@@ -106,8 +106,9 @@ void sa_free(sa_index *ix);                           /* NULL is a no-op        
  * take more than a quarter of the free device memory), the first SA row
  * whose suffix is not below v with the bracket of rows that start with v,
  * or the result of the reads that start with v when there are none (4^k + 1
- * entries of 16 bytes; see sa_set_prefix_table).  The host index may be
- * freed afterwards.  Released with sa_dfree (NULL is a no-op). */
+ * entries of 16 bytes; see sa_set_prefix_table).  A shorter text gets a
+ * table of at most 1 MiB of its own, which batches in input order start
+ * from whatever their settings.  The host index may be freed afterwards.  Released with sa_dfree (NULL is a no-op). */
 int sa_upload(const sa_index *ix, int device, sa_dindex **out);
 void sa_dfree(sa_dindex *d);
 int64_t sa_dindex_length(const sa_dindex *d);
@@ -194,9 +195,10 @@ typedef struct {
                             search kernel's own area does not depend on it);
                             0 = the index's default                             */
     int defer;           /* tuned, with inline_pack: not 0 = a read whose prefix-
-                            table bracket holds more than one row (or that has
-                            none) is set aside and searched together with other
-                            such reads, so that one long search does not keep the
+                            table bracket holds more than eight rows (or that has
+                            none, or several rows that share its first 32 bases)
+                            is set aside and searched together with other such
+                            reads, so that one long search does not keep the
                             other lanes of its wave idle; 0 = every 64 reads are
                             searched to their end before the next (0..1024; the
                             index default is 3).  Results never change.         */
@@ -216,7 +218,9 @@ int sa_default_cfg(const sa_dindex *d, sa_match_cfg *cfg);
  * The batch streams through pinned staging in chunks of whole reads (at most
  * 32 MiB of bytes or 2^19 reads each): the host copies one chunk in while the
  * device searches the one before, so the device sees each chunk as a batch
- * of its own (stage times and counts report the last chunk).
+ * of its own (stage times and counts report the last chunk).  A chunk of at
+ * most 4 MiB is not copied to the device: the kernels read it from the
+ * pinned staging and write the results there.
  * Thread-safe for distinct streams. */
 int match_batch(const sa_dindex *d, const char *reads, const int64_t *offs, int64_t nreads,
                 sa_hit *out, void *hip_stream, const sa_match_cfg *cfg);

@@ -191,12 +191,12 @@ __host__ __device__ inline size_t tile_lds_bytes(int levels) {
 // Start of the per-wave packing areas after the tile (16-byte aligned).
 __host__ __device__ inline size_t inline_area_offset(int levels) { return (tile_lds_bytes(levels) + 15) & ~(size_t)15; }
 
-// search_reads_kernel.  Registers are held to six waves per SIMD (78 used, no
+// search_reads_kernel.  Registers are held to six waves per SIMD (80, no
 // spills), and a wave's LDS area is sized so that 24 waves fit a compute
 // unit: what a wave waits for is memory latency, so more waves in flight
 // mean more of the memory's rate.  250 Mbp, 64M reads of 150 bases on
-// MI355X: 5.52 ms at 16 waves, 5.16 at 24; held to 8 waves per SIMD it spills
-// 7 registers and was slower (5.08 against 5.00).
+// MI355X, with the kernel's first form: 5.52 ms at 16 waves, 5.16 at 24; held
+// to 8 waves per SIMD it spilled 7 registers and was slower (5.08 against 5.00).
 constexpr int kSearchWavesPerSimd = 6;
 
 // LDS of search_reads_kernel in 4-byte words: after the tile (when it is
@@ -214,9 +214,8 @@ constexpr int kStagePieces = 64 * 11;
 constexpr int kStageBadWords = kStagePieces / 32;  // a bit per piece
 static_assert(kStagePieces % 32 == 0 && kStagePieces >= SA_MAX_READ / 16 + 1, "any read fits a wave's staging area");
 // Queued reads a wave searches together at most, and the words of their
-// records.  32 of them, two lanes each, against 64: 250 Mbp / 64M reads 4.75
-// against 4.82 ms, 4M reads of 20-300 bases 379 against 392 us (4M x 100
-// 280 against 273); 16: 4.94 ms.
+// records.  32 of them, two lanes each, or 64: the same within 1 % (250 Mbp /
+// 64M reads 4.53 ms, 4M reads of 100 bases 260 us); 16: 4.72 ms and 276 us.
 constexpr int kQueueReads = 32;
 constexpr int kPoolWords = 768;
 

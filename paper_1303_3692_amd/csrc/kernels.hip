@@ -1594,16 +1594,16 @@ static_assert(64 * kProbePieces <= kStagePieces && 16 * (kProbePieces - 1) >= kM
 //      queued reads are searched together, so that long binary searches run
 //      with all lanes busy and hold up nobody (search_queued).
 //
-// What bounds it: scattered lines and their latency.  On MI355X a random
-// 16-byte load brings in a 128-byte line whatever the cache policy (loads of
-// both halves of a line run at the rate of one), at most 52-58 G lines/s;
-// the 250 Mbp / 64M x 150 batch takes 233 M line misses (3.6 per read: 1.2
-// of ASCII, the table entry, the text) at 48 G/s.  Measured before (words in
-// registers, a second kernel for long reads, set-aside reads read again) and
-// after: that batch 5.33 and 4.86 ms; 16 Mbp, 4M x 100 bases 393 and 292 us,
-// 4M x 20-300 580 and 390 us, 50,001 x 20-1024 264 and 39 us, 65,536 x 1024
-// (on 10 Mbp) 114 and 53 us, 64 x 30-300 36 and 9 us.  Vector instructions
-// per chunk of 64 fell to a third (965 for that first batch).
+// What bounds it: lines. On MI355X a random 16-byte load brings in a 128-byte
+// line whatever the cache policy (loads of both halves of a line run at the
+// rate of one), at most 52-58 G lines/s.  The 250 Mbp / 64M x 150 batch needs
+// about 3.2 per read: 1.3 of ASCII, offsets and results, which alone take 2.0
+// ms (5.6 TB/s), the table entry (1.6 ms more), and the text, which hides
+// behind them; what is left is the queued searches.  Measured at first (words
+// in registers, a second kernel for long reads, set-aside reads read again)
+// and now: that batch 5.33 and 4.47 ms; 16 Mbp, 4M x 100 bases 393 and 243
+// us, 4M x 20-300 580 and 321 us, 50,001 x 20-1024 264 and 37 us, 65,536 x
+// 1024 (on 10 Mbp) 113 and 41 us, 64 x 30-300 30 and 8 us.
 template <bool COUNT, bool TILE>
 __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(COUNT ? 1 : kSearchWavesPerSimd))) void search_reads_kernel(
     DevIndex ix, int levels, int use_table_i, int group, int per, int64_t nchunks, int defer, InlineArea area,
