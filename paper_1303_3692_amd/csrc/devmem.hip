@@ -1,6 +1,8 @@
 // Device memory of resident indexes (see devmem.h).
 #include "devmem.h"
 
+#include <unistd.h>
+
 #include <chrono>
 #include <condition_variable>
 #include <mutex>
@@ -87,12 +89,16 @@ struct Keeper {
 
 // Never destroyed, so that an index freed while the process ends finds it;
 // its thread is ended before the HIP runtime is (which was loaded before).
+// A forked child has no such thread to wait for.
 Keeper &keeper() {
     static Keeper *k = new Keeper;
     static struct Closer {
         Keeper *k;
-        ~Closer() { k->close(); }
-    } closer{k};
+        pid_t owner;
+        ~Closer() {
+            if (getpid() == owner) k->close();
+        }
+    } closer{k, getpid()};
     return *k;
 }
 
