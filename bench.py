@@ -356,7 +356,7 @@ def main():
     # rocprofv3 counters, only when they were taken on these kernel sources
     # and this workload
     traffic, l2_hit = None, None
-    counters = os.path.join(ROOT, "profiles", f"search_tuned_{args.config}_counters.json")
+    counters = os.path.join(ROOT, "profiles", f"search_reads_{args.config}_counters.json")
     if os.path.exists(counters):
         prof = json.load(open(counters))
         if prof.get("kernel_src") == kernel_source_hash() and prof.get("workload") == args.config:
