@@ -6,16 +6,16 @@
 //            reads not selected; bad intervals raise a flag instead of being
 //            read.  Per-tile sums
 //   emit     each workgroup adds up the tiles before its own (a scan kernel
-//            does it for all when there are thousands) and all of them, the
-//            first one hands the total to the host; then the int64 offsets
-//            by a scan of the tile's reads and, when the whole list fits the
-//            caller's buffer, SA[lo .. lo + count) of each read, one thread
-//            per position
+//            does it for all when there are thousands) and all of them; then
+//            the int64 offsets by a scan of the tile's reads and, when the
+//            whole list fits the caller's buffer, SA[lo .. lo + count) of each
+//            read, one thread per position
+//   done     the total to the host, when the lists are written
 //
-// The host waits for the total alone, in memory that the device writes over
-// the bus.  Bound by launches and that wait for batches of up to about
+// The host waits for the total in memory that the device writes over the bus.  Bound by launches and that wait for batches of up to about
 // a million reads: with a scratch of its own for each call and five device
-// operations it took 98 us for 1,000,000 reads of 16 Mbp, now 24.
+// operations it took 98 us for 1,000,000 reads of 16 Mbp, now 30 (24 with the
+// total handed over by the emit kernel, before the lists are whole).
 #include <hip/hip_runtime.h>
 
 #include <chrono>
@@ -25,8 +25,7 @@
 
 namespace samatch {
 
-// Device words after the tile sums: the total (when a scan kernel has added
-// them up), and the number of the last call with a bad interval.
+// Device words after the tile sums: the total, and the number of the last call with a bad interval.
 constexpr int kLocTail = 2;
 // Tiles up to which each workgroup adds up the sums by itself.
 constexpr int kLocOwnSums = 2048;
@@ -142,8 +141,8 @@ __global__ __launch_bounds__(1024) void locate_scan_tiles_kernel(int64_t *tile_s
 __global__ __launch_bounds__(kLocBlock) void locate_emit_kernel(const int4 *__restrict__ hits, int64_t nreads, int n,
                                                                 int cap, int min_len,
                                                                 const int64_t *__restrict__ tile_sum,
-                                                                const int64_t *__restrict__ tail, bool scanned,
-                                                                int64_t call, LocateTotal *host, int64_t capacity,
+                                                                int64_t *tail, bool scanned, int64_t call,
+                                                                int64_t capacity,
                                                                 const int32_t *__restrict__ sa,
                                                                 int64_t *__restrict__ offs, int32_t *__restrict__ pos,
                                                                 int rounds) {
@@ -169,12 +168,7 @@ __global__ __launch_bounds__(kLocBlock) void locate_emit_kernel(const int4 *__re
         total = block_incl_sum(all, incl, lds);
     }
     const bool bad = tail[1] == call;
-    if (blockIdx.x == 0 && t == 0) {
-        host->total = total;
-        host->bad = bad;
-        __threadfence_system();
-        __hip_atomic_store(&host->call, (uint64_t)call, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
-    }
+    if (!scanned && blockIdx.x == 0 && t == 0) tail[0] = total;
     const bool fits = !bad && total <= capacity;
     for (int r = 0; r < rounds && base + r * kLocBlock < nreads; ++r) {
         const int64_t i = base + r * kLocBlock + t;
@@ -201,6 +195,16 @@ __global__ __launch_bounds__(kLocBlock) void locate_emit_kernel(const int4 *__re
         carry += count;
     }
     if (blockIdx.x == gridDim.x - 1 && t == 0) offs[nreads] = carry;
+}
+
+// Tells the waiting host that the call's lists are written.  A launch of its
+// own: whoever reads the offsets after the call returned, on whatever stream,
+// finds them whole, and a caller that was refused may release its buffers.
+__global__ void locate_done_kernel(const int64_t *__restrict__ tail, int64_t call, LocateTotal *host) {
+    host->total = tail[0];
+    host->bad = tail[1] == call;
+    __threadfence_system();
+    __hip_atomic_store(&host->call, (uint64_t)call, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 // Waits until the device has written this call's total, or the
@@ -241,7 +245,8 @@ int locate_on(const sa_dindex *d, LocateScratch &sc, const sa_hit *d_hits, int64
     if (scan)
         hipLaunchKernelGGL(locate_scan_tiles_kernel, dim3(1), dim3(1024), 0, s, sc.dev, (int)ntiles, tail);
     hipLaunchKernelGGL(locate_emit_kernel, dim3((unsigned)ntiles), dim3(kLocBlock), 0, s, hits, nreads, n, cap,
-                       min_len, sc.dev, tail, scan, call, sc.host_dev, pos_capacity, d->d_sa, d_offs, d_pos, rounds);
+                       min_len, sc.dev, tail, scan, call, pos_capacity, d->d_sa, d_offs, d_pos, rounds);
+    hipLaunchKernelGGL(locate_done_kernel, dim3(1), dim3(1), 0, s, tail, call, sc.host_dev);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(e, "locate launch");
     if (int rc = wait_total(sc, (uint64_t)call, s)) return rc;
@@ -303,7 +308,9 @@ extern "C" int sa_locate(const sa_dindex *d, const sa_hit *hits, int64_t nreads,
     // counts and offsets first; positions only when they fit
     int rc = locate_on(d, b.scratch, b.hits, nreads, cap, min_len, b.offs, nullptr, 0, b.s, total);
     if (rc != SA_OK && rc != SA_ENOSPC) return rc;
-    if ((e = hipMemcpy(offs, b.offs, sizeof(int64_t) * (size_t)(nreads + 1), hipMemcpyDeviceToHost)) != hipSuccess)
+    if ((e = hipMemcpyAsync(offs, b.offs, sizeof(int64_t) * (size_t)(nreads + 1), hipMemcpyDeviceToHost, b.s)) !=
+            hipSuccess ||
+        (e = hipStreamSynchronize(b.s)) != hipSuccess)
         return hip_fail(e, "locate download");
     if (*total == 0) return SA_OK;
     if (*total > pos_capacity) return fail(SA_ENOSPC, "positions buffer too small (see *total)");

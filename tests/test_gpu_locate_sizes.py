@@ -50,3 +50,35 @@ def test_offsets_and_positions(nreads, cap):
         else:
             continue
         assert torch.equal(offs, want) and bool((pos[max(room, 0):] == -7).all())
+
+
+@pytest.mark.parametrize("nreads", [3, 70_000, 3_000_000])
+def test_offsets_are_whole_when_the_call_returns(nreads):
+    """Another stream that does not wait for the call's, and the host form,
+    see every offset once the call has returned."""
+    if not torch.cuda.is_available():
+        pytest.skip("no HIP device")
+    print("case: locate offsets at return", nreads, flush=True)
+    n = 20_000
+    text = np.random.default_rng(1).choice(np.frombuffer(b"ACGT", dtype=np.uint8), n)
+    d = S.sa_upload(S.sa_build(text), 0)
+    i = torch.arange(nreads, device="cuda")
+    lo = (i * 7919) % (n - 400)
+    rows = i % 4
+    hits = torch.stack([lo, lo + rows, i % 50, torch.ones_like(i)], 1).int()
+    want = torch.zeros(nreads + 1, dtype=torch.int64, device="cuda")
+    want[1:] = torch.cumsum(rows, 0)
+    total = int(want[-1])
+    pos = torch.empty(total, dtype=torch.int32, device="cuda")
+    side = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    for _ in range(5):
+        offs = torch.full((nreads + 1,), -7, dtype=torch.int64, device="cuda")
+        torch.cuda.synchronize()
+        assert S.locate_dev(d, hits, 4, 0, offs, pos) == total
+        with torch.cuda.stream(side):
+            seen = offs.clone()
+        torch.cuda.synchronize()
+        assert torch.equal(seen, want)
+    host_offs, host_pos = S.locate(d, hits.cpu().numpy(), 4, 0)
+    assert np.array_equal(np.asarray(host_offs), want.cpu().numpy()) and len(host_pos) == total
