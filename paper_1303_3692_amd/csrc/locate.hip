@@ -12,8 +12,9 @@
 //            read, one thread per position
 //   done     the total to the host, when the lists are written
 //
-// The host waits for the total in memory that the device writes over the bus.  Bound by launches and that wait for batches of up to about
-// a million reads: with a scratch of its own for each call and five device
+// The host waits for the total in memory that the device writes over the bus.
+// Bound by launches and that wait for batches of up to about a million
+// reads: with a scratch of its own for each call and five device
 // operations it took 98 us for 1,000,000 reads of 16 Mbp, now 30 (24 with the
 // total handed over by the emit kernel, before the lists are whole).
 #include <hip/hip_runtime.h>

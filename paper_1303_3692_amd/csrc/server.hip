@@ -761,10 +761,11 @@ extern "C" int sa_server_create(const sa_dindex *const *refs, int nrefs, const s
                     (e = hipMalloc((void **)&sl.d_se, sizeof(int64_t) * 2 * (size_t)o.max_batch_reads)) != hipSuccess ||
                     (e = hipMalloc((void **)&sl.d_out, sizeof(sa_hit) * (size_t)o.max_batch_reads)) != hipSuccess)
                     return hip_fail(e, "slot allocation");
-                // every index's scratch for this stream now, not on the first batch (its
-                // batches are searched in input order and need no packed arrays)
+                // every index's scratch for this stream now, not on the first batch (the
+                // tuned search takes its batches in input order and needs no packed arrays)
                 for (sa_dindex *d : s->refs) {
-                    int rc = workspace_for(d, sl.stream)->reserve(o.max_batch_reads, false);
+                    const bool packs = resolve_cfg(d, nullptr).kernel != SA_KERNEL_TUNED;
+                    int rc = workspace_for(d, sl.stream)->reserve(o.max_batch_reads, packs);
                     if (rc) return rc;
                 }
             }
