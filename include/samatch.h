@@ -311,9 +311,10 @@ int sa_tune_candidates(const sa_dindex *d, const int64_t *d_offs, int64_t nreads
  * d_pos[d_offs[i] .. d_offs[i + 1]).  *total receives d_offs[nreads].  When
  * *total > pos_capacity the offsets are still written, no position is, and
  * the call returns SA_ENOSPC (call again with a buffer of *total entries).
- * Enqueued on hip_stream; waits for it to read the total, the positions are
- * written asynchronously after return.  SA_EINVAL for a selected hit whose
- * interval is not inside [0, n].  Allocates a small scratch per call. */
+ * Enqueued on hip_stream; waits for the total: the offsets are written when
+ * the call returns, the positions in the order of hip_stream.  SA_EINVAL for a selected hit whose
+ * interval is not inside [0, n].  Keeps a small scratch per (index, stream);
+ * concurrent calls on one stream are served one after the other. */
 int sa_locate_dev(const sa_dindex *d, const sa_hit *d_hits, int64_t nreads, int32_t cap, int32_t min_len,
                   int64_t *d_offs, int32_t *d_pos, int64_t pos_capacity, void *hip_stream, int64_t *total);
 
