@@ -573,17 +573,14 @@ __device__ __forceinline__ uint64_t row_order_key(const RowHead &row, int k) {
 
 // First row whose order key reaches `target`, found by the whole wave, 64 rows
 // at a time.
-__device__ __forceinline__ int first_row_from(const DevIndex &ix, int k, uint64_t target, int lane) {
-    int lo = 0, hi = ix.n;
-    const uint32_t share = 0xFFFFFFFFu / 65u * (uint32_t)(lane + 1);
+__device__ __forceinline__ uint32_t first_row_from(const DevIndex &ix, int k, uint64_t target, int lane) {
+    uint32_t lo = 0, hi = (uint32_t)ix.n;
     while (lo < hi) {
-        const int rows = hi - lo;
-        const int piv = lo + (rows <= 64 ? lane : (int)__umulhi((uint32_t)rows, share));
-        const bool at = piv < hi;
-        const bool reached = at && row_order_key(row_head(ix.rows, piv), k) >= target;
+        const uint32_t piv = wave_probe_row(lo, hi, lane);
+        const bool reached = piv < hi && row_order_key(row_head(ix.rows, (int)piv), k) >= target;
         const uint64_t r = wave_ballot(reached);
-        const int probes = min_i(rows, 64), to = r ? (int)__builtin_ctzll(r) : probes;
-        const int above = __shfl(piv, min_i(to, 63), 64), below = __shfl(piv, max_i(to - 1, 0), 64);
+        const int probes = (int)(hi - lo < 64u ? hi - lo : 64u), to = r ? (int)__builtin_ctzll(r) : probes;
+        const uint32_t above = __shfl(piv, min_i(to, 63), 64), below = __shfl(piv, max_i(to - 1, 0), 64);
         if (to < probes) hi = above;
         if (to > 0) lo = below + 1;
     }
@@ -615,38 +612,39 @@ __global__ __launch_bounds__(kTabThreads) void build_prefix_table_kernel(DevInde
     __shared__ uint32_t first[kTabSpan + 1];  // a string's first row, then T
     __shared__ uint32_t last[kTabSpan];       // the row after a string's last one, 0 without rows
     __shared__ uint32_t wave_min[kTabThreads / 64];
-    __shared__ int bound[2];
+    __shared__ uint32_t bound[2];
     __shared__ int near_short;
     const int t = threadIdx.x, lane = t & 63, wave = t >> 6, threads = blockDim.x;
     const int span = 1 << (2 * bases);  // a multiple of the threads, which are full waves
     const uint64_t v0 = (uint64_t)blockIdx.x << (2 * bases);
     if (t == 0) near_short = 0;
     if (wave < 2) {
-        const int r = first_row_from(ix, k, 2 * (v0 + (wave ? (uint64_t)span : 0u)) + 1, lane);
+        const uint32_t r = first_row_from(ix, k, 2 * (v0 + (wave ? (uint64_t)span : 0u)) + 1, lane);
         if (lane == 0) bound[wave] = r;
     }
     __syncthreads();
-    const int r0 = bound[0], r1 = bound[1];
+    const uint32_t r0 = bound[0], r1 = bound[1];  // at most 2^31 - 1; a stride past that needs the last bit
     for (int i = t; i < span; i += threads) {
-        first[i] = (uint32_t)r1;
+        first[i] = r1;
         last[i] = 0;
     }
-    if (t == 0) first[span] = (uint32_t)r1;
+    if (t == 0) first[span] = r1;
     __syncthreads();
-    for (int r = r0 + t; r < r1; r += threads) {
-        const uint64_t key = row_order_key(row_head(ix.rows, r), k);
+    auto order_key = [&](uint32_t r) { return row_order_key(row_head(ix.rows, (int)r), k); };
+    for (uint32_t r = r0 + t; r < r1; r += threads) {
+        const uint64_t key = order_key(r);
         const int i = (int)((key >> 1) - v0);
         if (key & 1) {
-            if (r == r0 || row_order_key(row_head(ix.rows, r - 1), k) != key) atomicMin(&first[i], (uint32_t)r);
-            if (r + 1 == r1 || row_order_key(row_head(ix.rows, r + 1), k) != key) last[i] = (uint32_t)r + 1;
+            if (r == r0 || order_key(r - 1) != key) atomicMin(&first[i], r);
+            if (r + 1 == r1 || order_key(r + 1) != key) last[i] = r + 1;
         } else {  // below its padded string, above the one before
-            atomicMin(&first[i - 1], (uint32_t)r);
+            atomicMin(&first[i - 1], r);
             near_short = 1;
         }
     }
-    if (t < k && r0 - 1 - t >= 0 && row_head(ix.rows, r0 - 1 - t).len < k) near_short = 1;
+    if (t < k && (uint32_t)t < r0 && row_head(ix.rows, (int)r0 - 1 - t).len < k) near_short = 1;
     __syncthreads();
-    uint32_t carry = (uint32_t)r1;
+    uint32_t carry = r1;
     for (int base = span - threads; base >= 0; base -= threads) {
         uint32_t x = first[base + t];
 #pragma unroll

@@ -1,0 +1,20 @@
+"""The row arithmetic of the prefix table's build at the largest supported
+text (n = 2^31 - 1), compiled for the CPU with the undefined-behaviour
+sanitizer."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+
+@pytest.mark.skipif(shutil.which("g++") is None, reason="needs g++")
+def test_rows_of_the_largest_text(tmp_path):
+    exe = tmp_path / "row_check"
+    subprocess.run(["g++", "-std=c++17", "-O1", "-fsanitize=undefined", "-fno-sanitize-recover=all",
+                    "-I" + os.path.join(ROOT, "paper_1303_3692_amd", "csrc"),
+                    os.path.join(ROOT, "tests", "native", "row_check.cpp"), "-o", str(exe)], check=True)
+    r = subprocess.run([str(exe)], capture_output=True, text=True)
+    assert r.returncode == 0 and r.stdout.strip() == "ok", r.stdout + r.stderr
