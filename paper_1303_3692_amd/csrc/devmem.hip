@@ -3,9 +3,11 @@
 
 #include <unistd.h>
 
+#include <algorithm>
 #include <chrono>
 #include <condition_variable>
 #include <mutex>
+#include <new>
 #include <system_error>
 #include <thread>
 #include <unordered_map>
@@ -20,7 +22,8 @@ struct Block {
     void *p;
     size_t bytes;
     int device;
-    Clock::time_point since;  // when it was kept
+    Clock::time_point since;  // when it was kept, or last refused by hipFree
+    bool idle;                // no kernel uses it: it may be handed out again
 };
 
 // Makes a device current for the scope.
@@ -39,36 +42,57 @@ struct Keeper {
     std::mutex mu;
     std::condition_variable cv;
     std::unordered_map<void *, Block> used;  // blocks handed out
-    std::vector<Block> kept;
+    std::vector<Block> kept;                 // has room for every block there is, so that keeping one allocates nothing
+    size_t blocks = 0;                       // there are: handed out, kept, or on their way
     std::thread watch;  // gives back what is not used again; ends when nothing is kept
     bool watching = false, closing = false;
 
     // The process ends, and its memory with it: nothing is kept any more.
     void close() {
+        std::thread last;
         {
             std::lock_guard<std::mutex> lk(mu);
             closing = true;
+            last.swap(watch);
         }
         cv.notify_all();
-        if (watch.joinable()) watch.join();
+        if (last.joinable()) last.join();
     }
 
-    static void release(const std::vector<Block> &blocks) {
-        for (const Block &b : blocks) {
-            Current c(b.device);
-            (void)hipFree(b.p);
+    // Gives those kept blocks back for which `which` holds (with the lock
+    // held, so that whoever finds too little memory meanwhile waits for
+    // this).  A block that hipFree refuses stays, and is tried again.
+    template <class F>
+    void release(F which) {
+        for (size_t i = 0; i < kept.size();) {
+            if (!which(kept[i])) {
+                ++i;
+                continue;
+            }
+            Current c(kept[i].device);
+            if (hipFree(kept[i].p) == hipSuccess) {
+                kept.erase(kept.begin() + (long)i);
+                --blocks;
+            } else {
+                (void)hipGetLastError();
+                kept[i].since = Clock::now();
+                ++i;
+            }
         }
     }
 
-    std::vector<Block> take_kept(int device, Clock::time_point before) {
-        std::vector<Block> out, stay;
+    size_t held(int device) const {
+        size_t bytes = 0;
         for (const Block &b : kept)
-            ((device < 0 || b.device == device) && b.since <= before ? out : stay).push_back(b);
-        kept.swap(stay);
-        return out;
+            if (b.device == device) bytes += b.bytes;
+        return bytes;
     }
 
     void run() {
+        // another thread may be capturing a stream in global mode, which
+        // forbids every thread a hipFree that has not asked for this mode
+        hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+        (void)hipThreadExchangeStreamCaptureMode(&mode);
         std::unique_lock<std::mutex> lk(mu);
         while (!closing && !kept.empty()) {
             Clock::time_point oldest = kept[0].since;
@@ -78,10 +102,8 @@ struct Keeper {
                 cv.wait_until(lk, due);
                 continue;
             }
-            const std::vector<Block> old = take_kept(-1, Clock::now() - std::chrono::seconds(kKeepSeconds));
-            lk.unlock();
-            release(old);
-            lk.lock();
+            const Clock::time_point before = Clock::now() - std::chrono::seconds(kKeepSeconds);
+            release([&](const Block &b) { return b.since <= before; });
         }
         watching = false;
     }
@@ -118,14 +140,18 @@ hipError_t dev_alloc(void **p, size_t bytes) {
         size_t best = k.kept.size();
         for (size_t i = 0; i < k.kept.size(); i++) {
             const Block &b = k.kept[i];
-            if (b.device == device && b.bytes >= bytes && b.bytes - bytes <= bytes / 8 &&
+            if (b.device == device && b.idle && b.bytes >= bytes && b.bytes - bytes <= bytes / 8 &&
                 (best == k.kept.size() || b.bytes < k.kept[best].bytes))
                 best = i;
         }
         if (best < k.kept.size()) {
             const Block b = k.kept[best];
+            try {
+                k.used.emplace(b.p, b);
+            } catch (const std::bad_alloc &) {
+                return hipErrorOutOfMemory;
+            }
             k.kept.erase(k.kept.begin() + (long)best);
-            k.used.emplace(b.p, b);
             *p = b.p;
             return hipSuccess;
         }
@@ -137,8 +163,16 @@ hipError_t dev_alloc(void **p, size_t bytes) {
         e = hipMalloc(p, bytes);
     }
     if (e != hipSuccess) return e;
-    std::lock_guard<std::mutex> lk(k.mu);
-    k.used.emplace(*p, Block{*p, bytes, device, Clock::time_point()});
+    try {
+        std::lock_guard<std::mutex> lk(k.mu);
+        k.kept.reserve(k.blocks + 1);
+        k.used.emplace(*p, Block{*p, bytes, device, Clock::time_point(), true});
+        ++k.blocks;
+    } catch (const std::bad_alloc &) {
+        (void)hipFree(*p);
+        *p = nullptr;
+        return hipErrorOutOfMemory;
+    }
     return hipSuccess;
 }
 
@@ -153,62 +187,48 @@ void dev_free(void *p) {
         auto it = k.used.find(p);
         if (it == k.used.end()) return;
         b = it->second;
-        k.used.erase(it);
+        k.used.erase(it);  // before hipFree, after which another thread may be given the same address
     }
     Current c(b.device);
-    const bool idle = hipDeviceSynchronize() == hipSuccess;
-    if (idle && !closing && b.bytes <= kKeepBytes) {
-        std::vector<Block> out;  // the oldest ones, when there is no room for this one
-        {
+    b.idle = hipDeviceSynchronize() == hipSuccess;
+    if (!b.idle || closing || b.bytes > kKeepBytes) {
+        if (hipFree(p) == hipSuccess) {
             std::lock_guard<std::mutex> lk(k.mu);
-            size_t held = b.bytes;
-            for (const Block &x : k.kept)
-                if (x.device == b.device) held += x.bytes;
-            for (size_t i = 0; i < k.kept.size() && held > kKeepBytes;) {
-                if (k.kept[i].device != b.device) {
-                    i++;
-                    continue;
-                }
-                held -= k.kept[i].bytes;
-                out.push_back(k.kept[i]);
-                k.kept.erase(k.kept.begin() + (long)i);
-            }
-            b.since = Clock::now();
-            k.kept.push_back(b);
-            if (!k.watching) {
-                if (k.watch.joinable()) k.watch.join();  // it has ended, or ends without the lock
-                try {
-                    k.watch = std::thread([&k] { k.run(); });
-                    k.watching = true;
-                } catch (const std::system_error &) {
-                    out.push_back(k.kept.back());  // nobody would give it back
-                    k.kept.pop_back();
-                }
-            }
+            --k.blocks;
+            return;
         }
-        Keeper::release(out);
-        return;
+        (void)hipGetLastError();  // kept, and tried again
     }
-    (void)hipFree(b.p);
+    std::lock_guard<std::mutex> lk(k.mu);
+    // the oldest ones go when there is no room for this one
+    size_t held = k.held(b.device) + b.bytes;
+    k.release([&](const Block &x) {
+        if (x.device != b.device || held <= kKeepBytes) return false;
+        held -= x.bytes;
+        return true;
+    });
+    b.since = Clock::now();
+    k.kept.push_back(b);
+    if (k.watching || k.closing) return;
+    if (k.watch.joinable()) k.watch.join();  // it has ended, or ends without the lock
+    try {
+        k.watch = std::thread([&k] { k.run(); });
+        k.watching = true;
+    } catch (const std::system_error &) {
+        k.release([&](const Block &x) { return x.p == p; });  // nobody would give it back
+    }
 }
 
 size_t dev_kept(int device) {
     Keeper &k = keeper();
     std::lock_guard<std::mutex> lk(k.mu);
-    size_t held = 0;
-    for (const Block &b : k.kept)
-        if (b.device == device) held += b.bytes;
-    return held;
+    return k.held(device);
 }
 
 void dev_trim(int device) {
     Keeper &k = keeper();
-    std::vector<Block> out;
-    {
-        std::lock_guard<std::mutex> lk(k.mu);
-        out = k.take_kept(device, Clock::time_point::max());
-    }
-    Keeper::release(out);
+    std::lock_guard<std::mutex> lk(k.mu);
+    k.release([&](const Block &b) { return b.device == device; });
 }
 
 }  // namespace samatch
