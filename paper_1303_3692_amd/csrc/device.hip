@@ -60,12 +60,12 @@ static hipError_t grow(void **p, size_t bytes) {
         *p = nullptr;
         if (e != hipSuccess) return e;
     }
-    return hipMalloc(p, bytes ? bytes : 16);
+    return dev_malloc(p, bytes ? bytes : 16);
 }
 
 int Workspace::reserve(int64_t nreads, bool pack_pass) {
     hipError_t e;
-    if (!b.stats && (e = hipMalloc((void **)&b.stats, sizeof(unsigned long long) * kStatWords)) != hipSuccess)
+    if (!b.stats && (e = dev_malloc((void **)&b.stats, sizeof(unsigned long long) * kStatWords)) != hipSuccess)
         return hip_fail(e, "scratch allocation");
     for (hipEvent_t &ev_i : ev)
         if (!ev_i && (e = hipEventCreate(&ev_i)) != hipSuccess) return hip_fail(e, "event creation");
@@ -81,7 +81,7 @@ int Workspace::reserve(int64_t nreads, bool pack_pass) {
         (e = grow((void **)&b.val[1], sizeof(uint32_t) * (size_t)c)) != hipSuccess ||
         (e = grow((void **)&b.hist, sizeof(uint32_t) * 256 * (size_t)nblocks)) != hipSuccess)
         return hip_fail(e, "scratch allocation");
-    if (!b.digit_total && (e = hipMalloc((void **)&b.digit_total, sizeof(uint32_t) * 256)) != hipSuccess)
+    if (!b.digit_total && (e = dev_malloc((void **)&b.digit_total, sizeof(uint32_t) * 256)) != hipSuccess)
         return hip_fail(e, "scratch allocation");
     cap = c;
     return SA_OK;
@@ -399,7 +399,7 @@ int set_prefix_table(sa_dindex *d, int k) {
 // rounded up to 16), packs them into d_text and checks them.
 int pack_on_device(const char *ascii, int64_t n, uint8_t *scratch, uint64_t *d_text, int64_t words) {
     unsigned long long *flag = nullptr, first_bad = ~0ull;
-    hipError_t e = hipMalloc((void **)&flag, sizeof *flag);
+    hipError_t e = dev_malloc((void **)&flag, sizeof *flag);
     if (e == hipSuccess) e = hipMemcpy(scratch, ascii, (size_t)n, hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipMemcpy(flag, &first_bad, sizeof first_bad, hipMemcpyHostToDevice);
     if (e == hipSuccess) e = launch_pack_text(scratch, n, d_text, words, flag, nullptr);

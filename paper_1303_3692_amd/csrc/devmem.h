@@ -5,8 +5,8 @@
 // that (16 Mbp, whose index takes 4.6 GB: 122 ms per index from the fiftieth
 // on, against 6 ms for everything else).  Blocks of freed indexes are
 // therefore kept for the next one: at most kKeepBytes per device, given back
-// when they have not been used for kKeepSeconds, when an allocation here
-// fails, or when dev_trim is called.
+// when they have not been used for kKeepSeconds, when an allocation of the
+// library finds too little memory, or when dev_trim is called.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -19,6 +19,10 @@ constexpr int kKeepSeconds = 2;
 
 // Memory on the current device, at least 256-byte aligned, contents undefined.
 hipError_t dev_alloc(void **p, size_t bytes);
+
+// hipMalloc for everything else the library allocates: when there is too
+// little memory, what is kept is given back and it is tried again.
+hipError_t dev_malloc(void **p, size_t bytes);
 
 // Returns a block of dev_alloc (NULL is a no-op).  Waits for all work on the
 // block's device first, as hipFree does, so that no kernel uses a block that

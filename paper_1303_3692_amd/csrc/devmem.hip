@@ -126,6 +126,15 @@ Keeper &keeper() {
 
 }  // namespace
 
+hipError_t dev_malloc(void **p, size_t bytes) {
+    hipError_t e = hipMalloc(p, bytes);
+    int device = 0;
+    if (e != hipErrorOutOfMemory || hipGetDevice(&device) != hipSuccess) return e;
+    (void)hipGetLastError();
+    dev_trim(device);  // (and waits for what its thread is just giving back)
+    return hipMalloc(p, bytes);
+}
+
 hipError_t dev_alloc(void **p, size_t bytes) {
     *p = nullptr;
     bytes = (bytes + 255) & ~(size_t)255;
@@ -156,13 +165,7 @@ hipError_t dev_alloc(void **p, size_t bytes) {
             return hipSuccess;
         }
     }
-    e = hipMalloc(p, bytes);
-    if (e != hipSuccess && dev_kept(device) > 0) {
-        (void)hipGetLastError();
-        dev_trim(device);
-        e = hipMalloc(p, bytes);
-    }
-    if (e != hipSuccess) return e;
+    if ((e = dev_malloc(p, bytes)) != hipSuccess) return e;
     try {
         std::lock_guard<std::mutex> lk(k.mu);
         k.kept.reserve(k.blocks + 1);

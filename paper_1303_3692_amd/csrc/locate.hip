@@ -23,6 +23,7 @@
 #include <thread>
 
 #include "device_state.h"
+#include "devmem.h"
 
 namespace samatch {
 
@@ -50,7 +51,7 @@ int LocateScratch::reserve(int64_t ntiles) {
         dev = nullptr;
         cap = 0;
         const int64_t c = std::max<int64_t>(ntiles, 256), zero[kLocTail] = {};
-        if ((e = hipMalloc((void **)&dev, sizeof(int64_t) * (size_t)(c + kLocTail))) != hipSuccess ||
+        if ((e = dev_malloc((void **)&dev, sizeof(int64_t) * (size_t)(c + kLocTail))) != hipSuccess ||
             (e = hipMemcpy(dev + c, zero, sizeof zero, hipMemcpyHostToDevice)) != hipSuccess)
             return hip_fail(e, "locate scratch");
         cap = c;
@@ -300,8 +301,8 @@ extern "C" int sa_locate(const sa_dindex *d, const sa_hit *hits, int64_t nreads,
     } b;
     hipError_t e;
     if ((e = hipStreamCreateWithFlags(&b.s, hipStreamNonBlocking)) != hipSuccess ||
-        (e = hipMalloc((void **)&b.hits, sizeof(sa_hit) * (size_t)(nreads > 0 ? nreads : 1))) != hipSuccess ||
-        (e = hipMalloc((void **)&b.offs, sizeof(int64_t) * (size_t)(nreads + 1))) != hipSuccess)
+        (e = dev_malloc((void **)&b.hits, sizeof(sa_hit) * (size_t)(nreads > 0 ? nreads : 1))) != hipSuccess ||
+        (e = dev_malloc((void **)&b.offs, sizeof(int64_t) * (size_t)(nreads + 1))) != hipSuccess)
         return hip_fail(e, "locate buffers");
     if (nreads > 0 &&
         (e = hipMemcpyAsync(b.hits, hits, sizeof(sa_hit) * (size_t)nreads, hipMemcpyHostToDevice, b.s)) != hipSuccess)
@@ -315,7 +316,7 @@ extern "C" int sa_locate(const sa_dindex *d, const sa_hit *hits, int64_t nreads,
         return hip_fail(e, "locate download");
     if (*total == 0) return SA_OK;
     if (*total > pos_capacity) return fail(SA_ENOSPC, "positions buffer too small (see *total)");
-    if ((e = hipMalloc((void **)&b.pos, sizeof(int32_t) * (size_t)*total)) != hipSuccess)
+    if ((e = dev_malloc((void **)&b.pos, sizeof(int32_t) * (size_t)*total)) != hipSuccess)
         return hip_fail(e, "locate buffers");
     rc = locate_on(d, b.scratch, b.hits, nreads, cap, min_len, b.offs, b.pos, *total, b.s, total);
     if (rc) return rc;

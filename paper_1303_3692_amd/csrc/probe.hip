@@ -6,6 +6,7 @@
 #include <algorithm>
 
 #include "device_state.h"
+#include "devmem.h"
 #include "internal.h"
 #include "samatch_measure.h"
 
@@ -70,8 +71,8 @@ extern "C" int sa_random_read_rate(int device, int log2_entries, double *loads_p
     hipEvent_t a = nullptr, b = nullptr;
     int rc = SA_OK;
     float best = 1e30f;
-    if ((e = hipMalloc((void **)&tab, sizeof(uint4) * (size_t)n)) != hipSuccess ||
-        (e = hipMalloc((void **)&out, sizeof(uint32_t) * (size_t)blocks * kBlock)) != hipSuccess ||
+    if ((e = dev_malloc((void **)&tab, sizeof(uint4) * (size_t)n)) != hipSuccess ||
+        (e = dev_malloc((void **)&out, sizeof(uint32_t) * (size_t)blocks * kBlock)) != hipSuccess ||
         (e = hipEventCreate(&a)) != hipSuccess || (e = hipEventCreate(&b)) != hipSuccess) {
         rc = hip_fail(e, "random-read probe set-up");
         goto done;

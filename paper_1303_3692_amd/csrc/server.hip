@@ -734,7 +734,7 @@ extern "C" int sa_server_create(const sa_dindex *const *refs, int nrefs, const s
             const int64_t budget = free_hbm - o.hbm_reserve_bytes - per_slot * o.nstreams;
             if (budget < (1 << 20)) return fail(SA_ENOSPC, "not enough free device memory for the server");
             const int64_t arena_bytes = std::min<int64_t>(budget, (int64_t)16 << 30);
-            if ((e = hipMalloc((void **)&s->d_arena, (size_t)arena_bytes)) != hipSuccess)
+            if ((e = dev_malloc((void **)&s->d_arena, (size_t)arena_bytes)) != hipSuccess)
                 return hip_fail(e, "arena allocation");
             s->arena.init(arena_bytes);
             if (o.host_pool_bytes > 0) {
@@ -755,11 +755,11 @@ extern "C" int sa_server_create(const sa_dindex *const *refs, int nrefs, const s
                     (e = hipEventCreateWithFlags(&sl.done, hipEventDisableTiming)) != hipSuccess ||
                     (e = hipHostMalloc((void **)&sl.h_pieces, sizeof(PieceDev) * kMaxPieces, hipHostMallocDefault)) !=
                         hipSuccess ||
-                    (e = hipMalloc((void **)&sl.d_pieces, sizeof(PieceDev) * kMaxPieces)) != hipSuccess ||
+                    (e = dev_malloc((void **)&sl.d_pieces, sizeof(PieceDev) * kMaxPieces)) != hipSuccess ||
                     (e = hipHostMalloc((void **)&sl.h_out, sizeof(sa_hit) * (size_t)o.max_batch_reads,
                                        hipHostMallocDefault)) != hipSuccess ||
-                    (e = hipMalloc((void **)&sl.d_se, sizeof(int64_t) * 2 * (size_t)o.max_batch_reads)) != hipSuccess ||
-                    (e = hipMalloc((void **)&sl.d_out, sizeof(sa_hit) * (size_t)o.max_batch_reads)) != hipSuccess)
+                    (e = dev_malloc((void **)&sl.d_se, sizeof(int64_t) * 2 * (size_t)o.max_batch_reads)) != hipSuccess ||
+                    (e = dev_malloc((void **)&sl.d_out, sizeof(sa_hit) * (size_t)o.max_batch_reads)) != hipSuccess)
                     return hip_fail(e, "slot allocation");
                 // every index's scratch for this stream now, not on the first batch (the
                 // tuned search takes its batches in input order and needs no packed arrays)

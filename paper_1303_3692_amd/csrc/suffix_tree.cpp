@@ -173,6 +173,7 @@ extern "C" int st_copy_nodes(const st_index *t, int32_t *out) {
 // ------------------------------------------------------------------ device
 
 #include "device_state.h"
+#include "devmem.h"
 
 struct st_dindex {
     const sa_dindex *d = nullptr;  // text and suffix array (not owned)
@@ -200,7 +201,7 @@ extern "C" int st_upload(const st_index *t, const sa_dindex *d, st_dindex **out)
     s->nnodes = (int64_t)t->nodes.size();
     const size_t bytes = sizeof(StNode) * t->nodes.size();
     hipError_t e;
-    if ((e = hipMalloc((void **)&s->d_nodes, bytes)) != hipSuccess) return hip_fail(e, "suffix tree allocation");
+    if ((e = dev_malloc((void **)&s->d_nodes, bytes)) != hipSuccess) return hip_fail(e, "suffix tree allocation");
     if ((e = hipMemcpy(s->d_nodes, t->nodes.data(), bytes, hipMemcpyHostToDevice)) != hipSuccess)
         return hip_fail(e, "suffix tree upload");
     *out = s.release();

@@ -12,6 +12,7 @@
 #include <vector>
 
 #include "device_state.h"
+#include "devmem.h"
 
 using namespace samatch;
 
@@ -331,9 +332,9 @@ extern "C" int sa_tune(sa_dindex *d, const uint8_t *d_reads, const int64_t *d_of
     // be a defect, and the tuner fails instead of keeping it
     sa_hit *d_out = nullptr, *d_ref = nullptr;
     unsigned long long *d_diff = nullptr;
-    hipError_t e = hipMalloc((void **)&d_out, sizeof(sa_hit) * (size_t)nreads);
-    if (e == hipSuccess) e = hipMalloc((void **)&d_ref, sizeof(sa_hit) * (size_t)nreads);
-    if (e == hipSuccess) e = hipMalloc((void **)&d_diff, sizeof(unsigned long long));
+    hipError_t e = dev_malloc((void **)&d_out, sizeof(sa_hit) * (size_t)nreads);
+    if (e == hipSuccess) e = dev_malloc((void **)&d_ref, sizeof(sa_hit) * (size_t)nreads);
+    if (e == hipSuccess) e = dev_malloc((void **)&d_diff, sizeof(unsigned long long));
     if (e != hipSuccess) {
         (void)hipFree(d_out);
         (void)hipFree(d_ref);

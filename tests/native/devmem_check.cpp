@@ -3,6 +3,7 @@
 // that counts its memory and can refuse.
 #include <hip/hip_runtime.h>
 
+#include <atomic>
 #include <chrono>
 #include <cstdio>
 #include <cstdlib>
@@ -20,6 +21,7 @@ size_t device_bytes = (size_t)64 << 30, in_use = 0;
 std::map<void *, size_t> &blocks = *new std::map<void *, size_t>;
 int refuse_frees = 0;        // so many calls of hipFree fail
 int frees = 0;
+std::atomic<bool> slow_frees{false};     // hipFree takes a second before the memory is there
 bool capturing = false;      // a stream is captured in global mode, by another thread
 bool capture_valid = true;
 thread_local hipStreamCaptureMode thread_mode = hipStreamCaptureModeGlobal;
@@ -61,6 +63,7 @@ hipError_t hipMalloc(void **p, size_t bytes) {
     return hipSuccess;
 }
 hipError_t hipFree(void *p) {
+    if (slow_frees) std::this_thread::sleep_for(std::chrono::seconds(1));
     std::lock_guard<std::mutex> lk(mu);
     ++frees;
     if (refused_by_capture()) return hipErrorStreamCaptureUnsupported;
@@ -159,6 +162,24 @@ int main(int argc, char **argv) {
         std::lock_guard<std::mutex> lk(mu);
         expect(capture_valid, "the capture is still valid");
         capturing = false;
+    } else if (!std::strcmp(what, "pressure")) {  // kept memory is there for every allocation of the library
+        void *p = block(7 * GiB), *rest = nullptr, *q = nullptr;
+        dev_free(p);
+        expect(dev_malloc(&rest, 60 * GiB) == hipSuccess && dev_kept(0) == 0, "dev_malloc takes what is kept");
+        expect(dev_malloc(&q, 5 * GiB) == hipErrorOutOfMemory, "and fails when there is no more");
+        p = block(3 * GiB);
+        dev_free(p);
+        p = block(4 * GiB);
+        expect(dev_kept(0) == 0, "so does dev_alloc");
+        dev_free(p);
+        // the keeper's thread is giving a block back while another is asked for
+        std::this_thread::sleep_for(std::chrono::milliseconds(1000 * kKeepSeconds - 100));
+        {
+            std::lock_guard<std::mutex> lk(mu);
+            slow_frees = true;
+        }
+        std::this_thread::sleep_for(std::chrono::milliseconds(400));
+        expect(dev_malloc(&q, 4 * GiB) == hipSuccess, "waits for what is being given back");
     } else if (!std::strcmp(what, "exit")) {  // the process ends with blocks kept, while threads free more
         std::thread([] {
             for (;;) {

@@ -22,7 +22,17 @@ def program(tmp_path_factory):
     return exe
 
 
-@pytest.mark.parametrize("what", ["kept", "limit", "refused", "capture", "exit"])
+@pytest.mark.parametrize("what", ["kept", "limit", "refused", "capture", "pressure", "exit"])
 def test_keeper(program, what):
     r = subprocess.run([str(program), what], capture_output=True, text=True, timeout=60)
     assert r.returncode == 0 and "ok" in r.stdout and "FAIL" not in r.stdout, r.stdout + r.stderr
+
+
+def test_every_allocation_can_use_kept_memory():
+    """Nothing but the keeper calls hipMalloc: an allocation past it would fail
+    while memory of a freed index is kept."""
+    import re
+
+    csrc = os.path.join(ROOT, "paper_1303_3692_amd", "csrc")
+    calls = [f for f in sorted(os.listdir(csrc)) if re.search(r"\bhipMalloc(Async|Managed|Pitch)?\(", open(os.path.join(csrc, f)).read())]
+    assert calls == ["devmem.hip"]
