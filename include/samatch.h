@@ -111,6 +111,14 @@ void sa_free(sa_index *ix);                           /* NULL is a no-op        
  * from whatever their settings.  The host index may be freed afterwards.  Released with sa_dfree (NULL is a no-op). */
 int sa_upload(const sa_index *ix, int device, sa_dindex **out);
 void sa_dfree(sa_dindex *d);
+
+/* The memory of a freed index is kept for the next one for up to 2 s: at most
+ * 8 GiB a device, and no more than 512 MiB or a quarter of what is free there
+ * besides.  Allocations of this library give it back when they need it; other
+ * allocators of the process, and other processes, see that much less free
+ * memory meanwhile.  This gives it back now (*bytes, when not NULL: how much
+ * that was). */
+int sa_trim(int device, int64_t *bytes);
 int64_t sa_dindex_length(const sa_dindex *d);
 
 /* Resident index of text[0..n) with its suffix array built on the device
@@ -119,7 +127,8 @@ int64_t sa_dindex_length(const sa_dindex *d);
  * same array sa_build gives and the same resident index sa_upload makes
  * from it.  Same validation and errors as sa_build; SA_EDEVICE /
  * SA_ENOMEM when the device fails or runs out of memory (scratch about
- * 29 bytes per base during construction, freed before returning).  The text
+ * 36.5 bytes per base during construction, in the prefix table's memory where
+ * that is enough, freed before returning).  The text
  * buffer is the caller's and is not kept. */
 int sa_build_device(const char *text, int64_t n, int device, sa_dindex **out);
 

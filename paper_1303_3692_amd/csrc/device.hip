@@ -372,7 +372,7 @@ int set_prefix_table(sa_dindex *d, int k) {
     hipError_t e;
     if (d->d_ptab) {
         if ((e = hipDeviceSynchronize()) != hipSuccess) return hip_fail(e, "prefix table release");
-        dev_free(d->d_ptab);
+        dev_free({d->d_ptab});
         d->d_ptab = nullptr;
     }
     d->view.ptab = nullptr;
@@ -596,12 +596,21 @@ extern "C" int sa_dindex_build_info(const sa_dindex *d, int *steps, int64_t *sor
 sa_dindex::~sa_dindex() {
     DeviceGuard g(device);
     ws.clear();
-    for (void *p : {(void *)d_text, (void *)d_sa, (void *)d_tile_key, (void *)d_tile_sa, (void *)d_rows,
-                    (void *)d_ptab, (void *)d_short})
-        dev_free(p);
+    dev_free({d_text, d_sa, d_tile_key, d_tile_sa, d_rows, d_ptab, d_short});
 }
 
 extern "C" void sa_dfree(sa_dindex *d) { delete d; }
+
+extern "C" int sa_trim(int device, int64_t *bytes) {
+    clear_error();
+    int ndev = 0;
+    const hipError_t e = hipGetDeviceCount(&ndev);
+    if (e != hipSuccess) return hip_fail(e, "hipGetDeviceCount");
+    if (device < 0 || device >= ndev) return fail(SA_EINVAL, "no such device");
+    const size_t given = dev_trim(device);
+    if (bytes) *bytes = (int64_t)given;
+    return SA_OK;
+}
 
 extern "C" int64_t sa_dindex_length(const sa_dindex *d) { return d ? d->n : -1; }
 

@@ -23,7 +23,11 @@ struct Block {
     size_t bytes;
     int device;
     Clock::time_point since;  // when it was kept, or last refused by hipFree
-    bool idle;                // no kernel uses it: it may be handed out again
+    enum State {
+        idle,     // may be handed out again
+        leaving,  // its caller waits for the kernels that may use it
+        refused,  // not known to be idle
+    } state;
 };
 
 // Makes a device current for the scope.
@@ -44,6 +48,7 @@ struct Keeper {
     std::unordered_map<void *, Block> used;  // blocks handed out
     std::vector<Block> kept;                 // has room for every block there is, so that keeping one allocates nothing
     size_t blocks = 0;                       // there are: handed out, kept, or on their way
+    size_t unasked = 0;                      // bytes kept since the device was last asked what is free
     std::thread watch;  // gives back what is not used again; ends when nothing is kept
     bool watching = false, closing = false;
 
@@ -65,7 +70,7 @@ struct Keeper {
     template <class F>
     void release(F which) {
         for (size_t i = 0; i < kept.size();) {
-            if (!which(kept[i])) {
+            if (kept[i].state == Block::leaving || !which(kept[i])) {
                 ++i;
                 continue;
             }
@@ -95,13 +100,7 @@ struct Keeper {
         (void)hipThreadExchangeStreamCaptureMode(&mode);
         std::unique_lock<std::mutex> lk(mu);
         while (!closing && !kept.empty()) {
-            Clock::time_point oldest = kept[0].since;
-            for (const Block &b : kept) oldest = std::min(oldest, b.since);
-            const Clock::time_point due = oldest + std::chrono::seconds(kKeepSeconds);
-            if (Clock::now() < due) {
-                cv.wait_until(lk, due);
-                continue;
-            }
+            cv.wait_for(lk, std::chrono::milliseconds(250));
             const Clock::time_point before = Clock::now() - std::chrono::seconds(kKeepSeconds);
             release([&](const Block &b) { return b.since <= before; });
         }
@@ -124,6 +123,16 @@ Keeper &keeper() {
     return *k;
 }
 
+// Bytes that may stay kept on the current device, of which `more` are new.
+size_t keep_limit(Keeper &k, size_t more) {
+    k.unasked += more;
+    if (k.unasked <= kKeepFreely) return kKeepBytes;
+    k.unasked = 0;
+    size_t free_bytes = 0, total = 0;
+    if (hipMemGetInfo(&free_bytes, &total) != hipSuccess) return 0;
+    return std::min(kKeepBytes, free_bytes / 4);
+}
+
 }  // namespace
 
 hipError_t dev_malloc(void **p, size_t bytes) {
@@ -131,7 +140,7 @@ hipError_t dev_malloc(void **p, size_t bytes) {
     int device = 0;
     if (e != hipErrorOutOfMemory || hipGetDevice(&device) != hipSuccess) return e;
     (void)hipGetLastError();
-    dev_trim(device);  // (and waits for what its thread is just giving back)
+    (void)dev_trim(device);  // (and waits for what its thread is just giving back)
     return hipMalloc(p, bytes);
 }
 
@@ -149,7 +158,7 @@ hipError_t dev_alloc(void **p, size_t bytes) {
         size_t best = k.kept.size();
         for (size_t i = 0; i < k.kept.size(); i++) {
             const Block &b = k.kept[i];
-            if (b.device == device && b.idle && b.bytes >= bytes && b.bytes - bytes <= bytes / 8 &&
+            if (b.device == device && b.state == Block::idle && b.bytes >= bytes && b.bytes - bytes <= bytes / 8 &&
                 (best == k.kept.size() || b.bytes < k.kept[best].bytes))
                 best = i;
         }
@@ -169,7 +178,7 @@ hipError_t dev_alloc(void **p, size_t bytes) {
     try {
         std::lock_guard<std::mutex> lk(k.mu);
         k.kept.reserve(k.blocks + 1);
-        k.used.emplace(*p, Block{*p, bytes, device, Clock::time_point(), true});
+        k.used.emplace(*p, Block{*p, bytes, device, Clock::time_point(), Block::idle});
         ++k.blocks;
     } catch (const std::bad_alloc &) {
         (void)hipFree(*p);
@@ -179,46 +188,52 @@ hipError_t dev_alloc(void **p, size_t bytes) {
     return hipSuccess;
 }
 
-void dev_free(void *p) {
-    if (!p) return;
+void dev_free(std::initializer_list<void *> ps) {
     Keeper &k = keeper();
-    Block b;
-    bool closing;
+    int device = -1;
     {
         std::lock_guard<std::mutex> lk(k.mu);
-        closing = k.closing;
-        auto it = k.used.find(p);
-        if (it == k.used.end()) return;
-        b = it->second;
-        k.used.erase(it);  // before hipFree, after which another thread may be given the same address
-    }
-    Current c(b.device);
-    b.idle = hipDeviceSynchronize() == hipSuccess;
-    if (!b.idle || closing || b.bytes > kKeepBytes) {
-        if (hipFree(p) == hipSuccess) {
-            std::lock_guard<std::mutex> lk(k.mu);
-            --k.blocks;
-            return;
+        for (void *p : ps) {
+            auto it = k.used.find(p);
+            if (it == k.used.end()) continue;
+            Block b = it->second;
+            k.used.erase(it);
+            b.state = Block::leaving;
+            k.kept.push_back(b);
+            device = b.device;
         }
-        (void)hipGetLastError();  // kept, and tried again
     }
+    if (device < 0) return;
+    Current c(device);
+    const bool idle = hipDeviceSynchronize() == hipSuccess;
     std::lock_guard<std::mutex> lk(k.mu);
-    // the oldest ones go when there is no room for this one
-    size_t held = k.held(b.device) + b.bytes;
-    k.release([&](const Block &x) {
-        if (x.device != b.device || held <= kKeepBytes) return false;
-        held -= x.bytes;
-        return true;
-    });
-    b.since = Clock::now();
-    k.kept.push_back(b);
-    if (k.watching || k.closing) return;
+    size_t bytes = 0;
+    for (Block &b : k.kept)
+        if (std::find(ps.begin(), ps.end(), b.p) != ps.end()) {
+            b.state = idle ? Block::idle : Block::refused;
+            b.since = Clock::now();
+            bytes += b.bytes;
+        }
+    const size_t limit = k.closing || !idle ? 0 : keep_limit(k, bytes);
+    // those that have no room by themselves go, then the oldest until the rest have
+    // (refused, they stay and are tried again)
+    k.release([&](const Block &b) { return b.bytes > limit && std::find(ps.begin(), ps.end(), b.p) != ps.end(); });
+    if (limit) {
+        size_t over = k.held(device);
+        over = over > limit ? over - limit : 0;
+        k.release([&](const Block &b) {
+            if (b.device != device || over == 0) return false;
+            over -= std::min(over, b.bytes);
+            return true;
+        });
+    }
+    if (k.watching || k.closing || k.kept.empty()) return;
     if (k.watch.joinable()) k.watch.join();  // it has ended, or ends without the lock
     try {
         k.watch = std::thread([&k] { k.run(); });
         k.watching = true;
     } catch (const std::system_error &) {
-        k.release([&](const Block &x) { return x.p == p; });  // nobody would give it back
+        k.release([&](const Block &b) { return b.device == device; });  // nobody would give them back
     }
 }
 
@@ -228,10 +243,12 @@ size_t dev_kept(int device) {
     return k.held(device);
 }
 
-void dev_trim(int device) {
+size_t dev_trim(int device) {
     Keeper &k = keeper();
     std::lock_guard<std::mutex> lk(k.mu);
+    const size_t before = k.held(device);
     k.release([&](const Block &b) { return b.device == device; });
+    return before - k.held(device);
 }
 
 }  // namespace samatch

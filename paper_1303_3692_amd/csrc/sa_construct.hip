@@ -384,7 +384,7 @@ int build_sa_device(const uint64_t *d_text, int64_t n, int32_t *d_sa, uint32_t *
         info->steps = steps;
         info->sorted_elems += n;
     }
-    dev_free(own);
+    dev_free({own});
     if (kept_h) (void)hipHostFree(kept_h);
     return rc;
 }

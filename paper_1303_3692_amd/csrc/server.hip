@@ -725,7 +725,7 @@ extern "C" int sa_server_create(const sa_dindex *const *refs, int nrefs, const s
             DeviceGuard g(s->device);
             if (!g.ok) return fail(SA_EDEVICE, "hipSetDevice failed");
             size_t free_b = 0, total_b = 0;
-            dev_trim(s->device);
+            (void)dev_trim(s->device);
             hipError_t e = hipMemGetInfo(&free_b, &total_b);
             if (e != hipSuccess) return hip_fail(e, "hipMemGetInfo");
             const int64_t free_hbm = o.test_fake_free_hbm >= 0 ? o.test_fake_free_hbm : (int64_t)free_b;

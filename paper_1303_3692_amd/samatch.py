@@ -25,7 +25,7 @@ SA_KERNEL_TUNED, SA_KERNEL_PLAIN = 0, 1
 # every extern "C" symbol the header declares
 EXPORTS = [
     "sa_build", "sa_build_from_sa", "sa_index_length", "sa_index_copy_sa", "sa_save", "sa_load", "sa_free",
-    "sa_upload", "sa_dfree", "sa_dindex_length", "sa_build_device", "sa_download", "sa_dindex_build_info",
+    "sa_upload", "sa_dfree", "sa_trim", "sa_dindex_length", "sa_build_device", "sa_download", "sa_dindex_build_info",
     "sa_dindex_bytes", "sa_set_prefix_table",
     "sa_default_cfg", "match_batch", "match_batch_dev", "match_batch_dev_noalloc", "sa_noalloc_max_reads",
     "sa_stage_times", "sa_probe_counts", "sa_tune", "sa_tune_candidates", "sa_random_read_rate",
@@ -99,6 +99,7 @@ def lib():
             "sa_free": ([p], None),
             "sa_upload": ([p, i32, pp], i32),
             "sa_dfree": ([p], None),
+            "sa_trim": ([i32, ctypes.POINTER(ctypes.c_int64)], i32),
             "sa_dindex_length": ([p], i64),
             "sa_build_device": ([p, i64, i32, pp], i32),
             "sa_download": ([p, pp], i32),
@@ -284,6 +285,13 @@ def sa_build_device(text, device: int = 0) -> DIndex:
     _check(lib().sa_build_device(buf.ctypes.data if len(buf) else None, len(buf), device, ctypes.byref(out)),
            "sa_build_device")
     return DIndex(out, device)
+
+
+def sa_trim(device: int = 0) -> int:
+    """Give back the memory kept of freed indexes; returns how many bytes that was."""
+    given = ctypes.c_int64()
+    _check(lib().sa_trim(device, ctypes.byref(given)), "sa_trim")
+    return given.value
 
 
 def sa_download(d: DIndex) -> Index:

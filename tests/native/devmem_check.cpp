@@ -114,22 +114,22 @@ int main(int argc, char **argv) {
     const size_t GiB = (size_t)1 << 30;
     if (!std::strcmp(what, "kept")) {  // used again, then given back
         void *p = block(GiB);
-        dev_free(p);
+        dev_free({p});
         expect(dev_kept(0) == GiB, "kept");
         expect(block(GiB) == p, "used again");
-        dev_free(p);
+        dev_free({p});
         expect(idle_within(kKeepSeconds + 2.0) && dev_kept(0) == 0, "given back");
     } else if (!std::strcmp(what, "limit")) {  // no more than kKeepBytes are kept, the oldest go first
         void *p[4];
         for (void *&x : p) x = block(3 * GiB);
-        for (void *x : p) dev_free(x);
+        for (void *x : p) dev_free({x});
         expect(dev_kept(0) == 6 * GiB && used() == 6 * GiB, "two of four blocks kept");
         expect(blocks.count(p[2]) && blocks.count(p[3]), "the last ones");
         dev_trim(0);
         expect(dev_kept(0) == 0 && used() == 0, "nothing after a trim");
     } else if (!std::strcmp(what, "refused")) {  // a block that hipFree refuses is not lost
         void *p = block(GiB);
-        dev_free(p);
+        dev_free({p});
         {
             std::lock_guard<std::mutex> lk(mu);
             refuse_frees = 1;
@@ -142,7 +142,7 @@ int main(int argc, char **argv) {
         expect(dev_kept(0) == GiB, "still kept");
         expect(idle_within(kKeepSeconds + 2.0) && dev_kept(0) == 0, "given back when tried again");
         p = block(GiB);
-        dev_free(p);
+        dev_free({p});
         {
             std::lock_guard<std::mutex> lk(mu);
             refuse_frees = 1;
@@ -153,7 +153,7 @@ int main(int argc, char **argv) {
         expect(used() == 0, "the next one gives it back");
     } else if (!std::strcmp(what, "capture")) {  // a capture of another thread goes on while kept blocks are given back
         void *p = block(GiB);
-        dev_free(p);
+        dev_free({p});
         {
             std::lock_guard<std::mutex> lk(mu);
             capturing = true;
@@ -164,27 +164,40 @@ int main(int argc, char **argv) {
         capturing = false;
     } else if (!std::strcmp(what, "pressure")) {  // kept memory is there for every allocation of the library
         void *p = block(7 * GiB), *rest = nullptr, *q = nullptr;
-        dev_free(p);
+        dev_free({p});
         expect(dev_malloc(&rest, 60 * GiB) == hipSuccess && dev_kept(0) == 0, "dev_malloc takes what is kept");
         expect(dev_malloc(&q, 5 * GiB) == hipErrorOutOfMemory, "and fails when there is no more");
-        p = block(3 * GiB);
-        dev_free(p);
-        p = block(4 * GiB);
+        expect(hipFree(rest) == hipSuccess, "release");
+        dev_free({block(3 * GiB)});
+        p = block(62 * GiB);
         expect(dev_kept(0) == 0, "so does dev_alloc");
-        dev_free(p);
+        dev_free({p});
+        expect(used() == 0, "a block of more than kKeepBytes is not kept");
         // the keeper's thread is giving a block back while another is asked for
+        dev_free({block(4 * GiB)});
         std::this_thread::sleep_for(std::chrono::milliseconds(1000 * kKeepSeconds - 100));
-        {
-            std::lock_guard<std::mutex> lk(mu);
-            slow_frees = true;
-        }
+        slow_frees = true;
         std::this_thread::sleep_for(std::chrono::milliseconds(400));
-        expect(dev_malloc(&q, 4 * GiB) == hipSuccess, "waits for what is being given back");
+        expect(dev_malloc(&q, 62 * GiB) == hipSuccess, "waits for what is being given back");
+    } else if (!std::strcmp(what, "full")) {  // little of a nearly full device is kept
+        void *rest = nullptr;
+        expect(dev_malloc(&rest, 60 * GiB) == hipSuccess, "allocation");
+        void *small = block(kKeepFreely / 2), *large = block(2 * GiB), *fits = block(GiB * 3 / 8);
+        dev_free({small});
+        expect(dev_kept(0) == kKeepFreely / 2, "a small block is kept");
+        dev_free({large});
+        expect(dev_kept(0) == kKeepFreely / 2, "one of more than a quarter of the free memory is not");
+        dev_free({fits});
+        expect(dev_kept(0) == kKeepFreely / 2 + GiB * 3 / 8, "one of less is");
+        expect(dev_trim(0) == kKeepFreely / 2 + GiB * 3 / 8 && dev_kept(0) == 0, "a trim says what it gave back");
+        small = block(kKeepFreely / 2), large = block(2 * GiB);
+        dev_free({small, nullptr, large});
+        expect(dev_kept(0) == kKeepFreely / 2, "of several blocks those that fit are kept");
     } else if (!std::strcmp(what, "exit")) {  // the process ends with blocks kept, while threads free more
         std::thread([] {
             for (;;) {
                 void *p = nullptr;
-                if (dev_alloc(&p, (size_t)1 << 20) == hipSuccess) dev_free(p);
+                if (dev_alloc(&p, (size_t)1 << 20) == hipSuccess) dev_free({p});
             }
         }).detach();
         std::this_thread::sleep_for(std::chrono::milliseconds(100));

@@ -22,7 +22,7 @@ def program(tmp_path_factory):
     return exe
 
 
-@pytest.mark.parametrize("what", ["kept", "limit", "refused", "capture", "pressure", "exit"])
+@pytest.mark.parametrize("what", ["kept", "limit", "refused", "capture", "pressure", "full", "exit"])
 def test_keeper(program, what):
     r = subprocess.run([str(program), what], capture_output=True, text=True, timeout=60)
     assert r.returncode == 0 and "ok" in r.stdout and "FAIL" not in r.stdout, r.stdout + r.stderr

@@ -40,3 +40,20 @@ def test_capture_while_kept_memory_is_given_back():
         assert (y == i + 1).all()
     # the table alone took 4^12 entries of 16 bytes
     assert torch.cuda.mem_get_info()[0] - before >= 16 << 24
+
+
+def test_trim():
+    """Kept memory is given back at once when that is asked for."""
+    text = np.random.default_rng(1).choice(np.frombuffer(b"ACGT", dtype=np.uint8), 1_000_000)
+    S.sa_trim()
+    index = S.sa_build_device(text, 0)
+    size = sum(index.index_bytes().values())
+    torch.cuda.synchronize()
+    before = torch.cuda.mem_get_info()[0]
+    index.free()
+    given = S.sa_trim()
+    assert size <= given <= size + 8 * 256 and S.sa_trim() == 0
+    assert torch.cuda.mem_get_info()[0] - before >= 16 << 24
+    with pytest.raises(S.SaError) as e:
+        S.sa_trim(-1)
+    assert e.value.code == S.SA_EINVAL
