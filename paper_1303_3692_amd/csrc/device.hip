@@ -449,20 +449,26 @@ int make_dindex(int device, int64_t n, const uint64_t *packed, const int32_t *ho
     } else if ((e = hipMemcpy(d->d_text, packed, text_bytes, hipMemcpyHostToDevice)) != hipSuccess) {
         return hip_fail(e, "index upload");
     }
-    // the table's memory, in which the suffixes are sorted before the table is filled
+    // the table's memory, in which the suffixes are sorted before the table is
+    // filled; a table that is too small for that, because memory is short, waits
+    // until the sort has given its own memory back
     size_t free_bytes = 0, total_bytes = 0;
     if ((e = hipMemGetInfo(&free_bytes, &total_bytes)) != hipSuccess) return hip_fail(e, "device memory query");
     const int k = default_prefix_bases(n, free_bytes + dev_kept(device));
-    if (k > 0 && (e = dev_alloc((void **)&d->d_ptab, table_bytes(k))) != hipSuccess)
+    auto take_table = [&] {
+        return k > 0 && !d->d_ptab ? dev_alloc((void **)&d->d_ptab, table_bytes(k)) : hipSuccess;
+    };
+    if (k > 0 && table_bytes(k) >= sa_sort_bytes(n) && (e = take_table()) != hipSuccess)
         return hip_fail(e, "prefix table allocation");
     if (host_sa) {
         if ((e = hipMemcpy(d->d_sa, host_sa, sa_bytes, hipMemcpyHostToDevice)) != hipSuccess)
             return hip_fail(e, "index upload");
     } else {
-        int rc = build_sa_device(d->d_text, n, d->d_sa, nullptr, d->d_ptab, k > 0 ? table_bytes(k) : 0, nullptr,
+        int rc = build_sa_device(d->d_text, n, d->d_sa, nullptr, d->d_ptab, d->d_ptab ? table_bytes(k) : 0, nullptr,
                                  &d->built);
         if (rc) return rc;
     }
+    if ((e = take_table()) != hipSuccess) return hip_fail(e, "prefix table allocation");
     if ((e = launch_build_rows(d->d_text, d->d_sa, (int32_t)n, d->d_rows, nullptr)) != hipSuccess ||
         (e = launch_build_tile(d->d_text, d->d_sa, (int32_t)n, d->tile_levels, d->d_tile_key, d->d_tile_sa,
                                nullptr)) != hipSuccess ||

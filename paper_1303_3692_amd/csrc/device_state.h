@@ -119,6 +119,8 @@ struct SaBuildInfo {
     int steps = 0;             // sorting rounds: the first bases, then each doubling
     int64_t sorted_elems = 0;  // (key, value) pairs sorted over all rounds
 };
+// Device memory that a text of n bases is sorted in: about 36.5 bytes a base.
+size_t sa_sort_bytes(int64_t n);
 int build_sa_device(const uint64_t *d_text, int64_t n, int32_t *d_sa, uint32_t *rank_out, void *scratch,
                     size_t scratch_bytes, hipStream_t s, SaBuildInfo *info);
 

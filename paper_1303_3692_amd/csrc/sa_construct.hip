@@ -263,21 +263,48 @@ __global__ __launch_bounds__(kScanBlock) void sa_flags_apply_kernel(
     }
 }
 
+// The arrays that a text of n bases is sorted in, from `base` on.
+struct SortArrays {
+    uint64_t *key[2];
+    uint32_t *val[2], *row[2], *rank, *hist, *digit_total, *tmax, *tsum, *kept;
+    size_t bytes;  // of all of them
+};
+
+SortArrays lay_out(int64_t n, char *base) {
+    const size_t tiles_scan = ((size_t)n + kScanTile - 1) / kScanTile;
+    SortArrays w{};
+    auto take = [&](size_t bytes) {
+        char *p = base ? base + w.bytes : nullptr;
+        w.bytes += (bytes + 255) & ~(size_t)255;
+        return (void *)p;
+    };
+    for (int k = 0; k < 2; ++k) {
+        w.key[k] = (uint64_t *)take(sizeof(uint64_t) * (size_t)n);
+        w.val[k] = (uint32_t *)take(sizeof(uint32_t) * (size_t)n);
+        w.row[k] = (uint32_t *)take(sizeof(uint32_t) * (size_t)n);
+    }
+    w.rank = (uint32_t *)take(sizeof(uint32_t) * (size_t)n);
+    w.hist = (uint32_t *)take(sizeof(uint32_t) * sort_hist_words<uint64_t>(n));
+    w.digit_total = (uint32_t *)take(sizeof(uint32_t) * 256);
+    w.tmax = (uint32_t *)take(sizeof(uint32_t) * tiles_scan);
+    w.tsum = (uint32_t *)take(sizeof(uint32_t) * tiles_scan);
+    w.kept = (uint32_t *)take(sizeof(uint32_t));
+    return w;
+}
+
 }  // namespace
+
+size_t sa_sort_bytes(int64_t n) { return lay_out(n, nullptr).bytes; }
 
 // Builds sa[0..n) of the packed text d_text (with zero pad words after the
 // text) on stream s; rank_out (nullable, n entries) receives 1 + the row of
 // each text position.  Works in the device memory [scratch, scratch +
-// scratch_bytes) when that is enough (about 29 bytes per base), else in
-// memory that it allocates and frees.
+// scratch_bytes) when that is enough (sa_sort_bytes), else in memory that it
+// allocates and frees.
 int build_sa_device(const uint64_t *d_text, int64_t n, int32_t *d_sa, uint32_t *rank_out, void *scratch,
                     size_t scratch_bytes, hipStream_t s, SaBuildInfo *info) {
     if (n < 1 || n > INT32_MAX) return fail(SA_EINVAL, "text length out of range for device construction");
-    const int64_t tiles_scan = (n + kScanTile - 1) / kScanTile;
-    uint64_t *key[2] = {nullptr, nullptr};
-    uint32_t *val[2] = {nullptr, nullptr}, *row[2] = {nullptr, nullptr};
-    uint32_t *rank = nullptr, *hist = nullptr, *digit_total = nullptr, *tmax = nullptr, *tsum = nullptr;
-    uint32_t *kept_d = nullptr, *kept_h = nullptr;
+    uint32_t *kept_h = nullptr;
     auto bits_of = [](int64_t most) {
         int bits = 1;
         while (((int64_t)1 << bits) <= most) bits++;
@@ -287,32 +314,15 @@ int build_sa_device(const uint64_t *d_text, int64_t n, int32_t *d_sa, uint32_t *
     hipError_t e = hipSuccess;
     // one block for all of it: each allocation and release is tens to hundreds
     // of microseconds, and there were fourteen (2 ms of 10 for 16 Mbp)
-    size_t used = 0;
-    char *base = nullptr;
-    auto take = [&](size_t bytes) {
-        char *p = base ? base + used : nullptr;
-        used += (bytes + 255) & ~(size_t)255;
-        return (void *)p;
-    };
-    auto lay_out = [&] {
-        used = 0;
-        for (int k = 0; k < 2; ++k) {
-            key[k] = (uint64_t *)take(sizeof(uint64_t) * (size_t)n);
-            val[k] = (uint32_t *)take(sizeof(uint32_t) * (size_t)n);
-            row[k] = (uint32_t *)take(sizeof(uint32_t) * (size_t)n);
-        }
-        rank = rank_out ? rank_out : (uint32_t *)take(sizeof(uint32_t) * (size_t)n);
-        hist = (uint32_t *)take(sizeof(uint32_t) * sort_hist_words<uint64_t>(n));
-        digit_total = (uint32_t *)take(sizeof(uint32_t) * 256);
-        tmax = (uint32_t *)take(sizeof(uint32_t) * (size_t)tiles_scan);
-        tsum = (uint32_t *)take(sizeof(uint32_t) * (size_t)tiles_scan);
-        kept_d = (uint32_t *)take(sizeof(uint32_t));
-    };
-    lay_out();
-    void *own = nullptr;
-    if (scratch && used <= scratch_bytes) base = (char *)scratch;
-    else if ((e = dev_alloc(&own, used)) == hipSuccess) base = (char *)own;
-    lay_out();
+    const size_t used = lay_out(n, nullptr).bytes;
+    void *own = nullptr, *base = nullptr;
+    if (scratch && used <= scratch_bytes) base = scratch;
+    else if ((e = dev_alloc(&own, used)) == hipSuccess) base = own;
+    const SortArrays w = lay_out(n, (char *)base);
+    uint64_t *const *key = w.key;
+    uint32_t *const *val = w.val, *const *row = w.row;
+    uint32_t *rank = rank_out ? rank_out : w.rank, *hist = w.hist, *digit_total = w.digit_total, *tmax = w.tmax,
+             *tsum = w.tsum, *kept_d = w.kept;
     if (e == hipSuccess) e = hipHostMalloc((void **)&kept_h, sizeof(uint32_t), hipHostMallocDefault);
     if (e != hipSuccess) rc = hip_fail(e, "suffix array scratch allocation");
 
