@@ -60,10 +60,13 @@ struct LocateTotal {
     uint64_t call;
 };
 
-// Scratch of sa_locate_dev, for calls that follow each other on one stream.
+// Scratch of sa_locate_dev, for calls that follow each other on one stream:
+// `mu` is held through a call, which waits for the device (and must not keep a
+// batch of another thread from being enqueued there meanwhile).
 struct LocateScratch {
     ~LocateScratch();
     int reserve(int64_t ntiles);
+    std::mutex mu;
     int64_t *dev = nullptr;      // tile sums, then two words
     int64_t cap = 0;             // tiles dev has room for
     LocateTotal *host = nullptr, *host_dev = nullptr;

@@ -229,7 +229,7 @@ int wait_total(LocateScratch &sc, uint64_t call, hipStream_t s) {
 
 }  // namespace
 
-// sa_locate_dev on the given scratch (whose calls are ordered by stream s).
+// sa_locate_dev on the given scratch, whose mutex is held.
 int locate_on(const sa_dindex *d, LocateScratch &sc, const sa_hit *d_hits, int64_t nreads, int32_t cap,
               int32_t min_len, int64_t *d_offs, int32_t *d_pos, int64_t pos_capacity, hipStream_t s, int64_t *total) {
     const int rounds = loc_rounds(nreads);
@@ -272,9 +272,9 @@ extern "C" int sa_locate_dev(const sa_dindex *d, const sa_hit *d_hits, int64_t n
     DeviceGuard g(d->device);
     if (!g.ok) return fail(SA_EDEVICE, "hipSetDevice failed");
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
-    Workspace *ws = workspace_for(const_cast<sa_dindex *>(d), s);
-    std::lock_guard<std::mutex> lk(ws->mu);
-    return locate_on(d, ws->locate, d_hits, nreads, cap, min_len, d_offs, d_pos, pos_capacity, s, total);
+    LocateScratch &sc = workspace_for(const_cast<sa_dindex *>(d), s)->locate;
+    std::lock_guard<std::mutex> lk(sc.mu);
+    return locate_on(d, sc, d_hits, nreads, cap, min_len, d_offs, d_pos, pos_capacity, s, total);
 }
 
 extern "C" int sa_locate(const sa_dindex *d, const sa_hit *hits, int64_t nreads, int32_t cap, int32_t min_len,
