@@ -60,7 +60,7 @@ struct LocateTotal {
     uint64_t call;
 };
 
-// Scratch of sa_locate_dev, for calls that follow each other on one stream:
+// Scratch of a locate, for calls that follow each other:
 // `mu` is held through a call, which waits for the device (and must not keep a
 // batch of another thread from being enqueued there meanwhile).
 struct LocateScratch {
@@ -145,6 +145,7 @@ struct sa_dindex {
     // of a text below kMinTableText bases: the table every search in input order starts from
     samatch::PrefixEntry *d_short = nullptr;
     int short_k = 0;
+    samatch::LocateScratch locate;  // of sa_locate
     int tile_levels = 0;  // levels stored (the kernel may use fewer)
     samatch::SaBuildInfo built{};  // when the suffix array was built on the device
     samatch::DevIndex view{};

@@ -285,12 +285,17 @@ extern "C" int sa_locate(const sa_dindex *d, const sa_hit *hits, int64_t nreads,
     if (pos_capacity > 0 && !pos) return fail(SA_EINVAL, "NULL positions buffer");
     DeviceGuard g(d->device);
     if (!g.ok) return fail(SA_EDEVICE, "hipSetDevice failed");
-    struct Buffers {
+    // the index's scratch, or one of its own while another thread's call has that
+    // (MI355X, one read, a call for the total and one for the list: 122 us, and
+    // 156 with a scratch per call, whose pinned memory has to be allocated)
+    LocateScratch own, &kept = const_cast<sa_dindex *>(d)->locate;
+    std::unique_lock<std::mutex> lk(kept.mu, std::try_to_lock);
+    LocateScratch &scratch = lk.owns_lock() ? kept : own;
+    struct Buffers {  // (released, and the stream waited for, before the scratch is)
         sa_hit *hits = nullptr;
         int64_t *offs = nullptr;
         int32_t *pos = nullptr;
         hipStream_t s = nullptr;
-        LocateScratch scratch;
         ~Buffers() {
             if (s) (void)hipStreamSynchronize(s);
             if (hits) (void)hipFree(hits);
@@ -308,7 +313,7 @@ extern "C" int sa_locate(const sa_dindex *d, const sa_hit *hits, int64_t nreads,
         (e = hipMemcpyAsync(b.hits, hits, sizeof(sa_hit) * (size_t)nreads, hipMemcpyHostToDevice, b.s)) != hipSuccess)
         return hip_fail(e, "locate upload");
     // counts and offsets first; positions only when they fit
-    int rc = locate_on(d, b.scratch, b.hits, nreads, cap, min_len, b.offs, nullptr, 0, b.s, total);
+    int rc = locate_on(d, scratch, b.hits, nreads, cap, min_len, b.offs, nullptr, 0, b.s, total);
     if (rc != SA_OK && rc != SA_ENOSPC) return rc;
     if ((e = hipMemcpyAsync(offs, b.offs, sizeof(int64_t) * (size_t)(nreads + 1), hipMemcpyDeviceToHost, b.s)) !=
             hipSuccess ||
@@ -318,7 +323,7 @@ extern "C" int sa_locate(const sa_dindex *d, const sa_hit *hits, int64_t nreads,
     if (*total > pos_capacity) return fail(SA_ENOSPC, "positions buffer too small (see *total)");
     if ((e = dev_malloc((void **)&b.pos, sizeof(int32_t) * (size_t)*total)) != hipSuccess)
         return hip_fail(e, "locate buffers");
-    rc = locate_on(d, b.scratch, b.hits, nreads, cap, min_len, b.offs, b.pos, *total, b.s, total);
+    rc = locate_on(d, scratch, b.hits, nreads, cap, min_len, b.offs, b.pos, *total, b.s, total);
     if (rc) return rc;
     if ((e = hipMemcpyAsync(pos, b.pos, sizeof(int32_t) * (size_t)*total, hipMemcpyDeviceToHost, b.s)) != hipSuccess ||
         (e = hipStreamSynchronize(b.s)) != hipSuccess)

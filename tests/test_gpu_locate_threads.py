@@ -52,3 +52,29 @@ def test_a_batch_is_enqueued_while_a_locate_waits(index):
     locating.join()
     torch.cuda.synchronize()
     assert total == [int(starts[-1])] and torch.equal(hits, again)
+
+
+def test_host_locates_of_several_threads(index):
+    """sa_locate of several threads at once, each with hits of its own."""
+    _, sa, d = index
+    wrong = []
+
+    def work(seed):
+        rng = np.random.default_rng(seed)
+        for _ in range(20):
+            count = int(rng.integers(1, 3000))
+            lo = rng.integers(0, len(sa) - 40, count)
+            rows = rng.integers(0, 40, count)
+            hits = np.stack([lo, lo + rows, rows, np.ones(count, int)], 1).astype(np.int32)
+            offs, pos = S.locate(d, hits, 16)
+            take = np.minimum(rows, 16)
+            want = [sa[a:a + t] for a, t in zip(lo, take)]
+            if not (np.array_equal(np.diff(offs), take) and np.array_equal(pos, np.concatenate(want))):
+                wrong.append(seed)
+
+    threads = [threading.Thread(target=work, args=(k,)) for k in range(4)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not wrong
