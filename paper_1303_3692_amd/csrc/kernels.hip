@@ -1786,10 +1786,11 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(COUNT ? 1 
             const int f = __ffsll((unsigned long long)todo) - 1;
             const uint8_t *A0 = reinterpret_cast<const uint8_t *>((uintptr_t)(reads + lane_value(a, f)) & ~(uintptr_t)15);
             // the run: lanes f, f + 1, ... while each read starts where the one before ends and still fits
+            // (empty ones among them take no room, and are finished already)
             const int64_t e = a + m, before = __shfl_up(e, 1, 64);
             const int64_t stop = (int64_t)((((uintptr_t)(reads + e) + 15) & ~(uintptr_t)15) - (uintptr_t)A0);
             const bool in = ((todo >> lane) & 1ull) != 0;
-            const bool ends_run = lane >= f && (!in || (lane > f && a != before) ||
+            const bool ends_run = lane >= f && ((lane > f && a != before) || (!in && e != a) ||
                                                 stop > (int64_t)(kStagePieces - filled) * 16);
             const uint64_t cut = wave_ballot(ends_run);
             const int end = cut ? __ffsll((unsigned long long)cut) - 1 : 64;
@@ -1798,7 +1799,7 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(COUNT ? 1 
             if (lane >= f && lane < end) at = 16u * (uint32_t)filled + (uint32_t)((uintptr_t)(reads + a) - (uintptr_t)A0);
             any_bad |= stage_pieces(reinterpret_cast<const uint4 *>(A0), np, w.codes + 1 + filled, w.bad, filled, lane, cnt);
             const uint64_t run = (end == 64 ? ~0ull : (1ull << end) - 1ull) & ~((1ull << f) - 1ull);
-            staged |= run;
+            staged |= run & todo;
             todo &= ~run;
             filled += np;
         }
