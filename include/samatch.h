@@ -107,8 +107,8 @@ void sa_free(sa_index *ix);                           /* NULL is a no-op        
  * whose suffix is not below v with the bracket of rows that start with v,
  * or the result of the reads that start with v when there are none (4^k + 1
  * entries of 16 bytes; see sa_set_prefix_table).  A shorter text gets a
- * table of at most 1 MiB of its own, which batches in input order start
- * from whatever their settings.  The host index may be freed afterwards.  Released with sa_dfree (NULL is a no-op). */
+ * table of at most 1 MiB of its own (see sa_match_cfg).  The host index may
+ * be freed afterwards.  Released with sa_dfree (NULL is a no-op). */
 int sa_upload(const sa_index *ix, int device, sa_dindex **out);
 void sa_dfree(sa_dindex *d);
 
@@ -180,7 +180,9 @@ typedef struct {
                             ascending; the last bucket takes every longer read   */
     int sort;            /* tuned: sort reads by prefix first: 1 = on the top 8, 16
                             or 24 prefix bits, the fewest with 2^bits >= reads/64;
-                            8, 16 or 24 = on that many bits; 0 = input order     */
+                            8, 16 or 24 = on that many bits; 0 = input order.
+                            With inline_pack and a text below 4096 bases a batch
+                            is searched in input order whatever this says        */
     int use_graph;       /* 1 = match_batch_dev replays the batch's launch sequence
                             as a hipGraph captured on first use for the same
                             buffers, size and settings (not on the null stream;
@@ -193,7 +195,9 @@ typedef struct {
     int group;           /* tuned: 64-read chunks per block of the work split
                             (1..64): workgroup rank r takes blocks r, r+G, ... */
     int prefix_table;    /* tuned: 1 = start each search from the prefix table
-                            (when the index has one), 0 = from the LDS tile     */
+                            (when the index has one), 0 = from the LDS tile; a
+                            text below 4096 bases has a small table that every
+                            search with inline packing starts from              */
     int inline_pack;     /* tuned, reads in input order (sort 0): 1 = the search
                             kernel converts its reads from ASCII itself (no
                             separate pack pass, one launch for the batch), when
@@ -228,8 +232,9 @@ int sa_default_cfg(const sa_dindex *d, sa_match_cfg *cfg);
  * 32 MiB of bytes or 2^19 reads each): the host copies one chunk in while the
  * device searches the one before, so the device sees each chunk as a batch
  * of its own (stage times and counts report the last chunk).  A chunk of at
- * most 4 MiB is not copied to the device: the kernels read it from the
- * pinned staging and write the results there.
+ * most 4 MiB (reads, offsets and results) is not copied to the device when
+ * the search kernel packs it itself: that reads it from the pinned staging
+ * and writes the results there.
  * Thread-safe for distinct streams. */
 int match_batch(const sa_dindex *d, const char *reads, const int64_t *offs, int64_t nreads,
                 sa_hit *out, void *hip_stream, const sa_match_cfg *cfg);
@@ -249,9 +254,10 @@ int match_batch_dev(const sa_dindex *d, const uint8_t *d_reads, const int64_t *d
  * results, but its scratch comes from one fixed array of
  * SA_NOALLOC_SCRATCH_BYTES per device, set aside when the library is loaded
  * and kept until the process ends, and it calls no allocating routine.  Its
- * size bounds the batch only on the path with a pack pass (cfg.sort != 0,
- * the plain kernel, or inline_pack = 0): sa_noalloc_max_reads(1) reads;
- * inline packing (the default with a prefix table) needs a few counters
+ * size bounds the batch only on the path with a pack pass (cfg.sort != 0
+ * for a text of at least 4096 bases, the plain kernel, or no inline
+ * packing): sa_noalloc_max_reads(1) reads; inline packing (the default with
+ * a prefix table and for texts below 4096 bases) needs a few counters
  * whatever the batch size (sa_noalloc_max_reads(0)).  A larger batch ->
  * SA_ENOSPC before any work.  cfg.use_graph is ignored (launches go to the
  * stream directly); cfg.profile and cfg.count -> SA_EINVAL.  Every call on

@@ -104,7 +104,7 @@ extern "C" int match_batch_dev_noalloc(const sa_dindex *dc, const uint8_t *d_rea
     if (!g.ok) return fail(SA_EDEVICE, "hipSetDevice failed");
     unsigned char *base = nullptr;
     if ((rc = scratch_for(d->device, &base))) return rc;
-    const bool pack_pass = !packs_inline(c);
+    const bool pack_pass = !searches_inline(d, c);  // as enqueue_pipeline has it
     const size_t need = layout(nreads, pack_pass, nullptr, nullptr);
     if (need > kScratchBytes)
         return fail(SA_ENOSPC, "batch of " + std::to_string(nreads) + " reads needs " + std::to_string(need) +
