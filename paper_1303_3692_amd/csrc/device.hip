@@ -471,8 +471,7 @@ int make_dindex(int device, int64_t n, const uint64_t *packed, const int32_t *ho
     if ((e = take_table()) != hipSuccess) return hip_fail(e, "prefix table allocation");
     if ((e = launch_build_rows(d->d_text, d->d_sa, (int32_t)n, d->d_rows, nullptr)) != hipSuccess ||
         (e = launch_build_tile(d->d_text, d->d_sa, (int32_t)n, d->tile_levels, d->d_tile_key, d->d_tile_sa,
-                               nullptr)) != hipSuccess ||
-        (k == 0 && (e = hipDeviceSynchronize()) != hipSuccess))
+                               nullptr)) != hipSuccess)
         return hip_fail(e, "tile build");
     DevIndex v{};
     v.text = d->d_text;
