@@ -51,7 +51,7 @@ def log(*a):
 
 def kernel_source_hash() -> str:
     h = hashlib.sha256()
-    for f in ("kernels.hip", "kernels.h", "radix_sort.h"):
+    for f in ("kernels.hip", "kernels.h", "split.h", "radix_sort.h"):
         h.update(open(os.path.join(ROOT, "paper_1303_3692_amd", "csrc", f), "rb").read())
     return h.hexdigest()[:16]
 

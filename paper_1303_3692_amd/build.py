@@ -47,7 +47,7 @@ def build_id() -> str:
     tuner): tuned launch settings are only reused for the same kernels."""
     import hashlib
     h = hashlib.sha256()
-    for s in ["kernels.hip", "kernels.h", "radix_sort.h", "device.hip", "device_state.h", "tune.hip"]:
+    for s in ["kernels.hip", "kernels.h", "split.h", "radix_sort.h", "device.hip", "device_state.h", "tune.hip"]:
         h.update(open(os.path.join(CSRC, s), "rb").read())
     return h.hexdigest()[:12]
 

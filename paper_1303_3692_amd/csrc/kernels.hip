@@ -20,6 +20,7 @@
 #include "kernels.h"
 #include "pivot.h"
 #include "radix_sort.h"
+#include "split.h"
 
 namespace samatch {
 namespace {
@@ -2348,31 +2349,10 @@ hipError_t launch_search_reads(const DevIndex &ix, int levels, int use_table, in
     const InlineArea area = inline_area(tile ? levels : 0);
     const size_t lds = inline_lds_bytes(area, block);
     if (lds > limit) return hipErrorInvalidValue;
-    // Persistent workgroups, no more than there are chunks for.  A batch too
-    // small to give half of the waves a chunk of 64 reads is cut into smaller
-    // chunks, down to one read: a wave's time grows with its longest search
-    // and with the bytes it stages, so few reads a wave are done sooner (64
-    // reads of 30-300 bases: 8 us as 64 chunks, 18 as one).  For all waves
-    // rather than half, launching them costs more than their smaller chunks
-    // save (100,000 reads of 25 bases: 13.0 against 10.0 us).
-    // A larger one is cut evenly: into as many reads a chunk as give every
-    // wave the same number of chunks, so that the last round of them is not
-    // nearly empty (4M reads: 11 rounds of 60 reads rather than 10 of 64 and
-    // a sixth of one).
-    const int64_t waves = (int64_t)cus * blocks_per_cu * (block / 64);
-    int per = 64;
-    while (per > 1 && nreads / per < waves / 2) per /= 2;
-    if (per == 64) {
-        const int64_t rounds = (nreads + 64 * waves - 1) / (64 * waves);
-        per = (int)((nreads + waves * rounds - 1) / (waves * rounds));
-    }
-    const int64_t chunks = (nreads + per - 1) / per;
-    const int64_t gmax = (int64_t)cus * blocks_per_cu, wg = block / 64;
-    group = (int)std::max<int64_t>(1, std::min<int64_t>(group, chunks / gmax));
-    const unsigned grid = (unsigned)std::min<int64_t>(gmax, (chunks + group * wg - 1) / (group * wg));
+    const SearchSplit sp = search_split(nreads, cus, blocks_per_cu, block / 64, group);
 #define SAMATCH_LAUNCH(C, T)                                                                                      \
-    hipLaunchKernelGGL((search_reads_kernel<C, T>), dim3(grid), dim3(block), lds, s, ix, levels, use_table, group, per, chunks, \
-                       defer, area, stats, reads, offs, ends, nreads, o)
+    hipLaunchKernelGGL((search_reads_kernel<C, T>), dim3(sp.grid), dim3(block), lds, s, ix, levels, use_table, sp.group, \
+                       sp.per, sp.chunks, defer, area, stats, reads, offs, ends, nreads, o)
     if (count) {
         if (tile) SAMATCH_LAUNCH(true, true);
         else SAMATCH_LAUNCH(true, false);
