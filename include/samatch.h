@@ -232,9 +232,9 @@ int sa_default_cfg(const sa_dindex *d, sa_match_cfg *cfg);
  * 32 MiB of bytes or 2^19 reads each): the host copies one chunk in while the
  * device searches the one before, so the device sees each chunk as a batch
  * of its own (stage times and counts report the last chunk).  A chunk of at
- * most 4 MiB (reads, offsets and results) is not copied to the device when
- * the search kernel packs it itself: that reads it from the pinned staging
- * and writes the results there.
+ * most 4 MiB (reads, offsets and results; with other calls under way on the
+ * device 2 MiB for all of them) is not copied there when the search kernel packs it itself: that
+ * reads it from the pinned staging and writes the results there.
  * Thread-safe for distinct streams. */
 int match_batch(const sa_dindex *d, const char *reads, const int64_t *offs, int64_t nreads,
                 sa_hit *out, void *hip_stream, const sa_match_cfg *cfg);

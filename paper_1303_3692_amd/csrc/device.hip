@@ -651,8 +651,22 @@ constexpr int64_t kHostChunkReads = (int64_t)1 << 19;
 // to the device and back: the search kernel reads and writes the pinned buffers
 // over the bus, each byte once, as a copy would (MI355X, 16 Mbp, reads of 150
 // bases: one 22 against 27 us, 1,000 34 against 43, 10,000 115 against 133,
-// 30,000 232 against 256; larger ones within 3 % either way).
-constexpr int64_t kDirectBytes = (int64_t)4 << 20;
+// 30,000 232 against 256; larger ones within 3 % either way).  Calls of
+// several threads share the bus, where kernels reach 39 GB/s and copies 53 in
+// either direction at once: while others are under way on the device, all of
+// them together may have kSharedBytes in place (8 threads, 20 batches each of
+// 20,000: 14.2 ms in place, 9.7 copied; 30 of 10,000: 13.6 and 8.8; 100 of
+// 1,000, in place, 17.5 where copies took 18.1).
+constexpr int64_t kDirectBytes = (int64_t)4 << 20, kSharedBytes = (int64_t)2 << 20;
+constexpr int kMaxDevices = 64;
+static std::atomic<int> g_host_batches[kMaxDevices];
+
+// Counts a call of match_batch while it is under way.
+struct HostBatch {
+    explicit HostBatch(int device) : n(g_host_batches[device % kMaxDevices]) { ++n; }
+    ~HostBatch() { --n; }
+    std::atomic<int> &n;
+};
 
 // memcpy split over a few threads (one copy thread moves ~10 GB/s; the
 // staging copies would otherwise bound a host batch below the bus rate).
@@ -702,6 +716,7 @@ extern "C" int match_batch(const sa_dindex *dc, const char *reads, const int64_t
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
     Workspace *ws = workspace_for(d, s);
     std::lock_guard<std::mutex> lk(ws->mu);
+    const HostBatch under_way(d->device);
     // chunks of whole reads, at most kHostChunkBytes of ASCII (or one read)
     // and kHostChunkReads reads each; chunk k uses slot k % 2, so the host
     // copies chunk k in (and chunk k - 2 out) while the device works on k - 1
@@ -739,7 +754,9 @@ extern "C" int match_batch(const sa_dindex *dc, const char *reads, const int64_t
         hipError_t e;
         // a small batch is read from the pinned buffers by the search kernel
         // itself, which writes its results there: one launch and no copies
-        const bool direct = kDirectBytes >= nb + (int64_t)(sizeof(int64_t) + sizeof(sa_hit)) * n && searches_inline(d, c);
+        const int64_t bytes = nb + (int64_t)(sizeof(int64_t) + sizeof(sa_hit)) * n;
+        const int calls = under_way.n.load();
+        const bool direct = bytes * calls <= (calls > 1 ? kSharedBytes : kDirectBytes) && searches_inline(d, c);
         if (!direct &&
             ((e = hipMemcpyAsync(hs.d_reads, hs.h_reads, (size_t)nb, hipMemcpyHostToDevice, s)) != hipSuccess ||
              (e = hipMemcpyAsync(hs.d_offs, hs.h_offs, sizeof(int64_t) * (size_t)(n + 1), hipMemcpyHostToDevice, s)) !=
