@@ -191,8 +191,8 @@ __host__ __device__ inline size_t tile_lds_bytes(int levels) {
 // Start of the per-wave packing areas after the tile (16-byte aligned).
 __host__ __device__ inline size_t inline_area_offset(int levels) { return (tile_lds_bytes(levels) + 15) & ~(size_t)15; }
 
-// search_reads_kernel.  Registers are held to six waves per SIMD (80, no
-// spills), and a wave's LDS area is sized so that 24 waves fit a compute
+// search_reads_kernel.  Registers are held to six waves per SIMD (80; no
+// spills, with the tile staged 22), and a wave's LDS area is sized so that 24 waves fit a compute
 // unit: what a wave waits for is memory latency, so more waves in flight
 // mean more of the memory's rate.  250 Mbp, 64M reads of 150 bases on
 // MI355X, with the kernel's first form: 5.52 ms at 16 waves, 5.16 at 24; held

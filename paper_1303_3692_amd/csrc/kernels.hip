@@ -117,7 +117,7 @@ __device__ __forceinline__ u64x2_a8 load_u64x2(const uint64_t *p) { return *rein
 // that are used again (the text, and the row records of repeats) rather than
 // prefix-table entries and ASCII reads, which a search touches once (on
 // MI355X this took the 250 Mbp / 64M-read batch from 6.47 to 5.93 ms; row
-// records loaded like that too made it 4.70 instead of 4.28 ms).
+// records loaded like that too: 4.69, through the caches 4.47 ms).
 __device__ __forceinline__ uint4 load_stream16(const void *p) {
     typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
     const u32x4 v = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(p));
@@ -603,7 +603,7 @@ __device__ __forceinline__ uint32_t first_row_from(const DevIndex &ix, int k, ui
 // groups; at most k - 1 suffixes are that short).  Bound by the table's
 // bytes: 16 Mbp (268 M entries, 4.3 GB) took 16.7 ms as a binary search per
 // entry for T and a second pass from the root for the strings without rows,
-// 1.9 ms now.
+// 1.3 ms now.
 constexpr int kTabThreads = 512;  // at most: a workgroup has no more threads than entries
 constexpr int kTabBases = 6;
 constexpr int kTabSpan = 1 << (2 * kTabBases);
@@ -948,8 +948,8 @@ __device__ __forceinline__ bool convert_piece(const uint4 &v, uint32_t *codes, u
 
 // The reference text, packed: one word (32 bases, two 16-byte loads) per
 // thread.  Bound by the text's bytes over the bus before it: the host checked
-// and packed 16 Mbp in 95 ms, one byte at a time; the device build takes
-// 23 ms in all where it took 122.
+// and packed 16 Mbp in 95 of the 122 ms that the device build took, one byte
+// at a time (with this and the steps after it the build takes 4.7).
 __global__ __launch_bounds__(256) void pack_text_kernel(const uint8_t *__restrict__ ascii, int64_t n,
                                                         uint64_t *__restrict__ text, int64_t words,
                                                         unsigned long long *__restrict__ first_bad) {
@@ -2338,9 +2338,9 @@ hipError_t launch_search_reads(const DevIndex &ix, int levels, int use_table, in
     if (inline_lds_bytes(inline_area(0), block) > limit) return hipErrorInvalidValue;
     // Without a prefix table every search starts at the root: stage the tile,
     // as deep as asked for while it does not cost a workgroup per compute
-    // unit its place (3,000 bases, 1M reads of 20-300 in three workgroups of
-    // 512 threads: 176 us with 8 levels, 226 with 10, which leave room for
-    // two).
+    // unit its place (MI355X, 4M reads of 100 bases on 16 Mbp in three
+    // workgroups of 512 threads: 1.18 ms with 8 levels, 1.39 with 10, which
+    // leave room for two).
     const bool tile = !(use_table && ix.ptab_k > 0);
     if (tile) {
         const size_t fit = std::min<size_t>((size_t)blocks_per_cu, limit / inline_lds_bytes(inline_area(0), block));

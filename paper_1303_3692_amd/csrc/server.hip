@@ -457,15 +457,12 @@ bool sa_server::launch(Slot &sl, std::unique_lock<std::mutex> &lk) {
     int rc;
     // the reads are in the arena, each request's back to back: the search
     // kernel packs them itself (coalesced, with the next chunk's loads in
-    // flight), under the deepest LDS tile that leaves room for its packing
-    // areas
+    // flight), which settings with a deep tile would not have it do
+    // (packs_inline); an index's own settings are never the plain kernel's
     sa_match_cfg c = resolve_cfg(d, nullptr);
-    if (c.kernel == SA_KERNEL_TUNED) {
-        c.sort = 0;
-        c.inline_pack = 1;
-        while (c.tile_levels > 1 && tuned_lds_bytes(c.tile_levels, c.block, c.max_words) > inline_lds_limit())
-            c.tile_levels--;
-    }
+    c.sort = 0;
+    c.inline_pack = 1;
+    while (c.tile_levels > 1 && !packs_inline(c)) c.tile_levels--;
     c.use_graph = 0;
     c.profile = o.measure >= 1 ? 1 : 0;  // stage events, read when the batch is reaped
     c.count = o.measure == 2 ? 1 : 0;
@@ -761,11 +758,10 @@ extern "C" int sa_server_create(const sa_dindex *const *refs, int nrefs, const s
                     (e = dev_malloc((void **)&sl.d_se, sizeof(int64_t) * 2 * (size_t)o.max_batch_reads)) != hipSuccess ||
                     (e = dev_malloc((void **)&sl.d_out, sizeof(sa_hit) * (size_t)o.max_batch_reads)) != hipSuccess)
                     return hip_fail(e, "slot allocation");
-                // every index's scratch for this stream now, not on the first batch (the
-                // tuned search takes its batches in input order and needs no packed arrays)
+                // every index's scratch for this stream now, not on the first batch (which is
+                // searched in input order and needs no packed arrays)
                 for (sa_dindex *d : s->refs) {
-                    const bool packs = resolve_cfg(d, nullptr).kernel != SA_KERNEL_TUNED;
-                    int rc = workspace_for(d, sl.stream)->reserve(o.max_batch_reads, packs);
+                    int rc = workspace_for(d, sl.stream)->reserve(o.max_batch_reads, false);
                     if (rc) return rc;
                 }
             }

@@ -165,9 +165,10 @@ sa_match_cfg base_cfg(const sa_dindex *d) {
 }
 
 // Stage 1: tile depth x workgroup shape.  With the prefix table the tile
-// serves only reads with a non-base among their first k bases, so its depth
-// changes little but the LDS it takes (and with it how many workgroups fit
-// a compute unit): three depths are tried instead of every one.
+// serves only reads with a non-base among their first k bases, from memory
+// when the search kernel packs the reads (its depth then changes nothing but
+// which settings that is, see packs_inline), and in a pack pass's search kernel
+// from LDS: three depths are tried instead of every one.
 std::vector<sa_match_cfg> stage1_candidates(const sa_dindex *d) {
     std::vector<int> levels;
     if (d->view.ptab_k > 0) {
