@@ -6,9 +6,9 @@
 #include <algorithm>
 #include <chrono>
 #include <condition_variable>
+#include <exception>
 #include <mutex>
 #include <new>
-#include <system_error>
 #include <thread>
 #include <unordered_map>
 #include <vector>
@@ -232,7 +232,7 @@ void dev_free(std::initializer_list<void *> ps) {
     try {
         k.watch = std::thread([&k] { k.run(); });
         k.watching = true;
-    } catch (const std::system_error &) {
+    } catch (const std::exception &) {
         k.release([&](const Block &b) { return b.device == device; });  // nobody would give them back
     }
 }
